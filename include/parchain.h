@@ -97,12 +97,16 @@ typedef struct {
                           kernels with HIP events on the call's stream (fills
                           the kernel_* stats); bit 1 (PC_TIME_PHASES): also
                           the rounds by phase (ms_nn, ms_merge, ms_update; 4
-                          more events and 3 host reads per round). 0: none */
+                          more events and 3 host reads per round; the pair
+                          matrix's build counts as nn and its sweeps, which
+                          update and search at once, as update). 0: none */
     int32_t cache_slots; /* cluster-pair distance cache (Alg. 4, Sec. 5):
                           capacity ~ cache_slots * n entries; -1 = default
                           (64 for average, 0 = off for complete, the paper's
                           settings; Ward and avg-2 values are O(1) from
-                          centroids and never use it) */
+                          centroids and never use it). With the default the
+                          late rounds of complete and average linkage may keep
+                          every pair's value in a matrix instead */
     int32_t reserved;
 } pc_options;
 
@@ -123,8 +127,9 @@ typedef struct {
      * search/evaluation kernels (HIP events around each launch) */
     double kernel_ms[4];      /* [0] search: ring search (bound pass), box-tree
                                  search or Gram pass 0; [1] block ring search,
-                                 full scan or interval tiles; [2] exact pair
-                                 tiles; [3] ring search (pair emission pass) or
+                                 full scan, interval tiles or pair-matrix
+                                 sweeps; [2] exact pair tiles or the pair
+                                 matrix's build; [3] ring search (pair emission pass) or
                                  Gram pass 1 with exact candidate values */
     int64_t kernel_launches[4];
     int64_t candidate_visits[4]; /* candidate clusters examined, per kernel above */
@@ -134,7 +139,8 @@ typedef struct {
     int64_t cache_derived;    /* pair values combined from cached parts
                                  (Lance-Williams rules, Table 2 / Sec. 5) */
     int64_t refined;          /* candidates the screening tiles could not rule
-                                 out, then given their exact FP64 value */
+                                 out, then given their exact FP64 value (the
+                                 pair matrix gives it to every pair) */
     int64_t fp64_fallbacks;   /* of those, the ones beyond one per screened
                                  chain tail: FP64 work owed to the tiles'
                                  error bounds */

@@ -193,6 +193,7 @@ hipError_t scratch_address(int dev, void **out) {
 // between calls) or windows of the static scratch array (fixed: never grown).
 struct Bufs {
   Buf ws, pairs, tiles, part, fidx, cand, cache[2];
+  Buf mat;  // pair-matrix rounds (a fixed window overlaps the records, which are dead by then)
   bool fixed = false;
 };
 
@@ -202,6 +203,7 @@ struct pc_context {
   int device = 0;
   size_t budget = 0;         // most device bytes the context may hold (0: no limit)
   bool over_budget = false;  // the last call stopped at the budget
+  bool mat_used = false;     // the running call uses the pair matrix
   Bufs own;
   Bufs *cur = &own;          // the buffers of the running call
   void *scratch = nullptr;   // this device's static scratch array (device address)
@@ -218,7 +220,7 @@ namespace {
 size_t held_bytes(const pc_context *c) {
   const Bufs &o = c->own;
   size_t b = o.ws.bytes + o.pairs.bytes + o.tiles.bytes + o.part.bytes + o.fidx.bytes + o.cand.bytes;
-  return b + o.cache[0].bytes + o.cache[1].bytes;
+  return b + o.cache[0].bytes + o.cache[1].bytes + o.mat.bytes;
 }
 
 // can b hold `bytes`, growing within the context's budget if need be?
@@ -227,7 +229,9 @@ bool fits(const pc_context *c, const Buf &b, size_t bytes) {
   if (b.bytes >= bytes) return true;
   if (c->cur->fixed) return false;
   if (!c->budget) return true;
-  return held_bytes(c) - b.bytes + bytes <= c->budget;
+  // (a matrix kept from an earlier call is given back first, see grow)
+  const size_t idle = &b != &c->own.mat && !c->mat_used ? c->own.mat.bytes : 0;
+  return held_bytes(c) - b.bytes - idle + bytes <= c->budget;
 }
 
 hipError_t grow(pc_context *c, Buf &b, size_t bytes) {
@@ -235,6 +239,12 @@ hipError_t grow(pc_context *c, Buf &b, size_t bytes) {
   if (!fits(c, b, bytes)) {
     c->over_budget = true;  // b is left as it was
     return hipErrorOutOfMemory;
+  }
+  Buf &m = c->own.mat;
+  if (c->budget && &b != &m && !c->mat_used && held_bytes(c) - b.bytes + bytes > c->budget) {
+    if (m.p) hipFree(m.p);
+    m.p = nullptr;
+    m.bytes = 0;
   }
   if (b.p) hipFree(b.p);
   b.p = nullptr;
@@ -305,7 +315,7 @@ int context_device(const pc_context *c) { return c->device; }
 void context_trim(pc_context *c) {
   hipSetDevice(c->device);
   Bufs &o = c->own;
-  for (Buf *b : {&o.ws, &o.pairs, &o.tiles, &o.part, &o.fidx, &o.cand, &o.cache[0], &o.cache[1]}) {
+  for (Buf *b : {&o.ws, &o.pairs, &o.tiles, &o.part, &o.fidx, &o.cand, &o.cache[0], &o.cache[1], &o.mat}) {
     if (b->p) hipFree(b->p);
     b->p = nullptr;
     b->bytes = 0;
@@ -320,7 +330,7 @@ void pc_context_destroy(pc_context *c) {
   hipSetDevice(c->device);
   hipDeviceSynchronize();
   Bufs &o = c->own;
-  for (Buf *b : {&o.ws, &o.pairs, &o.tiles, &o.part, &o.fidx, &o.cand, &o.cache[0], &o.cache[1]})
+  for (Buf *b : {&o.ws, &o.pairs, &o.tiles, &o.part, &o.fidx, &o.cand, &o.cache[0], &o.cache[1], &o.mat})
     if (b->p) hipFree(b->p);
   if (c->hcnt) hipHostFree(c->hcnt);
   for (int i = 0; i < 4; ++i)
@@ -467,6 +477,8 @@ static pc_status carve_scratch(char *base, size_t ws, int64_t n, int d, int link
     return fail(PC_ERR_OUT_OF_MEMORY, "input too large for the allocation-free scratch buffer");
   const size_t rest = total - off - 8 * 256;  // alignment slack of the windows below
   const bool gram = d >= kGramMinDim && d <= kGramMaxDim;
+  B.mat.p = base + off;  // the records below are dead once the pair matrix is built
+  B.mat.bytes = total - off;
   double fc = 0.0, fp = 0.0, ft = 0.0, ff = 0.0, fk = 0.0;  // shares of the rest
   if (centroid_link(linkage)) {
     fc = gram ? 1.0 : 0.0;
@@ -509,6 +521,61 @@ static long long initial_cap(const pc_context *ctx, const Buf &b, long long want
   return std::max<long long>(1, std::min(want, c));
 }
 
+// Largest number of active clusters that the pair matrix takes. Its sweeps
+// cost about 4 m^2 entries, so it pays once the searches of the rounds before
+// cost more than that: ring searches (d <= 3) are cheap down to few clusters,
+// Gram searches are dearer the higher d and the more points. Measured (whole
+// calls, complete / average, ms):
+//   24K points d = 2: 8192 clusters 4.0 / 4.0, 16384 4.8 / 4.7, all points 10.9 / 11.1
+//   24K points d = 10: 8192 11.3 / 11.3, 12288 9.8 / 10.1, all points 13.8 / 15.0
+//   200K points d = 5 complete: 8192 201, 16384 151, 32768 127
+//   24K points d = 64: 12288 19.9 / 27.8, 16384 18.2 / 22.6, all points 20.3 / 23.9
+//   50K points d = 128: 16384 72.8 / 139, 32768 63.5 / 71.1, 49152 70.9 / 73.1
+// Two matrices of 32768 clusters are 17 GB.
+static int matrix_max(int linkage, int d, int64_t n) {
+  int64_t m;
+  if (d <= 3) m = linkage == kAverage ? 12288 : 8192;
+  else if (d <= 16) m = std::max<int64_t>(12288, n / 6);
+  else m = std::max<int64_t>(16384, n * 3 / 4);
+  // complete linkage in the plane and in space searches rings faster than it
+  // builds a matrix of many points (65K points d = 2: 15.2 ms without, 8.7 with;
+  // 150K 19.4 / 15.4; 300K 22.8 / 31.5; d = 3 200K 93 / 35, 1M 965 / 363)
+  if (linkage == kComplete && d <= 2 && n > 150000) m = 0;
+  if (linkage == kComplete && d == 3 && n > 2000000) m = 0;
+  return (int)std::min<int64_t>(m, 32768);
+}
+
+// A tuning knob or test hook that pins the search of a call keeps it off the
+// pair matrix (as does an explicit cache_slots).
+static bool search_pinned() {
+  static const char *const knobs[] = {"PC_TREE_MAX_DIM", "PC_GRAM_MIN_DIM",    "PC_TREE_GRAM_SWITCH", "PC_CELL_BUDGET",
+                                      "PC_WAVE_TERMS",   "PC_WAVE_BUDGET",     "PC_FULL_SCAN_MAX",    "PC_TEST_CAND_CAP",
+                                      "PC_TEST_PAIR_CAP", "PC_TEST_CACHE_CAP", "PC_TEST_GRAM_BATCH"};
+  for (const char *k : knobs)
+    if (getenv(k)) return true;
+  return false;
+}
+
+// Room for the matrix of m clusters: false if it does not fit the budget, the
+// scratch window or the device (the call then goes on without it).
+static bool matrix_room(pc_context *ctx, Mx &X, int m, int n) {
+  const size_t need = mx_layout(X, nullptr, m, n);
+  Buf &b = ctx->cur->mat;
+  if (b.bytes < need) {
+    if (ctx->cur->fixed) return false;
+    size_t fr = 0, tot = 0;
+    if (hipMemGetInfo(&fr, &tot) != hipSuccess) return false;
+    if (need > (fr + b.bytes) / 2) return false;
+    if (!fits(ctx, b, need)) return false;
+    if (grow(ctx, b, need) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+  }
+  mx_layout(X, (char *)b.p, m, n);
+  return true;
+}
+
 static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32_t d, int points_on_device,
                           int32_t linkage, const pc_options *opt, pc_merge *out, int out_on_device, void *stream,
                           pc_stats *stats, bool noalloc) {
@@ -523,6 +590,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   if (stats && stats->struct_size != sizeof(pc_stats)) return fail(PC_ERR_INVALID_ARG, "pc_stats.struct_size");
   const int prune = opt ? (opt->prune != 0) : 1;
   int cache_slots = opt ? opt->cache_slots : -1;
+  const bool cache_default = cache_slots < 0;
   if (cache_slots < 0) cache_slots = linkage == kAverage ? 64 : 0;
   if (centroid_link(linkage)) cache_slots = 0;  // Ward / avg-2 values cost less than a probe
   const int elem = opt ? opt->precision : PC_PREC_FP16_REFINE;
@@ -551,6 +619,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   }
 
   ctx->over_budget = false;
+  ctx->mat_used = false;
   State S;
   memset(&S, 0, sizeof(S));
   const size_t need = layout(S, nullptr, n, d, linkage, !points_on_device, elem);
@@ -621,13 +690,27 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     pc_status st = grow_part(ctx, S, 2LL * n + 64);
     if (st != PC_OK) return st;
   }
+  // pair-matrix rounds (complete, average)
+  Mx X;
+  memset(&X, 0, sizeof(X));
+  bool direct = false;  // the matrix holds the points themselves
+  int mx_max = 0;       // enter with at most this many active clusters
+  if (prune && cache_default && !centroid_link(linkage) && !search_pinned()) {
+    mx_max = matrix_max(linkage, d, n);
+    if (const char *e = getenv("PC_MATRIX_MAX")) mx_max = std::max(0, atoi(e));
+    if (n <= mx_max) direct = matrix_room(ctx, X, (int)n, (int)n);
+  }
+  if (direct) {
+    ctx->mat_used = true;
+    cache_slots = 0;
+  }
   if (centroid_link(linkage) && gram_ok) {
     pc_status st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, std::max<long long>(1 << 22, 4 * n),
                                                  kCandBytes, 1024));
     if (st != PC_OK) return st;
     if (const char *e = getenv("PC_TEST_CAND_CAP")) S.cand_cap = std::min<long long>(S.cand_cap, atoll(e));
   }
-  if (!centroid_link(linkage)) {
+  if (!centroid_link(linkage) && !direct) {
     pc_status st = grow_pairs(ctx, S, initial_cap(ctx, ctx->cur->pairs, std::max<long long>(1 << 20, 2 * n),
                                                   kPairBytes, 1024));
     if (st != PC_OK) return st;
@@ -674,7 +757,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     HIPCHK(hipStreamSynchronize(s));
     if (ctx->hcnt->nonfinite) return fail(PC_ERR_NONFINITE_INPUT, "non-finite coordinate");
   }
-  launch_init(S, xdev, s);
+  if (!direct) launch_init(S, xdev, s);
   HIPCHK(hipGetLastError());
   HIPCHK(hipEventRecord(ctx->ev[1], s));
 
@@ -706,6 +789,45 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   Counters &h = *ctx->hcnt;
   while (nact > 1) {
     if (rounds > n) return fail(PC_ERR_DEVICE, "round loop did not converge");
+    if (!direct && nact <= mx_max) {
+      if (matrix_room(ctx, X, nact, (int)n)) ctx->mat_used = true;
+      else mx_max = nact * 3 / 4;  // less room than that: try again later
+    }
+    if (ctx->mat_used) {
+      // the remaining rounds; launches are queued several rounds at a time
+      if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
+      launch_mx_enter(S, X, nact, merges, direct, s);
+      HIPCHK(hipGetLastError());
+      if (S.phases) HIPCHK(hipEventRecord(ctx->rev[1], s));
+      while (nact > 1) {
+        const int batch = S.phases ? 1 : (nact > 4096 ? 6 : (nact > 512 ? 12 : 24));
+        for (int r = 0; r < batch; ++r) {
+          if (S.phases) HIPCHK(hipEventRecord(ctx->rev[2], s));
+          launch_mx_book(S, X, s);
+          if (S.phases) HIPCHK(hipEventRecord(ctx->rev[3], s));
+          launch_mx_pass(S, X, nact, s);
+          HIPCHK(hipGetLastError());
+        }
+        if (S.phases) HIPCHK(hipEventRecord(ctx->ev[2], s));
+        HIPCHK(hipMemcpyAsync(&h, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        take_times();
+        if (h.mx_err == 1) return fail(PC_ERR_DEVICE, "a cluster found no neighbour");
+        if (h.mx_err) return fail(PC_ERR_DEVICE, "round merged nothing");
+        if (S.phases) {
+          float a = 0.f, b = 0.f, c = 0.f;
+          if (nact == X.cap && hipEventElapsedTime(&a, ctx->rev[0], ctx->rev[1]) == hipSuccess) ms_nn += a;
+          if (hipEventElapsedTime(&b, ctx->rev[2], ctx->rev[3]) == hipSuccess) ms_merge += b;
+          if (hipEventElapsedTime(&c, ctx->rev[3], ctx->ev[2]) == hipSuccess) ms_update += c;
+        }
+        if (debug) fprintf(stderr, "[parchain] matrix rounds %d: nact %d\n", h.mx_rounds, h.n_act);
+        nact = h.n_act;
+      }
+      merges = h.mx_merges;
+      rounds += h.mx_rounds;
+      terms += h.mx_terms;
+      break;
+    }
     if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
     if (tree_ok) {
       const bool use_tree = !gram_ok || tree_gram_switch <= 0 || nact > tree_gram_switch;

@@ -142,6 +142,14 @@ struct Counters {
   int n_scr32;
   int scan_err;        // a prefix scan's look-back gave up (see ScanWs)
   long long refined;   // screened candidates given an exact FP64 value
+  // pair-matrix rounds (pc_matrix.hip)
+  int mx_old;      // clusters before the round's merges
+  int mx_merged;   // merges of the round
+  int mx_merges;   // merges of the call so far
+  int mx_rounds;   // rounds run
+  int mx_err;      // 1: a cluster without a neighbour, 2: a round merged nothing
+  int mx_pad;
+  long long mx_terms;  // clusters whose neighbour was searched, summed over the rounds
 };
 
 // Workspace of the single-pass prefix scans (decoupled look-back): two status
@@ -188,6 +196,26 @@ struct KTimer {
   }
   void commit() { kept = done.size(); }
   void drop() { done.resize(kept); }
+};
+
+// Pair-matrix rounds (pc_matrix.hip): per-cluster records of one round, in
+// active-list order.
+struct MxClusters {
+  int4 *id;       // cluster ID, size, node, 0
+  double *eff;    // largest height in the subtree
+  double *rsize;  // 1 / size
+};
+struct Mx {
+  int cap;          // clusters at entry
+  double *k[2];     // pair values (both halves, infinity on the diagonal), this round's and the next one's
+  MxClusters c[2];
+  int2 *src;        // a new cluster's sources in the old records (y: -1 if unmerged)
+  int *place;       // an old cluster's place in the new records if it was not merged, else -1
+  int *beg;         // first point position of a cluster at entry
+  int *own;         // cluster of every point position at entry
+  double *nnv[2];   // nearest neighbour: key and place
+  int *nni[2];
+  int cur;          // host: the buffer that holds the current round
 };
 
 // All device arrays of one clustering call. Slots are storage indices of
@@ -325,6 +353,29 @@ struct State {
 
 };
 
+// Heights: complete and Ward keys are squared distances; average and avg-2
+// keys are the heights themselves.
+__device__ __forceinline__ double key_to_height(int link, double v) {
+  return (link == kAverage || link == kAvgSq) ? v : sqrt(v);
+}
+
+// start / end event of a timed launch of slot k (nothing unless the call times its kernels)
+inline void tmark(State &S, int k, bool end, hipStream_t s) {
+  if (!S.timing) return;
+  KTimer &t = *S.kt;
+  int idx;
+  if (t.take(idx) != hipSuccess) return;  // (no event: this launch goes untimed)
+  (void)hipEventRecord(t.pool[idx], s);
+  if (!end) {
+    t.open[k] = idx;
+  } else if (t.open[k] >= 0) {
+    t.done.push_back(k);
+    t.done.push_back(t.open[k]);
+    t.done.push_back(idx);
+    t.open[k] = -1;
+  }
+}
+
 // ------------------------------------------------------ launch wrappers ----
 // primitives (pc_prims.hip)
 // the scan workspace over `words` long longs at `base`
@@ -356,5 +407,14 @@ void launch_pairs(State &S, int round, int npairs_host, long long ntiles_host, h
 void launch_pairs_prefix(State &S, int npairs_host, hipStream_t s);
 void launch_round_tail(State &S, int round, int nact_host, int merges_before, hipStream_t s);
 void launch_finalize(State &S, void *out_rows, hipStream_t s);
+
+// pair-matrix rounds (pc_matrix.hip)
+// carves the arrays for m clusters of n points out of `base` (or counts bytes)
+size_t mx_layout(Mx &X, char *base, int m, int n);
+// records, matrix and nearest neighbours of the m active clusters (direct:
+// of the n input points themselves)
+void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s);
+void launch_mx_book(State &S, Mx &X, hipStream_t s);
+void launch_mx_pass(State &S, Mx &X, int bound, hipStream_t s);
 
 }  // namespace pc

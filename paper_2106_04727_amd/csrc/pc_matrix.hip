@@ -1,0 +1,726 @@
+// Pair-matrix rounds: once few enough clusters are active, every cluster
+// pair's value is kept in a dense FP64 matrix and the remaining rounds of
+// Alg. 1 run on it.
+//
+//   build    exact values of all active pairs from the points: every point
+//            pair once (complete: the largest squared distance; average: the
+//            sum of the distances)
+//   pass     one sweep per round: the merged clusters' rows and columns are
+//            combined by the Lance-Williams rules of Table 2 (complete: the
+//            maximum, average: the sum), the matrix is compacted into the
+//            other buffer, and every row's nearest neighbour is found on the
+//            way
+//   book     one block: reciprocal pairs, rows of the dendrogram, the next
+//            round's cluster records
+//
+// No round waits for the host: the launches of several rounds are queued at
+// once and kernels of rounds that are not needed any more exit at once.
+//
+// Both halves of the matrix are kept, bit for bit equal: a row is then read
+// in one contiguous sweep, and a value does not depend on which side asks.
+#include <float.h>
+#include <math.h>
+
+#include <algorithm>
+
+#include "pc_common.hpp"
+
+namespace pc {
+
+namespace {
+
+constexpr int kWin = 64;          // points per window of the build (rows and columns)
+constexpr int kBookThreads = 1024;
+constexpr int kBookItems = 4;
+
+// row stride of a matrix of n clusters: an odd number of 256-byte segments,
+// so that the same column of successive rows falls on different channels
+__host__ __device__ __forceinline__ long long mx_ld(int n) { return (((long long)n + 31) / 32 | 1) * 32; }
+
+__device__ __forceinline__ int wave_max_i(int v) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
+  return v;
+}
+
+// Average: every squared distance starts from kTiny, which keeps the
+// reciprocal root finite at distance zero. Float distances are zero or at least
+// 2^-149, so kTiny changes no other value, and a sum below kZero is one of
+// roots of kTiny: zero.
+constexpr double kTiny = 1e-300, kZero = 1e-120;
+
+// Square root of a positive double for the sums of average linkage:
+// hardware reciprocal root, then Goldschmidt's coupled iteration and one
+// residual correction (Markstein). No scaling: x is at least kTiny and below
+// 2^260.
+__device__ __forceinline__ double root_sum(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  const double e = __builtin_fma(-g, g, x);
+  return __builtin_fma(e, h, g);
+}
+
+// a cluster whose points do not lie in one window: several tiles add to its entries
+__device__ __forceinline__ bool straddles(int beg, int size) { return beg / kWin != (beg + size - 1) / kWin; }
+
+template <int LINK>
+__device__ __forceinline__ void put(double *p, double v, bool shared) {
+  if (!shared) *p = v;
+  else if (LINK == kComplete) atomicMax((unsigned long long *)p, pos_bits(v));
+  else unsafeAtomicAdd(p, v);
+}
+
+// ------------------------------------------------------------------ enter --
+// Cluster records of the active list (from slots, or of single points).
+__global__ void k_mx_enter(State S, Mx X, int merges, int direct) {
+  const int n = S.n;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S.cnt->mx_merges = merges;
+    const long long m = direct ? n : S.cnt->n_act;
+    // every pair's exact value is computed from all its point pairs
+    S.cnt->cluster_evals += m * (m - 1) / 2;
+    S.cnt->refined += m * (m - 1) / 2;
+    S.cnt->point_pairs += (long long)n * (n - 1) / 2;
+    S.cnt->visits[1] += m * (m - 1);
+  }
+  if (direct) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+      X.c[0].id[i] = make_int4(i, 1, i, 0);
+      X.c[0].eff[i] = 0.0;
+      X.c[0].rsize[i] = 1.0;
+      X.beg[i] = i;
+      X.own[i] = i;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) S.cnt->n_act = n;
+    return;
+  }
+  const int nact = S.cnt->n_act;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x) {
+    const int s = S.act[i];
+    X.c[0].id[i] = make_int4(S.cid[s], S.csize[s], S.node[s], 0);
+    X.c[0].eff[i] = S.eff[s];
+    X.c[0].rsize[i] = 1.0 / (double)S.csize[s];
+    X.beg[i] = S.cbeg[s];
+    S.mdst[s] = i;  // slot -> place in the active list
+  }
+}
+// cluster of every point position (points lie in active-list order)
+__global__ void k_mx_own(State S, Mx X) {
+  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < S.n; p += gridDim.x * blockDim.x)
+    X.own[p] = S.mdst[S.powner[p]];
+}
+
+// entries that several tiles add to start at zero
+__global__ __launch_bounds__(kBlock) void k_mx_zero(Mx X, int m) {
+  const long long ld = mx_ld(m);
+  for (int i = blockIdx.x; i < m; i += gridDim.x) {
+    const bool all = straddles(X.beg[i], X.c[0].id[i].y);
+    for (int j = i + 1 + threadIdx.x; j < m; j += kBlock)
+      if (all || straddles(X.beg[j], X.c[0].id[j].y)) X.k[0][i * ld + j] = 0.0;
+  }
+}
+
+// ------------------------------------------------------------------ build --
+// Values of all cluster pairs, upper half, d <= 16. A block stages 64 row
+// points in LDS as FP64; each wavefront takes two windows of 64 column points
+// at a time, a column point of each per lane, and walks the rows. At the last
+// row of a cluster the lanes' sums (maxima) go to LDS; after kHold of them the
+// wavefront adds up the columns of every column cluster, a (row cluster,
+// column cluster) pair per lane, and stores one value per pair. Pairs with a
+// cluster that reaches into another window are added (maximised) in memory.
+// Bound by the FP64 vector units: d subtractions and fused multiply-adds, the
+// root (7 and the hardware's reciprocal root) and the sum per point pair. All
+// loads are amortised over 64 rows.
+constexpr int kHold = 8;
+template <int LINK, int MAXD>
+__global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, int n, int d, int m, int group) {
+  __shared__ __attribute__((aligned(16))) double rows[kWin][MAXD];
+  __shared__ int rown[kWin];
+  __shared__ double held[kBlock / kWave][kHold][2 * kWin];
+  __shared__ int heldr[kBlock / kWave][kHold];
+  __shared__ int sown[kBlock / kWave][2 * kWin];             // column clusters: owner,
+  __shared__ unsigned char sbeg[kBlock / kWave][2 * kWin];   // first column,
+  __shared__ unsigned char send[kBlock / kWave][2 * kWin];   // last column, top bit
+                                                             // set if shared
+  const int nwin = (n + kWin - 1) / kWin;
+  const int I = blockIdx.x;
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int r0 = I * kWin, nrow = min(kWin, n - r0);
+  const int pbeg = I / 2 + blockIdx.y * group;  // pairs of column windows
+  const int pend = min((nwin + 1) / 2, pbeg + group);
+  if (pbeg >= pend) return;  // uniform per block
+  for (int t = threadIdx.x; t < kWin * MAXD; t += kBlock) {
+    const int i = t / MAXD, k = t % MAXD;
+    rows[i][k] = i < nrow && k < d ? (double)px[(size_t)(r0 + i) * d + k] : 0.0;
+  }
+  if (threadIdx.x < kWin) rown[threadIdx.x] = threadIdx.x < nrow ? X.own[r0 + threadIdx.x] : -1;
+  __syncthreads();
+  // rows that end a cluster within this window
+  const int ro = rown[lane];
+  const int rnext = lane + 1 < nrow ? rown[lane + 1] : -1;
+  const unsigned long long ends = __ballot(lane < nrow && ro != rnext);
+  const bool row_in = r0 > 0 && X.own[r0 - 1] == rown[0];                    // first row's cluster began earlier
+  const bool row_out = r0 + nrow < n && X.own[r0 + nrow] == rown[nrow - 1];  // last row's cluster goes on
+  const int rfirst = rown[0], rlast = rown[nrow - 1];
+  const long long ld = mx_ld(m);
+  double *K = X.k[0];
+  const double q0 = LINK == kAverage ? kTiny : 0.0;
+  for (int P = pbeg + w; P < pend; P += kBlock / kWave) {
+    double cv[2][MAXD];
+    int oc[2];
+    bool cshared[2];  // this lane's column cluster reaches into another window
+    int nseg = 0, ncol = 0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int J = 2 * P + c;
+      const int pos = J * kWin + lane;
+      const bool in = J >= I && pos < n;
+      oc[c] = in ? X.own[pos] : -1;
+#pragma unroll
+      for (int k = 0; k < MAXD; ++k) cv[c][k] = in && k < d ? (double)px[(size_t)pos * d + k] : 0.0;
+      const int prev = in && pos > 0 ? X.own[pos - 1] : -2;
+      const int next = in && pos + 1 < n ? X.own[pos + 1] : -2;
+      const bool head = in && (lane == 0 || prev != oc[c]);
+      const bool tail = in && (lane == kWave - 1 || next != oc[c]);
+      const unsigned long long heads = __ballot(head);
+      const int w0 = J * kWin;
+      cshared[c] = in && ((w0 > 0 && X.own[w0 - 1] == oc[c]) || (w0 + kWin < n && X.own[w0 + kWin] == oc[c]));
+      const int k = nseg + __popcll(heads & lanemask_lt()) - (head ? 0 : 1);
+      if (head) {
+        sown[w][k] = oc[c];
+        sbeg[w][k] = (unsigned char)(c * kWin + lane);
+      }
+      if (tail) send[w][k] = (unsigned char)((c * kWin + lane) | (cshared[c] ? 0x80 : 0));
+      nseg += __popcll(heads);
+      ncol += __popcll(__ballot(in));
+    }
+    if (nseg == 0) continue;
+    const bool points = nseg == ncol;  // every column cluster here is one point
+    double acc[2] = {0.0, 0.0};
+    int hold = 0;
+    for (int r = 0; r < nrow; ++r) {
+      double q[2] = {q0, q0};
+#pragma unroll
+      for (int k = 0; k < MAXD; ++k) {
+        const double a = rows[r][k];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const double u = a - cv[c][k];
+          if (LINK == kComplete) q[c] += u * u;  // as the oracle sums: bit-identical maxima
+          else q[c] = __builtin_fma(u, u, q[c]);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (LINK == kComplete) acc[c] = q[c] > acc[c] ? q[c] : acc[c];
+        else acc[c] += root_sum(q[c]);
+      }
+      if (!((ends >> r) & 1ull)) continue;  // uniform
+      if (points) {
+        const int ri = __builtin_amdgcn_readfirstlane(rown[r]);
+        const bool rs = (row_in && ri == rfirst) || (row_out && ri == rlast);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          if (ri < oc[c])
+            put<LINK>(K + (size_t)ri * ld + oc[c], LINK == kAverage && acc[c] < kZero ? 0.0 : acc[c], rs || cshared[c]);
+      } else {
+        held[w][hold][lane] = acc[0];
+        held[w][hold][kWin + lane] = acc[1];
+        if (lane == 0) heldr[w][hold] = rown[r];
+        if (++hold == kHold || (ends >> r) == 1ull) {
+          // (a wavefront's LDS operations complete in order)
+          for (int t = lane; t < hold * nseg; t += kWave) {
+            const int h = t / nseg, k = t - h * nseg;
+            const int e = send[w][k] & 0x7f;
+            double x = held[w][h][sbeg[w][k]];
+            for (int c = sbeg[w][k] + 1; c <= e; ++c) {
+              const double y = held[w][h][c];
+              x = LINK == kComplete ? (y > x ? y : x) : x + y;
+            }
+            const int ri = heldr[w][h], ci = sown[w][k];
+            if (ri < ci)
+              put<LINK>(K + (size_t)ri * ld + ci, LINK == kAverage && x < kZero ? 0.0 : x,
+                        (row_in && ri == rfirst) || (row_out && ri == rlast) || (send[w][k] & 0x80));
+          }
+          hold = 0;
+        }
+      }
+      acc[0] = acc[1] = 0.0;
+    }
+  }
+}
+
+// The same for d > 16: 64 x 64 tiles, each thread a 4 x 4 block, coordinates
+// staged 16 at a time; the tile's values go through LDS, where the rows and
+// columns of each cluster are combined.
+constexpr int kKc = 16;
+template <int LINK>
+__global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, int n, int d, int m, int group) {
+  __shared__ __attribute__((aligned(16))) float As[kKc][kWin + 4];
+  __shared__ __attribute__((aligned(16))) float Bs[kKc][kWin + 4];
+  __shared__ double tile[kWin][kWin + 1];
+  __shared__ int rown[kWin + 2], cown[kWin + 2];  // with the neighbours outside the window
+  const int nwin = (n + kWin - 1) / kWin;
+  const int I = blockIdx.x;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int r0 = I * kWin, nrow = min(kWin, n - r0);
+  const int jbeg = I + blockIdx.y * group, jend = min(nwin, jbeg + group);
+  const long long ld = mx_ld(m);
+  double *K = X.k[0];
+  for (int J = jbeg; J < jend; ++J) {
+    const int c0 = J * kWin, ncol = min(kWin, n - c0);
+    __syncthreads();
+    for (int t = threadIdx.x; t < kWin + 2; t += kBlock) {
+      const int pr = r0 + t - 1, pc = c0 + t - 1;
+      rown[t] = pr >= 0 && pr < n ? X.own[pr] : -1;
+      cown[t] = pc >= 0 && pc < n ? X.own[pc] : -1;
+    }
+    double q[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) q[a][b] = LINK == kAverage ? kTiny : 0.0;
+    for (int k0 = 0; k0 < d; k0 += kKc) {
+      const int kc = min(kKc, d - k0);
+      __syncthreads();
+      for (int t = threadIdx.x; t < kWin * kKc; t += kBlock) {
+        const int i = t / kKc, k = t % kKc;
+        float a = 0.0f, b = 0.0f;
+        if (k < kc) {
+          if (i < nrow) a = px[(size_t)(r0 + i) * d + k0 + k];
+          if (i < ncol) b = px[(size_t)(c0 + i) * d + k0 + k];
+        }
+        As[k][i] = a;
+        Bs[k][i] = b;
+      }
+      __syncthreads();
+#pragma unroll 4
+      for (int k = 0; k < kKc; ++k) {
+        const float4 av = *(const float4 *)&As[k][ty * 4];
+        const float4 bv = *(const float4 *)&Bs[k][tx * 4];
+        const double ar[4] = {(double)av.x, (double)av.y, (double)av.z, (double)av.w};
+        const double br[4] = {(double)bv.x, (double)bv.y, (double)bv.z, (double)bv.w};
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const double u = ar[a] - br[b];
+            if (LINK == kComplete) q[a][b] += u * u;
+            else q[a][b] = __builtin_fma(u, u, q[a][b]);
+          }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) tile[ty * 4 + a][tx * 4 + b] = LINK == kComplete ? q[a][b] : root_sum(q[a][b]);
+    __syncthreads();
+    // columns of a cluster, row by row: the value lands in the cluster's last column
+    for (int t = threadIdx.x; t < kWin * kWin; t += kBlock) {
+      const int r = t / kWin, c = t % kWin;
+      if (r >= nrow || c >= ncol) continue;
+      const int o = cown[c + 1];
+      if (c + 1 < ncol && cown[c + 2] == o) continue;  // not its last column here
+      if (c > 0 && cown[c] == o) {
+        double v = tile[r][c];
+        for (int cc = c - 1; cc >= 0 && cown[cc + 1] == o; --cc) {
+          const double u = tile[r][cc];
+          v = LINK == kComplete ? (u > v ? u : v) : v + u;
+        }
+        tile[r][c] = v;
+      }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < kWin * kWin; t += kBlock) {
+      const int r = t / kWin, c = t % kWin;
+      if (r >= nrow || c >= ncol) continue;
+      const int o = cown[c + 1], ri = rown[r + 1];
+      if (c + 1 < ncol && cown[c + 2] == o) continue;
+      if (r + 1 < nrow && rown[r + 2] == ri) continue;  // not its last row here
+      if (ri >= o) continue;
+      double v = tile[r][c];
+      int rr = r - 1;
+      for (; rr >= 0 && rown[rr + 1] == ri; --rr) {
+        const double u = tile[rr][c];
+        v = LINK == kComplete ? (u > v ? u : v) : v + u;
+      }
+      // shared with a tile of another window: the cluster lies across an edge
+      const bool sh = (rown[0] == ri) || (r == nrow - 1 && rown[r + 2] == ri) || (cown[0] == o) ||
+                      (c == ncol - 1 && cown[c + 2] == o);
+      put<LINK>(K + (size_t)ri * ld + o, LINK == kAverage && v < kZero ? 0.0 : v, sh);
+    }
+  }
+}
+
+// lower half = upper half transposed, 64 x 64 tiles through LDS; infinity on
+// the diagonal
+__global__ __launch_bounds__(kBlock) void k_mx_mirror(Mx X, int m) {
+  __shared__ double t[kWin][kWin + 1];
+  const int I = blockIdx.x, J = blockIdx.y;
+  if (J < I) return;
+  const long long ld = mx_ld(m);
+  double *K = X.k[0];
+  const int r0 = I * kWin, c0 = J * kWin;
+  for (int j = threadIdx.x; j < kWin * kWin; j += kBlock) {
+    const int r = j / kWin, c = j % kWin;
+    if (r0 + r < m && c0 + c < m) t[r][c] = K[(size_t)(r0 + r) * ld + c0 + c];
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < kWin * kWin; j += kBlock) {
+    const int r = j / kWin, c = j % kWin;  // of the transposed tile
+    if (c0 + r < m && r0 + c < m && c0 + r >= r0 + c)
+      K[(size_t)(c0 + r) * ld + r0 + c] = c0 + r > r0 + c ? t[c][r] : INFINITY;
+  }
+}
+
+// ------------------------------------------------------------------- pass --
+struct Near {
+  double v;
+  int cid, q;
+};
+__device__ __forceinline__ void nearer(Near &b, double v, int cid, int q) {
+  if (v < b.v || (v == b.v && cid < b.cid)) {
+    b.v = v;
+    b.cid = cid;
+    b.q = q;
+  }
+}
+
+// FIRST: nearest neighbours of the matrix as built. Else one round: row p of
+// the new matrix from the rows and columns of its sources, and its nearest
+// neighbour (key, then cluster ID) unless that is known: an unmerged cluster
+// whose neighbour did not merge keeps it (merging brings no cluster nearer,
+// Sec. 2.1). TPR threads per row, four columns of a thread in flight; a column
+// index past the end repeats the last one, so no lane is masked. Average
+// linkage compares sums times 1/size first (the row's own size is common to
+// all) and divides only for a value that may win: the product and the quotient
+// differ by less than 2^-50.
+// Bound by memory: about (n_old^2 + n_new^2) * 8 bytes a round.
+template <int LINK, bool FIRST, bool NEAR>
+__device__ __forceinline__ void pass_row(const double *__restrict__ A, const double *__restrict__ B, bool two,
+                                         double *__restrict__ out, const int2 *__restrict__ src,
+                                         const double *__restrict__ rsize, const int4 *__restrict__ id, int p,
+                                         double sz, int nn, int t, int tpr, Near &b) {
+  constexpr int U = 4;
+  double lim = INFINITY;  // b.v, for average in units of the sums over size
+  for (int q0 = t; q0 < nn; q0 += U * tpr) {
+    double v[U], rs[U];
+    int2 c[U];
+    int q[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      q[j] = min(q0 + j * tpr, nn - 1);
+      if (!FIRST) c[j] = src[q[j]];
+      if (NEAR && LINK == kAverage) rs[j] = rsize[q[j]];
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = A[FIRST ? q[j] : c[j].x];
+    if (!FIRST) {
+      if (two) {  // uniform in the row: a merged cluster's
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const double x = B[c[j].x];
+          if (c[j].y < 0) {
+            v[j] = LINK == kComplete ? (x > v[j] ? x : v[j]) : v[j] + x;
+          } else {
+            const double y = A[c[j].y], z = B[c[j].y];
+            if (LINK == kComplete) {
+              const double m1 = x > v[j] ? x : v[j], m2 = z > y ? z : y;
+              v[j] = m1 > m2 ? m1 : m2;
+            } else {
+              // the same grouping on both sides of the diagonal
+              v[j] = p < q[j] ? (v[j] + x) + (y + z) : (v[j] + y) + (x + z);
+            }
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+          if (c[j].y >= 0) {
+            const double y = A[c[j].y];
+            v[j] = LINK == kComplete ? (y > v[j] ? y : v[j]) : v[j] + y;
+          }
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) out[q[j]] = v[j];
+    }
+    if (NEAR) {
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const double key = LINK == kAverage ? v[j] * rs[j] : v[j];
+        if (key <= lim) {
+          const int4 o = id[q[j]];
+          nearer(b, LINK == kAverage ? v[j] / (sz * (double)o.y) : v[j], o.x, q[j]);
+          lim = LINK == kAverage ? b.v * sz * (1.0 + 0x1p-49) : b.v;
+        }
+      }
+    }
+  }
+}
+
+template <int LINK, bool FIRST, int TPR>
+__global__ __launch_bounds__(kBlock) void k_mx_pass(Mx X, int src, const Counters *cnt) {
+  const int nn = cnt->n_act;
+  if (cnt->mx_err || (!FIRST && nn <= 1)) return;
+  const bool fresh = FIRST || cnt->mx_merged == 0;  // every cluster looks again, see k_mx_book
+  const int dst = FIRST ? src : src ^ 1;
+  const long long lo = mx_ld(FIRST ? nn : cnt->mx_old), ln = mx_ld(nn);
+  const MxClusters &C = X.c[dst];
+  const int t = threadIdx.x % TPR;
+  constexpr int RPB = kBlock / TPR;
+  __shared__ Near red[kBlock / kWave];
+  for (int p0 = blockIdx.x * RPB; p0 < nn; p0 += gridDim.x * RPB) {
+    // (uniform in a wavefront)
+    const int p = TPR == kBlock ? p0 : __builtin_amdgcn_readfirstlane(p0 + threadIdx.x / TPR);
+    if (TPR < kBlock && p >= nn) break;
+    int ra = p, rb = -1, old = -1;
+    if (!FIRST) {
+      const int2 c = X.src[p];
+      ra = c.x;
+      rb = c.y;
+      if (rb < 0 && !fresh) old = X.place[X.nni[src][ra]];
+    }
+    const double *A = X.k[src] + (size_t)ra * lo;
+    const double *B = X.k[src] + (size_t)(rb < 0 ? ra : rb) * lo;
+    double *out = X.k[dst] + (size_t)p * ln;
+    Near b{INFINITY, 0x7fffffff, -1};
+    if (old >= 0) {
+      pass_row<LINK, FIRST, false>(A, B, false, out, X.src, C.rsize, C.id, p, 0.0, nn, t, TPR, b);
+      if (t == 0) {
+        X.nnv[dst][p] = X.nnv[src][ra];
+        X.nni[dst][p] = old;
+      }
+      continue;
+    }
+    pass_row<LINK, FIRST, true>(A, B, rb >= 0, out, X.src, C.rsize, C.id, p, (double)C.id[p].y, nn, t, TPR, b);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      const double ov = __shfl_xor(b.v, o, kWave);
+      const int oc = __shfl_xor(b.cid, o, kWave), oq = __shfl_xor(b.q, o, kWave);
+      nearer(b, ov, oc, oq);
+    }
+    if (TPR > kWave) {
+      const int w = threadIdx.x / kWave;
+      if ((threadIdx.x & (kWave - 1)) == 0) red[w] = b;
+      __syncthreads();
+      if (threadIdx.x == 0)
+        for (int j = 1; j < kBlock / kWave; ++j) nearer(b, red[j].v, red[j].cid, red[j].q);
+      __syncthreads();
+    }
+    if (t == 0) {
+      X.nnv[dst][p] = b.v;
+      X.nni[dst][p] = b.q;
+    }
+  }
+}
+
+// ------------------------------------------------------------------- book --
+// One block, one round: the reciprocal pairs of the nearest neighbours found
+// by the last pass merge (Alg. 1), every cluster gets its place in the next
+// round's records, and the merges their dendrogram rows. Exact ties between a
+// kept neighbour and a new cluster can leave a round without a reciprocal pair;
+// then every cluster looks again, and the pair of the smallest value whose
+// lower ID is lowest is reciprocal.
+__global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src) {
+  Counters *cnt = S.cnt;
+  const int n = cnt->n_act;
+  if (n <= 1 || cnt->mx_err) return;  // uniform
+  __shared__ unsigned long long ws[kBookThreads / kWave + 1];
+  const MxClusters &O = X.c[src], &N = X.c[src ^ 1];
+  const int *nni = X.nni[src];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int base = cnt->mx_merges;
+  int kept = 0, merged = 0, bad = 0;
+  constexpr int kTileN = kBookThreads * kBookItems;
+  for (int b0 = 0; b0 < n; b0 += kTileN) {
+    int mate[kBookItems], part[kBookItems];
+    int4 id[kBookItems], idm[kBookItems];
+    double eff[kBookItems], effm[kBookItems];
+    unsigned long long cntv = 0;
+    // two dependent loads in all: the neighbour, then everything of both
+#pragma unroll
+    for (int j = 0; j < kBookItems; ++j) {
+      const int i = min(b0 + (int)threadIdx.x * kBookItems + j, n - 1);
+      mate[j] = nni[i];
+      id[j] = O.id[i];
+      eff[j] = O.eff[i];
+    }
+#pragma unroll
+    for (int j = 0; j < kBookItems; ++j) {
+      const int u = max(mate[j], 0);
+      part[j] = nni[u];
+      idm[j] = O.id[u];
+      effm[j] = O.eff[u];
+    }
+#pragma unroll
+    for (int j = 0; j < kBookItems; ++j) {
+      const int i = b0 + threadIdx.x * kBookItems + j;
+      if (i >= n) {
+        mate[j] = -2;  // no cluster here
+        continue;
+      }
+      if (mate[j] < 0) bad = 1;  // no neighbour: NaN values cannot occur on finite input
+      if (part[j] != i) mate[j] = -1;
+      else if (idm[j].x < id[j].x) mate[j] = -2;  // merges into the other one
+      if (mate[j] != -1) X.place[i] = -1;
+      if (mate[j] != -2) cntv += mate[j] >= 0 ? (1ull << 32) + 1ull : 1ull;
+    }
+    unsigned long long x = cntv;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const unsigned long long y = __shfl_up(x, o, kWave);
+      if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) ws[w] = x;
+    __syncthreads();
+    if (threadIdx.x < kBookThreads / kWave) {
+      unsigned long long a = ws[threadIdx.x], s = a;
+#pragma unroll
+      for (int o = 1; o < kBookThreads / kWave; o <<= 1) {
+        const unsigned long long y = __shfl_up(s, o, kWave);
+        if ((int)threadIdx.x >= o) s += y;
+      }
+      ws[threadIdx.x] = s - a;
+      if (threadIdx.x == kBookThreads / kWave - 1) ws[kBookThreads / kWave] = s;
+    }
+    __syncthreads();
+    unsigned long long ex = x - cntv + ws[w];
+    const unsigned long long tot = ws[kBookThreads / kWave];
+    __syncthreads();
+    int p = kept + (int)(ex & 0xffffffffu), mr = base + merged + (int)(ex >> 32);
+#pragma unroll
+    for (int j = 0; j < kBookItems; ++j) {
+      const int i = b0 + threadIdx.x * kBookItems + j;
+      const int b = mate[j];
+      if (b == -2) continue;
+      X.src[p] = make_int2(i, b);
+      int sz = id[j].y, node = id[j].z;
+      double e = eff[j];
+      if (b >= 0) {
+        const double h = key_to_height(S.linkage, X.nnv[src][i]);
+        S.row_na[mr] = node;
+        S.row_nb[mr] = idm[j].z;
+        S.row_h[mr] = h;
+        S.row_lo[mr] = id[j].x;
+        sz += idm[j].y;
+        S.row_size[mr] = sz;
+        e = fmax(fmax(e, effm[j]), h);
+        S.row_eff[mr] = e;
+        node = S.n + mr;
+        ++mr;
+      } else {
+        X.place[i] = p;
+      }
+      N.id[p] = make_int4(id[j].x, sz, node, 0);
+      N.eff[p] = e;
+      N.rsize[p] = 1.0 / (double)sz;
+      ++p;
+    }
+    kept += (int)(tot & 0xffffffffu);
+    merged += (int)(tot >> 32);
+  }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) {
+    if (bad) cnt->mx_err = 1;
+    else if (merged == 0 && cnt->mx_rounds > 0 && cnt->mx_merged == 0) cnt->mx_err = 2;
+    cnt->mx_old = n;
+    cnt->mx_merged = merged;
+    cnt->n_act = kept;
+    cnt->mx_merges = base + merged;
+    cnt->mx_rounds += 1;
+    cnt->mx_terms += n;
+  }
+}
+
+inline int nblk(long long n, int cap = 4096) {
+  const long long b = (n + kBlock - 1) / kBlock;
+  return (int)(b < 1 ? 1 : (b < cap ? b : cap));
+}
+
+template <int LINK, bool FIRST>
+void launch_pass(State &S, Mx &X, int bound, int src, hipStream_t s) {
+  // a wavefront per row while that fills the chip, else a block: wider rows
+  // then have four times the loads in flight
+  if (bound <= 2048) k_mx_pass<LINK, FIRST, kWave><<<(bound + 3) / 4, kBlock, 0, s>>>(X, src, S.cnt);
+  else k_mx_pass<LINK, FIRST, kBlock><<<bound, kBlock, 0, s>>>(X, src, S.cnt);
+}
+
+template <int LINK>
+void launch_build(State &S, Mx &X, const float *px, int m, hipStream_t s) {
+  const int n = S.n, d = S.d;
+  const int nwin = (n + kWin - 1) / kWin;
+  if (m < n) k_mx_zero<<<std::min(m, 1 << 16), kBlock, 0, s>>>(X, m);
+  if (d <= 16) {
+    const int pairs = (nwin + 1) / 2;
+    // column windows per block: enough blocks for small inputs, few stagings for large ones
+    const int group = pairs <= 256 ? 4 : 32;
+    const dim3 g(nwin, (pairs + group - 1) / group);
+    if (d <= 2) k_mx_build_lo<LINK, 2><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
+    else if (d <= 3) k_mx_build_lo<LINK, 3><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
+    else if (d <= 5) k_mx_build_lo<LINK, 5><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
+    else if (d <= 10) k_mx_build_lo<LINK, 10><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
+    else k_mx_build_lo<LINK, 16><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
+  } else {
+    const int group = nwin <= 64 ? 1 : 8;
+    k_mx_build_hi<LINK><<<dim3(nwin, (nwin + group - 1) / group), kBlock, 0, s>>>(px, X, n, d, m, group);
+  }
+  const int t = (m + kWin - 1) / kWin;
+  k_mx_mirror<<<dim3(t, t), kBlock, 0, s>>>(X, m);
+}
+
+}  // namespace
+
+size_t mx_layout(Mx &X, char *base, int m, int n) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    off = (off + 255) & ~(size_t)255;
+    char *p = base ? base + off : nullptr;
+    off += bytes;
+    return p;
+  };
+  X.cap = m;
+  const size_t mat = (size_t)m * (size_t)mx_ld(m) * sizeof(double);
+  for (int i = 0; i < 2; ++i) {
+    X.k[i] = (double *)take(mat);
+    X.c[i].id = (int4 *)take((size_t)m * sizeof(int4));
+    X.c[i].eff = (double *)take((size_t)m * sizeof(double));
+    X.c[i].rsize = (double *)take((size_t)m * sizeof(double));
+    X.nnv[i] = (double *)take((size_t)m * sizeof(double));
+    X.nni[i] = (int *)take((size_t)m * sizeof(int));
+  }
+  X.src = (int2 *)take((size_t)m * sizeof(int2));
+  X.place = (int *)take((size_t)m * sizeof(int));
+  X.beg = (int *)take((size_t)m * sizeof(int));
+  X.own = (int *)take((size_t)n * sizeof(int));
+  X.cur = 0;
+  return off + 256;
+}
+
+void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s) {
+  k_mx_enter<<<nblk(m), kBlock, 0, s>>>(S, X, merges, direct ? 1 : 0);
+  if (!direct) k_mx_own<<<nblk(S.n), kBlock, 0, s>>>(S, X);
+  const float *px = direct ? S.xin : S.px;
+  tmark(S, 2, false, s);
+  if (S.linkage == kComplete) launch_build<kComplete>(S, X, px, m, s);
+  else launch_build<kAverage>(S, X, px, m, s);
+  tmark(S, 2, true, s);
+  tmark(S, 1, false, s);
+  if (S.linkage == kComplete) launch_pass<kComplete, true>(S, X, m, 0, s);
+  else launch_pass<kAverage, true>(S, X, m, 0, s);
+  tmark(S, 1, true, s);
+}
+
+void launch_mx_book(State &S, Mx &X, hipStream_t s) { k_mx_book<<<1, kBookThreads, 0, s>>>(S, X, X.cur); }
+
+void launch_mx_pass(State &S, Mx &X, int bound, hipStream_t s) {
+  tmark(S, 1, false, s);
+  if (S.linkage == kComplete) launch_pass<kComplete, false>(S, X, bound, X.cur, s);
+  else launch_pass<kAverage, false>(S, X, bound, X.cur, s);
+  tmark(S, 1, true, s);
+  X.cur ^= 1;
+}
+
+}  // namespace pc

@@ -835,12 +835,6 @@ __device__ __forceinline__ double beta_key(unsigned predbits) {
   return b * b * kSlack;
 }
 
-// Heights: complete and Ward keys are squared distances; average and avg-2
-// keys are the heights themselves.
-__device__ __forceinline__ double key_to_height(int link, double v) {
-  return (link == kAverage || link == kAvgSq) ? v : sqrt(v);
-}
-
 // ------------------------------------------------------ ring search kernel --
 // One thread per terminal. PASS 0: Ward (final result) or, for complete and
 // average, the search bound plus the best inline-evaluated candidate. PASS 1
@@ -4060,22 +4054,6 @@ inline int nblk(long long n, int cap = 4096) {
   long long b = (n + kBlock - 1) / kBlock;
   if (b < 1) b = 1;
   return (int)(b < cap ? b : cap);
-}
-
-inline void tmark(State &S, int k, bool end, hipStream_t s) {
-  if (!S.timing) return;
-  KTimer &t = *S.kt;
-  int idx;
-  if (t.take(idx) != hipSuccess) return;  // (no event: this launch goes untimed)
-  (void)hipEventRecord(t.pool[idx], s);
-  if (!end) {
-    t.open[k] = idx;
-  } else if (t.open[k] >= 0) {
-    t.done.push_back(k);
-    t.done.push_back(t.open[k]);
-    t.done.push_back(idx);
-    t.open[k] = -1;
-  }
 }
 
 // the ring searches with or without the cache probes (centroid linkages
