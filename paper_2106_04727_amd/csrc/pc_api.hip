@@ -521,6 +521,24 @@ static long long initial_cap(const pc_context *ctx, const Buf &b, long long want
   return std::max<long long>(1, std::min(want, c));
 }
 
+// Largest number of active clusters that Ward's and avg-2's scan rounds take: a
+// scan costs about m^2 / 2 keys of d terms, the other searches of those rounds
+// little but their launches and host reads. Measured (whole calls, Ward, ms):
+//   65K points d = 2: none 5.9, 4096 clusters 3.9, 8192 3.7, 16384 3.8, 32768 4.0
+//   65K points d = 3 (box tree before): none 23.1, 8192 14.4, 16384 11.2, 32768 8.7
+//   65K points d = 5: none 18.7, 8192 13.2, 16384 12.8, 32768 13.3
+//   20K points d = 16: none 11.9, 4096 6.5, 8192 6.1, 16384 6.0, all 7.2
+//   20K points d = 64: none 17.5, 4096 11.1, 8192 11.1, 16384 14.4
+//   20K points d = 128: none 23.5, 4096 16.9, 8192 17.5, 16384 24.8
+static int scan_max(int d) {
+  if (d <= 2) return 12288;
+  if (d == 3) return 32768;
+  if (d <= 8) return 16384;
+  if (d <= 16) return 12288;
+  if (d <= 48) return 8192;
+  return d <= 96 ? 6144 : 4096;
+}
+
 // Largest number of active clusters that the pair matrix takes. Its sweeps
 // cost about 4 m^2 entries, so it pays once the searches of the rounds before
 // cost more than that: ring searches (d <= 3) are cheap down to few clusters,
@@ -533,6 +551,7 @@ static long long initial_cap(const pc_context *ctx, const Buf &b, long long want
 //   50K points d = 128: 16384 72.8 / 139, 32768 63.5 / 71.1, 49152 70.9 / 73.1
 // Two matrices of 32768 clusters are 17 GB.
 static int matrix_max(int linkage, int d, int64_t n) {
+  if (centroid_link(linkage)) return scan_max(d);
   int64_t m;
   if (d <= 3) m = linkage == kAverage ? 12288 : 8192;
   else if (d <= 16) m = std::max<int64_t>(12288, n / 6);
@@ -558,8 +577,9 @@ static bool search_pinned() {
 
 // Room for the matrix of m clusters: false if it does not fit the budget, the
 // scratch window or the device (the call then goes on without it).
-static bool matrix_room(pc_context *ctx, Mx &X, int m, int n) {
-  const size_t need = mx_layout(X, nullptr, m, n);
+static bool matrix_room(pc_context *ctx, Mx &X, int m, int n, int linkage) {
+  const bool scan = centroid_link(linkage);
+  const size_t need = scan ? sc_layout(X, nullptr, m) : mx_layout(X, nullptr, m, n);
   Buf &b = ctx->cur->mat;
   if (b.bytes < need) {
     if (ctx->cur->fixed) return false;
@@ -572,7 +592,8 @@ static bool matrix_room(pc_context *ctx, Mx &X, int m, int n) {
       return false;
     }
   }
-  mx_layout(X, (char *)b.p, m, n);
+  if (scan) sc_layout(X, (char *)b.p, m);
+  else mx_layout(X, (char *)b.p, m, n);
   return true;
 }
 
@@ -690,21 +711,21 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     pc_status st = grow_part(ctx, S, 2LL * n + 64);
     if (st != PC_OK) return st;
   }
-  // pair-matrix rounds (complete, average)
+  // pair-matrix rounds (complete, average) or scan rounds (Ward, avg-2)
   Mx X;
   memset(&X, 0, sizeof(X));
   bool direct = false;  // the matrix holds the points themselves
   int mx_max = 0;       // enter with at most this many active clusters
-  if (prune && cache_default && !centroid_link(linkage) && !search_pinned()) {
+  if (prune && (cache_default || centroid_link(linkage)) && !search_pinned()) {
     mx_max = matrix_max(linkage, d, n);
     if (const char *e = getenv("PC_MATRIX_MAX")) mx_max = std::max(0, atoi(e));
-    if (n <= mx_max) direct = matrix_room(ctx, X, (int)n, (int)n);
+    if (n <= mx_max) direct = matrix_room(ctx, X, (int)n, (int)n, linkage);
   }
   if (direct) {
     ctx->mat_used = true;
     cache_slots = 0;
   }
-  if (centroid_link(linkage) && gram_ok) {
+  if (centroid_link(linkage) && gram_ok && !direct) {
     pc_status st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, std::max<long long>(1 << 22, 4 * n),
                                                  kCandBytes, 1024));
     if (st != PC_OK) return st;
@@ -790,13 +811,14 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   while (nact > 1) {
     if (rounds > n) return fail(PC_ERR_DEVICE, "round loop did not converge");
     if (!direct && nact <= mx_max) {
-      if (matrix_room(ctx, X, nact, (int)n)) ctx->mat_used = true;
+      if (matrix_room(ctx, X, nact, (int)n, linkage)) ctx->mat_used = true;
       else mx_max = nact * 3 / 4;  // less room than that: try again later
     }
     if (ctx->mat_used) {
       // the remaining rounds; launches are queued several rounds at a time
       if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
-      launch_mx_enter(S, X, nact, merges, direct, s);
+      if (centroid_link(linkage)) launch_sc_enter(S, X, nact, merges, direct, s);
+      else launch_mx_enter(S, X, nact, merges, direct, s);
       HIPCHK(hipGetLastError());
       if (S.phases) HIPCHK(hipEventRecord(ctx->rev[1], s));
       while (nact > 1) {

@@ -148,7 +148,7 @@ struct Counters {
   int mx_merges;   // merges of the call so far
   int mx_rounds;   // rounds run
   int mx_err;      // 1: a cluster without a neighbour, 2: a round merged nothing
-  int mx_pad;
+  int mx_nterm;    // scan rounds: clusters whose neighbour is searched
   long long mx_terms;  // clusters whose neighbour was searched, summed over the rounds
 };
 
@@ -201,7 +201,7 @@ struct KTimer {
 // Pair-matrix rounds (pc_matrix.hip): per-cluster records of one round, in
 // active-list order.
 struct MxClusters {
-  int4 *id;       // cluster ID, size, node, 0
+  int4 *id;       // cluster ID, size, node, slot (centroid linkages)
   double *eff;    // largest height in the subtree
   double *rsize;  // 1 / size
 };
@@ -216,6 +216,13 @@ struct Mx {
   double *nnv[2];   // nearest neighbour: key and place
   int *nni[2];
   int cur;          // host: the buffer that holds the current round
+  // scan rounds (Ward, avg-2): no matrix; clusters whose neighbour is searched
+  // and the best candidates that each part of the columns holds for them
+  int *term;
+  int4 *mpair;      // the round's merged pairs: slots (kept, dropped) and sizes
+  double *pv;
+  int2 *pc;         // cluster ID, place
+  int parts;        // host: column parts of the last scan
 };
 
 // All device arrays of one clustering call. Slots are storage indices of
@@ -359,6 +366,58 @@ __device__ __forceinline__ double key_to_height(int link, double v) {
   return (link == kAverage || link == kAvgSq) ? v : sqrt(v);
 }
 
+// Ward key: 2|A||B|/(|A|+|B|) * ||cA - cB||^2 (Table 1, squared). Sizes are
+// integers below 2^53, so the weight is exact before the division.
+template <int MAXD>
+__device__ __forceinline__ double ward_key(const double *ct, double nt, const double *cc, double nc, int d) {
+  double q = 0.0;
+  if (MAXD > 0) {
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k)
+      if (k < d) {
+        double t = ct[k] - cc[k];
+        q += t * t;
+      }
+  } else {
+    for (int k = 0; k < d; ++k) {
+      double t = ct[k] - cc[k];
+      q += t * t;
+    }
+  }
+  const double w = (2.0 * nt * nc) / (nt + nc);
+  return w * q;
+}
+
+// avg-2 key: ||cA - cB||^2 + (Var(A)/|A| + Var(B)/|B|) (Table 1, the mean
+// squared point distance), v = Var/|.| per cluster. The two spread terms are
+// added first, so the value does not depend on which side asks.
+template <int MAXD>
+__device__ __forceinline__ double avgsq_key(const double *ct, double vt, const double *cc, double vc, int d) {
+  double q = 0.0;
+  if (MAXD > 0) {
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k)
+      if (k < d) {
+        double t = ct[k] - cc[k];
+        q += t * t;
+      }
+  } else {
+    for (int k = 0; k < d; ++k) {
+      double t = ct[k] - cc[k];
+      q += t * t;
+    }
+  }
+  return q + (vt + vc);
+}
+
+// Key of a centroid linkage (Ward: sizes; avg-2: spread terms).
+template <int LINK, int MAXD>
+__device__ __forceinline__ double cen_key(const double *ct, double nt, double vt, const double *cc, double nc,
+                                          double vc, int d) {
+  if (LINK == kWard) return ward_key<MAXD>(ct, nt, cc, nc, d);
+  return avgsq_key<MAXD>(ct, vt, cc, vc, d);
+}
+
 // start / end event of a timed launch of slot k (nothing unless the call times its kernels)
 inline void tmark(State &S, int k, bool end, hipStream_t s) {
   if (!S.timing) return;
@@ -414,6 +473,9 @@ size_t mx_layout(Mx &X, char *base, int m, int n);
 // records, matrix and nearest neighbours of the m active clusters (direct:
 // of the n input points themselves)
 void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s);
+// scan rounds: the same without a matrix (Ward, avg-2)
+size_t sc_layout(Mx &X, char *base, int m);
+void launch_sc_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s);
 void launch_mx_book(State &S, Mx &X, hipStream_t s);
 void launch_mx_pass(State &S, Mx &X, int bound, hipStream_t s);
 

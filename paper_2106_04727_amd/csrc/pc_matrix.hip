@@ -80,6 +80,7 @@ __global__ void k_mx_enter(State S, Mx X, int merges, int direct) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     S.cnt->mx_merges = merges;
     const long long m = direct ? n : S.cnt->n_act;
+    S.cnt->mx_terms += m;
     // every pair's exact value is computed from all its point pairs
     S.cnt->cluster_evals += m * (m - 1) / 2;
     S.cnt->refined += m * (m - 1) / 2;
@@ -518,23 +519,97 @@ __global__ __launch_bounds__(kBlock) void k_mx_pass(Mx X, int src, const Counter
 }
 
 // ------------------------------------------------------------------- book --
+constexpr int kScanMaxDim = 8;  // a searching cluster per lane up to this d
+
+// Var of the union (the merge rule of Sec. 2.1 with its size factor), as k_merge
+__device__ __forceinline__ void merge_var(const State &S, int4 M, double cab) {
+  const double ns = (double)(M.z + M.w);
+  const double v = S.cvar[M.x] + S.cvar[M.y] + ((double)M.z * (double)M.w / ns) * cab;
+  S.cvar[M.x] = v;
+  S.cmv[M.x] = v / ns;
+}
+
+// centroid of a merged cluster (kept slot, dropped slot, their sizes), as k_merge
+template <int LINK>
+__device__ __forceinline__ void merge_centroid(const State &S, int4 M) {
+  const int d = S.d;
+  double *sa = S.wsum + (size_t)M.x * d, *ca = S.wcen + (size_t)M.x * d;
+  const double *sb = S.wsum + (size_t)M.y * d, *cb = S.wcen + (size_t)M.y * d;
+  const double ns = (double)(M.z + M.w);
+  if (LINK == kAvgSq) {
+    double cab = 0.0;
+    for (int k = 0; k < d; ++k) {
+      const double t = ca[k] - cb[k];
+      cab += t * t;
+    }
+    merge_var(S, M, cab);
+  }
+  for (int k = 0; k < d; ++k) {
+    const double sum = sa[k] + sb[k];
+    sa[k] = sum;
+    ca[k] = sum / ns;
+  }
+}
+
+// Exclusive scan of one value per thread over the block; `total` for all.
+__device__ __forceinline__ unsigned long long book_scan(unsigned long long v, unsigned long long *ws,
+                                                        unsigned long long &total) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  constexpr int kW = kBookThreads / kWave;
+  unsigned long long x = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const unsigned long long y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  if (lane == kWave - 1) ws[w] = x;
+  __syncthreads();
+  unsigned long long before = 0, tot = 0;
+#pragma unroll
+  for (int k = 0; k < kW; ++k) {
+    const unsigned long long y = ws[k];
+    before += k < w ? y : 0ull;
+    tot += y;
+  }
+  __syncthreads();
+  total = tot;
+  return x - v + before;
+}
+
 // One block, one round: the reciprocal pairs of the nearest neighbours found
 // by the last pass merge (Alg. 1), every cluster gets its place in the next
 // round's records, and the merges their dendrogram rows. Exact ties between a
 // kept neighbour and a new cluster can leave a round without a reciprocal pair;
 // then every cluster looks again, and the pair of the smallest value whose
 // lower ID is lowest is reciprocal.
+template <int LINK>
 __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src) {
+  constexpr bool CEN = centroid_link(LINK);
   Counters *cnt = S.cnt;
   const int n = cnt->n_act;
   if (n <= 1 || cnt->mx_err) return;  // uniform
-  __shared__ unsigned long long ws[kBookThreads / kWave + 1];
+  __shared__ unsigned long long ws[kBookThreads / kWave];
   const MxClusters &O = X.c[src], &N = X.c[src ^ 1];
-  const int *nni = X.nni[src];
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int base = cnt->mx_merges;
+  int *nni = X.nni[src];
+  double *nnv = X.nnv[src];
+  const int base = cnt->mx_merges, before = cnt->mx_merged, rounds = cnt->mx_rounds;
   int kept = 0, merged = 0, bad = 0;
   constexpr int kTileN = kBookThreads * kBookItems;
+  if (CEN && X.parts > 1) {
+    // the best of the column parts of the last scan
+    const int nt = cnt->mx_nterm;
+    for (int i = threadIdx.x; i < nt; i += kBookThreads) {
+      Near b{INFINITY, 0x7fffffff, -1};
+      for (int k = 0; k < X.parts; ++k) {
+        const int2 c = X.pc[(size_t)k * X.cap + i];
+        nearer(b, X.pv[(size_t)k * X.cap + i], c.x, c.y);
+      }
+      const int p = X.term[i];
+      nnv[p] = b.v;
+      nni[p] = b.q;
+    }
+    __syncthreads();
+  }
   for (int b0 = 0; b0 < n; b0 += kTileN) {
     int mate[kBookItems], part[kBookItems];
     int4 id[kBookItems], idm[kBookItems];
@@ -568,29 +643,9 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src
       if (mate[j] != -1) X.place[i] = -1;
       if (mate[j] != -2) cntv += mate[j] >= 0 ? (1ull << 32) + 1ull : 1ull;
     }
-    unsigned long long x = cntv;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const unsigned long long y = __shfl_up(x, o, kWave);
-      if (lane >= o) x += y;
-    }
-    if (lane == kWave - 1) ws[w] = x;
-    __syncthreads();
-    if (threadIdx.x < kBookThreads / kWave) {
-      unsigned long long a = ws[threadIdx.x], s = a;
-#pragma unroll
-      for (int o = 1; o < kBookThreads / kWave; o <<= 1) {
-        const unsigned long long y = __shfl_up(s, o, kWave);
-        if ((int)threadIdx.x >= o) s += y;
-      }
-      ws[threadIdx.x] = s - a;
-      if (threadIdx.x == kBookThreads / kWave - 1) ws[kBookThreads / kWave] = s;
-    }
-    __syncthreads();
-    unsigned long long ex = x - cntv + ws[w];
-    const unsigned long long tot = ws[kBookThreads / kWave];
-    __syncthreads();
-    int p = kept + (int)(ex & 0xffffffffu), mr = base + merged + (int)(ex >> 32);
+    unsigned long long tot;
+    const unsigned long long ex = book_scan(cntv, ws, tot);
+    int p = kept + (int)(ex & 0xffffffffu), ml = merged + (int)(ex >> 32);
 #pragma unroll
     for (int j = 0; j < kBookItems; ++j) {
       const int i = b0 + threadIdx.x * kBookItems + j;
@@ -600,38 +655,295 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src
       int sz = id[j].y, node = id[j].z;
       double e = eff[j];
       if (b >= 0) {
-        const double h = key_to_height(S.linkage, X.nnv[src][i]);
+        const int mr = base + ml;
+        const double h = key_to_height(LINK, nnv[i]);
         S.row_na[mr] = node;
         S.row_nb[mr] = idm[j].z;
         S.row_h[mr] = h;
         S.row_lo[mr] = id[j].x;
+        if (CEN) X.mpair[ml] = make_int4(id[j].w, idm[j].w, id[j].y, idm[j].y);
         sz += idm[j].y;
         S.row_size[mr] = sz;
         e = fmax(fmax(e, effm[j]), h);
         S.row_eff[mr] = e;
         node = S.n + mr;
-        ++mr;
+        ++ml;
       } else {
         X.place[i] = p;
       }
-      N.id[p] = make_int4(id[j].x, sz, node, 0);
+      N.id[p] = make_int4(id[j].x, sz, node, id[j].w);
       N.eff[p] = e;
-      N.rsize[p] = 1.0 / (double)sz;
+      if (LINK == kAverage) N.rsize[p] = 1.0 / (double)sz;
       ++p;
     }
     kept += (int)(tot & 0xffffffffu);
     merged += (int)(tot >> 32);
   }
   bad = __syncthreads_or(bad);
+  int nterm = n;
+  if (CEN) {
+    // merged clusters' centroids, then the clusters that search again: merged,
+    // or their neighbour did (see k_mx_pass)
+    if (S.d <= kScanMaxDim)
+      for (int m = threadIdx.x; m < merged; m += kBookThreads) merge_centroid<LINK>(S, X.mpair[m]);
+    nterm = 0;
+    for (int b0 = 0; b0 < kept && !bad; b0 += kTileN) {
+      int old[kBookItems];
+      double v[kBookItems];
+      unsigned long long c = 0;
+#pragma unroll
+      for (int j = 0; j < kBookItems; ++j) {
+        const int p = b0 + threadIdx.x * kBookItems + j;
+        old[j] = -2;
+        if (p >= kept) continue;
+        const int2 s = X.src[p];
+        old[j] = s.y < 0 && merged > 0 ? X.place[nni[s.x]] : -1;
+        v[j] = nnv[s.x];
+        c += old[j] < 0 ? 1ull : 0ull;
+      }
+      unsigned long long tot;
+      int t = nterm + (int)book_scan(c, ws, tot);
+#pragma unroll
+      for (int j = 0; j < kBookItems; ++j) {
+        const int p = b0 + threadIdx.x * kBookItems + j;
+        if (old[j] == -1) {
+          X.term[t++] = p;
+        } else if (old[j] >= 0) {
+          X.nnv[src ^ 1][p] = v[j];
+          X.nni[src ^ 1][p] = old[j];
+        }
+      }
+      nterm += (int)tot;
+    }
+  }
   if (threadIdx.x == 0) {
     if (bad) cnt->mx_err = 1;
-    else if (merged == 0 && cnt->mx_rounds > 0 && cnt->mx_merged == 0) cnt->mx_err = 2;
+    else if (merged == 0 && rounds > 0 && before == 0) cnt->mx_err = 2;
     cnt->mx_old = n;
     cnt->mx_merged = merged;
     cnt->n_act = kept;
     cnt->mx_merges = base + merged;
-    cnt->mx_rounds += 1;
-    cnt->mx_terms += n;
+    cnt->mx_rounds = rounds + 1;
+    if (CEN) {
+      cnt->mx_nterm = nterm;
+      cnt->cluster_evals += (long long)nterm * (kept - 1);
+      cnt->refined += (long long)nterm * (kept - 1);
+      cnt->visits[1] += (long long)nterm * (kept - 1);
+    }
+    cnt->mx_terms += CEN ? nterm : kept;
+  }
+}
+
+// -------------------------------------------------------------------- scan --
+// Ward and avg-2: values follow from the centroids in O(d), so nothing is kept
+// but the records: a round compares every searching cluster with all others.
+// Up to kScanMaxDim coordinates: a searching cluster per lane, its centroid in
+// registers; the columns of a part are dealt out to the block's 16 wavefronts,
+// which stage 64 at a time in LDS and walk them (broadcast reads). The keys are
+// those of the other searches, evaluated in the same order. Ward's division is
+// taken only where the cross-multiplied test leaves the column a chance.
+// Bound by the FP64 units (about 3 d + 8 slots per pair) and, below some
+// thousand clusters, by the launch and the two dependent sweeps of a round.
+constexpr int kScanThreads = 1024;
+template <int LINK, int MAXD>
+__global__ __launch_bounds__(kScanThreads) void k_sc_scan(State S, Mx X, int dst) {
+  const Counters *cnt = S.cnt;
+  const int nn = cnt->n_act, nt = cnt->mx_nterm;
+  if (nn <= 1 || cnt->mx_err) return;
+  constexpr int kW = kScanThreads / kWave;
+  __shared__ double cen[kW][kWave][MAXD];
+  __shared__ double vcol[kW][kWave];
+  __shared__ int4 idc[kW][kWave];
+  __shared__ Near red[kW][kWave];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int d = S.d, parts = gridDim.y;
+  const int chunks = (nn + kWave - 1) / kWave;
+  for (int t0 = blockIdx.x * kWave; t0 < nt; t0 += gridDim.x * kWave) {
+    const int ti = min(t0 + lane, nt - 1);
+    const int p = X.term[ti];
+    const int4 me = X.c[dst].id[p];
+    double ct[MAXD];
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k) ct[k] = k < d ? S.wcen[(size_t)me.w * d + k] : 0.0;
+    const double sz = (double)me.y, vt = LINK == kAvgSq ? S.cmv[me.w] : 0.0;
+    Near b{INFINITY, 0x7fffffff, -1};
+    double lim = INFINITY;
+    for (int c = blockIdx.y * kW + w; c < chunks; c += parts * kW) {
+      const int q0 = c * kWave, cols = min(kWave, nn - q0);
+      {
+        const int4 o = X.c[dst].id[min(q0 + lane, nn - 1)];
+        idc[w][lane] = o;
+#pragma unroll
+        for (int k = 0; k < MAXD; ++k) cen[w][lane][k] = k < d ? S.wcen[(size_t)o.w * d + k] : 0.0;
+        vcol[w][lane] = LINK == kAvgSq ? S.cmv[o.w] : (double)o.y;
+      }
+      // (a wavefront's LDS operations complete in order)
+      for (int j = 0; j < cols; ++j) {
+        double q = 0.0;
+#pragma unroll
+        for (int k = 0; k < MAXD; ++k) {
+          const double u = ct[k] - cen[w][j][k];
+          q += u * u;  // (coordinates past d add zero)
+        }
+        const double x = vcol[w][j];
+        bool near;
+        double key = 0.0;
+        if (LINK == kWard) {
+          near = q * (2.0 * sz * x) <= lim * (sz + x);
+        } else {
+          key = q + (vt + x);
+          near = key <= lim;
+        }
+        if (near && q0 + j != p) {
+          if (LINK == kWard) key = ((2.0 * sz * x) / (sz + x)) * q;
+          nearer(b, key, idc[w][j].x, q0 + j);
+          lim = LINK == kWard ? b.v * (1.0 + 0x1p-48) : b.v;
+        }
+      }
+    }
+    red[w][lane] = b;
+    __syncthreads();
+    if (w == 0) {
+      for (int k = 1; k < kW; ++k) nearer(b, red[k][lane].v, red[k][lane].cid, red[k][lane].q);
+      if (t0 + lane < nt) {
+        if (parts == 1) {
+          X.nnv[dst][p] = b.v;
+          X.nni[dst][p] = b.q;
+        } else {
+          X.pv[(size_t)blockIdx.y * X.cap + t0 + lane] = b.v;
+          X.pc[(size_t)blockIdx.y * X.cap + t0 + lane] = make_int2(b.cid, b.q);
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// More coordinates: 64 x 64 tiles of centroids, each thread a 4 x 4 block, 16
+// coordinates staged at a time.
+template <int LINK>
+__global__ __launch_bounds__(kBlock) void k_sc_scan_hi(State S, Mx X, int dst) {
+  const Counters *cnt = S.cnt;
+  const int nn = cnt->n_act, nt = cnt->mx_nterm;
+  if (nn <= 1 || cnt->mx_err) return;
+  __shared__ __attribute__((aligned(16))) double As[kKc][kWin + 2];
+  __shared__ __attribute__((aligned(16))) double Bs[kKc][kWin + 2];
+  __shared__ int4 idr[kWin], idc[kWin];
+  __shared__ int place[kWin];
+  __shared__ double vr[kWin], vc[kWin];
+  const int d = S.d, parts = gridDim.y;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int chunks = (nn + kWin - 1) / kWin;
+  for (int t0 = blockIdx.x * kWin; t0 < nt; t0 += gridDim.x * kWin) {
+    __syncthreads();
+    if (threadIdx.x < kWin) {
+      const int p = X.term[min(t0 + (int)threadIdx.x, nt - 1)];
+      const int4 o = X.c[dst].id[p];
+      place[threadIdx.x] = p;
+      idr[threadIdx.x] = o;
+      vr[threadIdx.x] = LINK == kAvgSq ? S.cmv[o.w] : (double)o.y;
+    }
+    Near b[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) b[a] = Near{INFINITY, 0x7fffffff, -1};
+    for (int c = blockIdx.y; c < chunks; c += parts) {
+      const int q0 = c * kWin;
+      __syncthreads();
+      if (threadIdx.x < kWin) {
+        const int4 o = X.c[dst].id[min(q0 + (int)threadIdx.x, nn - 1)];
+        idc[threadIdx.x] = o;
+        vc[threadIdx.x] = LINK == kAvgSq ? S.cmv[o.w] : (double)o.y;
+      }
+      double q[4][4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[a][e] = 0.0;
+      for (int k0 = 0; k0 < d; k0 += kKc) {
+        __syncthreads();
+        for (int t = threadIdx.x; t < kWin * kKc; t += kBlock) {
+          const int i = t / kKc, k = t % kKc;
+          const bool in = k0 + k < d;
+          As[k][i] = in ? S.wcen[(size_t)idr[i].w * d + k0 + k] : 0.0;
+          Bs[k][i] = in ? S.wcen[(size_t)idc[i].w * d + k0 + k] : 0.0;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < kKc; ++k) {
+          const double2 a0 = *(const double2 *)&As[k][ty * 4], a1 = *(const double2 *)&As[k][ty * 4 + 2];
+          const double2 b0 = *(const double2 *)&Bs[k][tx * 4], b1 = *(const double2 *)&Bs[k][tx * 4 + 2];
+          const double ar[4] = {a0.x, a0.y, a1.x, a1.y}, br[4] = {b0.x, b0.y, b1.x, b1.y};
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const double u = ar[a] - br[e];
+              q[a][e] += u * u;
+            }
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const int r = ty * 4 + a;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int cc = tx * 4 + e, col = q0 + cc;
+          if (col >= nn || col == place[r]) continue;
+          const double x = vc[cc], sz = vr[r];
+          const double key = LINK == kWard ? ((2.0 * sz * x) / (sz + x)) * q[a][e] : q[a][e] + (sz + x);
+          nearer(b[a], key, idc[cc].x, col);
+        }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(b[a].v, o, kWave);
+        const int oc = __shfl_xor(b[a].cid, o, kWave), oq = __shfl_xor(b[a].q, o, kWave);
+        nearer(b[a], ov, oc, oq);
+      }
+      const int r = ty * 4 + a;
+      if (tx == 0 && t0 + r < nt) {
+        if (parts == 1) {
+          X.nnv[dst][place[r]] = b[a].v;
+          X.nni[dst][place[r]] = b[a].q;
+        } else {
+          X.pv[(size_t)blockIdx.y * X.cap + t0 + r] = b[a].v;
+          X.pc[(size_t)blockIdx.y * X.cap + t0 + r] = make_int2(b[a].cid, b[a].q);
+        }
+      }
+    }
+  }
+}
+
+// centroids of the round's merged clusters, d > kScanMaxDim: a wavefront each
+template <int LINK>
+__global__ __launch_bounds__(kBlock) void k_sc_merge(State S, Mx X) {
+  const Counters *cnt = S.cnt;
+  if (cnt->mx_err || cnt->n_act <= 1) return;
+  extern __shared__ double sq[];  // d per wavefront (avg-2)
+  const int d = S.d, nm = cnt->mx_merged;
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  for (int m = blockIdx.x * (kBlock / kWave) + w; m < nm; m += gridDim.x * (kBlock / kWave)) {
+    const int4 M = X.mpair[m];
+    double *sa = S.wsum + (size_t)M.x * d, *ca = S.wcen + (size_t)M.x * d;
+    const double *sb = S.wsum + (size_t)M.y * d, *cb = S.wcen + (size_t)M.y * d;
+    const double ns = (double)(M.z + M.w);
+    for (int k = lane; k < d; k += kWave) {
+      if (LINK == kAvgSq) {
+        const double t = ca[k] - cb[k];
+        sq[w * d + k] = t * t;
+      }
+      const double sum = sa[k] + sb[k];
+      sa[k] = sum;
+      ca[k] = sum / ns;
+    }
+    if (LINK == kAvgSq && lane == 0) {
+      double cab = 0.0;
+      for (int k = 0; k < d; ++k) cab += sq[w * d + k];  // in order, as k_merge
+      merge_var(S, M, cab);
+    }
   }
 }
 
@@ -669,6 +981,61 @@ void launch_build(State &S, Mx &X, const float *px, int m, hipStream_t s) {
   }
   const int t = (m + kWin - 1) / kWin;
   k_mx_mirror<<<dim3(t, t), kBlock, 0, s>>>(X, m);
+}
+
+// Column parts of a scan: enough blocks to fill the chip while a wavefront
+// still has a chunk of 64 columns of its own.
+constexpr int kScanParts = 8;
+
+template <int LINK>
+void launch_scan(State &S, Mx &X, int bound, int dst, hipStream_t s) {
+  const int tiles = (bound + kWave - 1) / kWave;
+  const bool first = dst == X.cur;
+  tmark(S, 1, false, s);
+  if (S.d <= kScanMaxDim) {
+    const int chunks = (bound + kWave - 1) / kWave, per = kScanThreads / kWave;
+    X.parts = std::max(1, std::min(kScanParts, std::min(chunks / per, 512 / tiles)));
+    const dim3 g(tiles, X.parts);
+    if (S.d <= 2) k_sc_scan<LINK, 2><<<g, kScanThreads, 0, s>>>(S, X, dst);
+    else if (S.d <= 3) k_sc_scan<LINK, 3><<<g, kScanThreads, 0, s>>>(S, X, dst);
+    else if (S.d <= 5) k_sc_scan<LINK, 5><<<g, kScanThreads, 0, s>>>(S, X, dst);
+    else k_sc_scan<LINK, 8><<<g, kScanThreads, 0, s>>>(S, X, dst);
+  } else {
+    if (!first) k_sc_merge<LINK><<<std::min(1024, bound / 8 + 1), kBlock,
+                                   LINK == kAvgSq ? S.d * sizeof(double) * (kBlock / kWave) : 0, s>>>(S, X);
+    X.parts = std::max(1, std::min(kScanParts, std::min(tiles, 2048 / tiles)));
+    k_sc_scan_hi<LINK><<<dim3(tiles, X.parts), kBlock, 0, s>>>(S, X, dst);
+  }
+  tmark(S, 1, true, s);
+}
+
+// Records of the active list; direct: of single points, with their centroids.
+__global__ void k_sc_enter(State S, Mx X, int merges, int direct) {
+  const int n = direct ? S.n : S.cnt->n_act, d = S.d;
+  const long long tid = blockIdx.x * (long long)blockDim.x + threadIdx.x, step = (long long)gridDim.x * blockDim.x;
+  for (long long i = tid; i < n; i += step) {
+    const int s = direct ? (int)i : S.act[i];
+    X.c[0].id[i] = direct ? make_int4(s, 1, s, s) : make_int4(S.cid[s], S.csize[s], S.node[s], s);
+    X.c[0].eff[i] = direct ? 0.0 : S.eff[s];
+    X.term[i] = (int)i;
+    if (direct && S.linkage == kAvgSq) {
+      S.cvar[s] = 0.0;
+      S.cmv[s] = 0.0;
+    }
+  }
+  if (direct)
+    for (long long j = tid; j < (long long)n * d; j += step) S.wsum[j] = S.wcen[j] = (double)S.xin[j];
+  if (tid == 0) {
+    Counters *c = S.cnt;
+    c->n_act = n;
+    c->mx_merges = merges;
+    c->mx_nterm = n;
+    c->mx_terms += n;
+    const long long pairs = (long long)n * (n - 1);
+    c->cluster_evals += pairs;
+    c->refined += pairs;
+    c->visits[1] += pairs;
+  }
 }
 
 }  // namespace
@@ -713,13 +1080,62 @@ void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_
   tmark(S, 1, true, s);
 }
 
-void launch_mx_book(State &S, Mx &X, hipStream_t s) { k_mx_book<<<1, kBookThreads, 0, s>>>(S, X, X.cur); }
+// ------------------------------------------------------------ scan rounds --
+size_t sc_layout(Mx &X, char *base, int m) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    off = (off + 255) & ~(size_t)255;
+    char *p = base ? base + off : nullptr;
+    off += bytes;
+    return p;
+  };
+  X.cap = m;
+  for (int i = 0; i < 2; ++i) {
+    X.c[i].id = (int4 *)take((size_t)m * sizeof(int4));
+    X.c[i].eff = (double *)take((size_t)m * sizeof(double));
+    X.nnv[i] = (double *)take((size_t)m * sizeof(double));
+    X.nni[i] = (int *)take((size_t)m * sizeof(int));
+  }
+  X.src = (int2 *)take((size_t)m * sizeof(int2));
+  X.place = (int *)take((size_t)m * sizeof(int));
+  X.term = (int *)take((size_t)m * sizeof(int));
+  X.mpair = (int4 *)take((size_t)(m / 2 + 1) * sizeof(int4));
+  X.pv = (double *)take((size_t)kScanParts * m * sizeof(double));
+  X.pc = (int2 *)take((size_t)kScanParts * m * sizeof(int2));
+  X.cur = 0;
+  return off + 256;
+}
+
+void launch_sc_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s) {
+  k_sc_enter<<<nblk(direct ? (long long)m * S.d : m), kBlock, 0, s>>>(S, X, merges, direct ? 1 : 0);
+  if (S.linkage == kWard) launch_scan<kWard>(S, X, m, 0, s);
+  else launch_scan<kAvgSq>(S, X, m, 0, s);
+}
+
+void launch_mx_book(State &S, Mx &X, hipStream_t s) {
+  switch (S.linkage) {
+  case kComplete: k_mx_book<kComplete><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
+  case kAverage: k_mx_book<kAverage><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
+  case kWard: k_mx_book<kWard><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
+  default: k_mx_book<kAvgSq><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
+  }
+}
 
 void launch_mx_pass(State &S, Mx &X, int bound, hipStream_t s) {
-  tmark(S, 1, false, s);
-  if (S.linkage == kComplete) launch_pass<kComplete, false>(S, X, bound, X.cur, s);
-  else launch_pass<kAverage, false>(S, X, bound, X.cur, s);
-  tmark(S, 1, true, s);
+  switch (S.linkage) {
+  case kComplete:
+    tmark(S, 1, false, s);
+    launch_pass<kComplete, false>(S, X, bound, X.cur, s);
+    tmark(S, 1, true, s);
+    break;
+  case kAverage:
+    tmark(S, 1, false, s);
+    launch_pass<kAverage, false>(S, X, bound, X.cur, s);
+    tmark(S, 1, true, s);
+    break;
+  case kWard: launch_scan<kWard>(S, X, bound, X.cur ^ 1, s); break;
+  default: launch_scan<kAvgSq>(S, X, bound, X.cur ^ 1, s); break;
+  }
   X.cur ^= 1;
 }
 

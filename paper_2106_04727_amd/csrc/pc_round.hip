@@ -416,58 +416,6 @@ __global__ void k_cell_scatter(State S) {
 }
 
 // ------------------------------------------------------- linkage values --
-// Ward key: 2|A||B|/(|A|+|B|) * ||cA - cB||^2 (Table 1, squared). Sizes are
-// integers below 2^53, so the weight is exact before the division.
-template <int MAXD>
-__device__ __forceinline__ double ward_key(const double *ct, double nt, const double *cc, double nc, int d) {
-  double q = 0.0;
-  if (MAXD > 0) {
-#pragma unroll
-    for (int k = 0; k < MAXD; ++k)
-      if (k < d) {
-        double t = ct[k] - cc[k];
-        q += t * t;
-      }
-  } else {
-    for (int k = 0; k < d; ++k) {
-      double t = ct[k] - cc[k];
-      q += t * t;
-    }
-  }
-  const double w = (2.0 * nt * nc) / (nt + nc);
-  return w * q;
-}
-
-// avg-2 key: ||cA - cB||^2 + (Var(A)/|A| + Var(B)/|B|) (Table 1, the mean
-// squared point distance), v = Var/|.| per cluster. The two spread terms are
-// added first, so the value does not depend on which side asks.
-template <int MAXD>
-__device__ __forceinline__ double avgsq_key(const double *ct, double vt, const double *cc, double vc, int d) {
-  double q = 0.0;
-  if (MAXD > 0) {
-#pragma unroll
-    for (int k = 0; k < MAXD; ++k)
-      if (k < d) {
-        double t = ct[k] - cc[k];
-        q += t * t;
-      }
-  } else {
-    for (int k = 0; k < d; ++k) {
-      double t = ct[k] - cc[k];
-      q += t * t;
-    }
-  }
-  return q + (vt + vc);
-}
-
-// Key of a centroid linkage (Ward: sizes; avg-2: spread terms).
-template <int LINK, int MAXD>
-__device__ __forceinline__ double cen_key(const double *ct, double nt, double vt, const double *cc, double nc,
-                                          double vc, int d) {
-  if (LINK == kWard) return ward_key<MAXD>(ct, nt, cc, nc, d);
-  return avgsq_key<MAXD>(ct, vt, cc, vc, d);
-}
-
 // Exact complete (largest squared distance) or average (mean distance) value
 // of a small pair, rows = the cluster with the lower ID.
 template <int LINK>

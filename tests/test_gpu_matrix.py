@@ -1,11 +1,13 @@
-"""Pair-matrix rounds (complete and average linkage) at the sizes where their
-kernels can go wrong: windows of 64 points and one point more or less, matrices
-entered with single points or with clusters that lie across windows, every
-width of the coordinate loops, ties, and inputs whose matrix does not fit.
+"""Pair-matrix rounds (complete and average linkage) and scan rounds (Ward and
+avg-2) at the sizes where their kernels can go wrong: windows of 64 points and
+one point more or less, rounds entered with single points or with clusters that
+lie across windows, every width of the coordinate loops, ties, and inputs whose
+matrix does not fit.
 
-Tolerances are those of the other parity tests: complete heights are the
-oracle's bit for bit, average heights within 1e-12 (a mean of N FP64 terms in
-another order differs by at most (N - 1) 2^-53 relative)."""
+Tolerances are those of the other parity tests: complete
+and Ward heights are the oracle's bit for bit, average heights within 1e-12 (a
+mean of N FP64 terms in another order differs by at most (N - 1) 2^-53
+relative), avg-2 heights within 1e-10 (spreads by an equivalent merge rule)."""
 import numpy as np
 import pytest
 
@@ -15,7 +17,8 @@ from tests import _trees
 
 pytestmark = pytest.mark.gpu
 
-RTOL = {"complete": 0.0, "average": 1e-12}
+LINKS = ["complete", "average", "ward", "avgsq"]
+RTOL = {"complete": 0.0, "average": 1e-12, "ward": 0.0, "avgsq": 1e-10}
 
 
 @pytest.fixture(scope="module")
@@ -29,11 +32,11 @@ def pc():
     return pc
 
 
-@pytest.mark.parametrize("link", ["complete", "average"])
-@pytest.mark.parametrize("n,d", [(2, 1), (3, 2), (63, 2), (64, 3), (65, 5), (129, 10), (700, 2), (1500, 6),
-                                 (130, 16), (900, 17), (257, 64), (400, 200)])
+@pytest.mark.parametrize("link", LINKS)
+@pytest.mark.parametrize("n,d", [(2, 1), (3, 2), (63, 2), (64, 3), (65, 5), (129, 10), (700, 2), (1500, 6), (1100, 8),
+                                 (2300, 9), (130, 16), (900, 17), (257, 64), (400, 200)])
 def test_matrix_rounds(pc, link, n, d, monkeypatch):
-    """The matrix of the points, entered later with clusters, and not at all."""
+    """Entered with the points, later with clusters, and not at all."""
     x = synth.blobs(n, d, max(1, n // 60), 0.03, 900 + n + d)
     Zo, cert = oracle.nnchain(x, link, threads=8)
     assert cert["min_gap"] >= 1e-10 or n < 3, "fixed input no longer certified tie-free"
@@ -47,7 +50,7 @@ def test_matrix_rounds(pc, link, n, d, monkeypatch):
         assert _trees.same_tree(Z, Zo, n, rtol=RTOL[link]), (link, n, d, cap)
 
 
-@pytest.mark.parametrize("link", ["complete", "average"])
+@pytest.mark.parametrize("link", LINKS)
 @pytest.mark.parametrize("cap", [None, 60])
 def test_matrix_ties(pc, link, cap, monkeypatch):
     """Lattice points and points given twice: equal keys everywhere."""
