@@ -822,14 +822,18 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
       HIPCHK(hipGetLastError());
       if (S.phases) HIPCHK(hipEventRecord(ctx->rev[1], s));
       while (nact > 1) {
-        const int batch = S.phases ? 1 : (nact > 4096 ? 6 : (nact > 512 ? 12 : 24));
+        // as many rounds as leave the tail's number of clusters if each merges
+        // a fifth of them (10 to 30% on most data); those not needed exit at once
+        int batch = 0;
+        for (double m = nact; m > mx_tail_max(linkage, d) && batch < 12; m *= 0.8) ++batch;
+        if (S.phases) batch = 1;
         for (int r = 0; r < batch; ++r) {
           if (S.phases) HIPCHK(hipEventRecord(ctx->rev[2], s));
-          launch_mx_book(S, X, s);
-          if (S.phases) HIPCHK(hipEventRecord(ctx->rev[3], s));
-          launch_mx_pass(S, X, nact, s);
+          launch_mx_round(S, X, nact, s);
           HIPCHK(hipGetLastError());
         }
+        launch_mx_tail(S, X, s);
+        HIPCHK(hipGetLastError());
         if (S.phases) HIPCHK(hipEventRecord(ctx->ev[2], s));
         HIPCHK(hipMemcpyAsync(&h, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));

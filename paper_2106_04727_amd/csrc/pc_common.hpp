@@ -149,6 +149,8 @@ struct Counters {
   int mx_rounds;   // rounds run
   int mx_err;      // 1: a cluster without a neighbour, 2: a round merged nothing
   int mx_nterm;    // scan rounds: clusters whose neighbour is searched
+  int mx_ran;      // the last round's launches had a round to run
+  int mx_pad;
   long long mx_terms;  // clusters whose neighbour was searched, summed over the rounds
 };
 
@@ -207,7 +209,8 @@ struct MxClusters {
 };
 struct Mx {
   int cap;          // clusters at entry
-  double *k[2];     // pair values (both halves, infinity on the diagonal), this round's and the next one's
+  double *k[2];     // pair values (both halves, infinity on the diagonal); round r of the
+                    // matrix reads buffer r & 1 and writes the other one
   MxClusters c[2];
   int2 *src;        // a new cluster's sources in the old records (y: -1 if unmerged)
   int *place;       // an old cluster's place in the new records if it was not merged, else -1
@@ -215,7 +218,6 @@ struct Mx {
   int *own;         // cluster of every point position at entry
   double *nnv[2];   // nearest neighbour: key and place
   int *nni[2];
-  int cur;          // host: the buffer that holds the current round
   // scan rounds (Ward, avg-2): no matrix; clusters whose neighbour is searched
   // and the best candidates that each part of the columns holds for them
   int *term;
@@ -476,7 +478,10 @@ void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_
 // scan rounds: the same without a matrix (Ward, avg-2)
 size_t sc_layout(Mx &X, char *base, int m);
 void launch_sc_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s);
-void launch_mx_book(State &S, Mx &X, hipStream_t s);
-void launch_mx_pass(State &S, Mx &X, int bound, hipStream_t s);
+// one round of at most `bound` clusters (nothing once few are left or on error)
+void launch_mx_round(State &S, Mx &X, int bound, hipStream_t s);
+// all rounds from at most mx_tail_max clusters on, in one launch
+int mx_tail_max(int linkage, int d);
+void launch_mx_tail(State &S, Mx &X, hipStream_t s);
 
 }  // namespace pc

@@ -463,9 +463,10 @@ __device__ __forceinline__ void pass_row(const double *__restrict__ A, const dou
 }
 
 template <int LINK, bool FIRST, int TPR>
-__global__ __launch_bounds__(kBlock) void k_mx_pass(Mx X, int src, const Counters *cnt) {
+__global__ __launch_bounds__(kBlock) void k_mx_pass(Mx X, const Counters *cnt) {
   const int nn = cnt->n_act;
-  if (cnt->mx_err || (!FIRST && nn <= 1)) return;
+  if (cnt->mx_err || (!FIRST && (nn <= 1 || !cnt->mx_ran))) return;
+  const int src = FIRST ? 0 : (cnt->mx_rounds & 1) ^ 1;
   const bool fresh = FIRST || cnt->mx_merged == 0;  // every cluster looks again, see k_mx_book
   const int dst = FIRST ? src : src ^ 1;
   const long long lo = mx_ld(FIRST ? nn : cnt->mx_old), ln = mx_ld(nn);
@@ -582,17 +583,22 @@ __device__ __forceinline__ unsigned long long book_scan(unsigned long long v, un
 // kept neighbour and a new cluster can leave a round without a reciprocal pair;
 // then every cluster looks again, and the pair of the smallest value whose
 // lower ID is lowest is reciprocal.
+// Rounds of at most `stop` clusters are left to the tail kernels.
 template <int LINK>
-__global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src) {
+__global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int stop) {
   constexpr bool CEN = centroid_link(LINK);
   Counters *cnt = S.cnt;
   const int n = cnt->n_act;
-  if (n <= 1 || cnt->mx_err) return;  // uniform
+  if (n <= 1 || n <= stop || cnt->mx_err) {  // uniform
+    if (threadIdx.x == 0) cnt->mx_ran = 0;
+    return;
+  }
   __shared__ unsigned long long ws[kBookThreads / kWave];
+  const int rounds = cnt->mx_rounds, src = rounds & 1;
   const MxClusters &O = X.c[src], &N = X.c[src ^ 1];
   int *nni = X.nni[src];
   double *nnv = X.nnv[src];
-  const int base = cnt->mx_merges, before = cnt->mx_merged, rounds = cnt->mx_rounds;
+  const int base = cnt->mx_merges, before = cnt->mx_merged;
   int kept = 0, merged = 0, bad = 0;
   constexpr int kTileN = kBookThreads * kBookItems;
   if (CEN && X.parts > 1) {
@@ -724,6 +730,7 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src
     cnt->n_act = kept;
     cnt->mx_merges = base + merged;
     cnt->mx_rounds = rounds + 1;
+    cnt->mx_ran = 1;
     if (CEN) {
       cnt->mx_nterm = nterm;
       cnt->cluster_evals += (long long)nterm * (kept - 1);
@@ -746,10 +753,10 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int src
 // thousand clusters, by the launch and the two dependent sweeps of a round.
 constexpr int kScanThreads = 1024;
 template <int LINK, int MAXD>
-__global__ __launch_bounds__(kScanThreads) void k_sc_scan(State S, Mx X, int dst) {
+__global__ __launch_bounds__(kScanThreads) void k_sc_scan(State S, Mx X) {
   const Counters *cnt = S.cnt;
-  const int nn = cnt->n_act, nt = cnt->mx_nterm;
-  if (nn <= 1 || cnt->mx_err) return;
+  const int nn = cnt->n_act, nt = cnt->mx_nterm, dst = cnt->mx_rounds & 1;
+  if (nn <= 1 || cnt->mx_err || !cnt->mx_ran) return;
   constexpr int kW = kScanThreads / kWave;
   __shared__ double cen[kW][kWave][MAXD];
   __shared__ double vcol[kW][kWave];
@@ -822,10 +829,10 @@ __global__ __launch_bounds__(kScanThreads) void k_sc_scan(State S, Mx X, int dst
 // More coordinates: 64 x 64 tiles of centroids, each thread a 4 x 4 block, 16
 // coordinates staged at a time.
 template <int LINK>
-__global__ __launch_bounds__(kBlock) void k_sc_scan_hi(State S, Mx X, int dst) {
+__global__ __launch_bounds__(kBlock) void k_sc_scan_hi(State S, Mx X) {
   const Counters *cnt = S.cnt;
-  const int nn = cnt->n_act, nt = cnt->mx_nterm;
-  if (nn <= 1 || cnt->mx_err) return;
+  const int nn = cnt->n_act, nt = cnt->mx_nterm, dst = cnt->mx_rounds & 1;
+  if (nn <= 1 || cnt->mx_err || !cnt->mx_ran) return;
   __shared__ __attribute__((aligned(16))) double As[kKc][kWin + 2];
   __shared__ __attribute__((aligned(16))) double Bs[kKc][kWin + 2];
   __shared__ int4 idr[kWin], idc[kWin];
@@ -921,7 +928,7 @@ __global__ __launch_bounds__(kBlock) void k_sc_scan_hi(State S, Mx X, int dst) {
 template <int LINK>
 __global__ __launch_bounds__(kBlock) void k_sc_merge(State S, Mx X) {
   const Counters *cnt = S.cnt;
-  if (cnt->mx_err || cnt->n_act <= 1) return;
+  if (cnt->mx_err || cnt->n_act <= 1 || !cnt->mx_ran) return;
   extern __shared__ double sq[];  // d per wavefront (avg-2)
   const int d = S.d, nm = cnt->mx_merged;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -947,17 +954,372 @@ __global__ __launch_bounds__(kBlock) void k_sc_merge(State S, Mx X) {
   }
 }
 
+// -------------------------------------------------------------------- tail --
+// The last rounds in one block, everything in LDS: a round of a few hundred
+// clusters is otherwise bound by two launches and some ten dependent loads
+// from memory (25 us); here it is bound by its barriers (about 3 us). Clusters
+// keep their places; `act` lists the ones alive.
+constexpr int kTailThreads = 1024;
+constexpr int kMatTail = 176;    // lower triangle of 176 clusters: 123 KB
+constexpr int kCenTail = 512;    // scan rounds: one cluster per thread at most,
+constexpr int kCenTailNd = 4096; // and two FP64 values per coordinate: 64 KB
+
+struct TailShared {
+  unsigned long long ws[kTailThreads / kWave];
+  int nact, merged, nterm, err;
+};
+
+// rank of this thread among those with `f`, and their number
+__device__ __forceinline__ int tail_rank(bool f, unsigned long long *ws, int &total) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const unsigned long long m = __ballot(f);
+  if (lane == 0) ws[w] = (unsigned long long)__popcll(m);
+  __syncthreads();
+  int before = 0, tot = 0;
+#pragma unroll
+  for (int k = 0; k < kTailThreads / kWave; ++k) {
+    const int c = (int)ws[k];
+    before += k < w ? c : 0;
+    tot += c;
+  }
+  __syncthreads();
+  total = tot;
+  return before + __popcll(m & lanemask_lt());
+}
+
+// Records of the tail's clusters in LDS.
+struct TailRec {
+  double *eff, *nnv;
+  int *cid, *size, *node, *nni, *st, *act, *term;  // st: merge number, -1 unmerged, -2 dropped
+  int *ma, *mb;                                    // merged pairs
+};
+__device__ __forceinline__ char *tail_carve(TailRec &R, char *p, int n) {
+  auto take = [&](size_t bytes) {
+    char *q = p;
+    p += (bytes + 15) & ~(size_t)15;
+    return q;
+  };
+  R.eff = (double *)take(n * 8);
+  R.nnv = (double *)take(n * 8);
+  R.cid = (int *)take(n * 4);
+  R.size = (int *)take(n * 4);
+  R.node = (int *)take(n * 4);
+  R.nni = (int *)take(n * 4);
+  R.st = (int *)take(n * 4);
+  R.act = (int *)take(n * 4);
+  R.term = (int *)take(n * 4);
+  R.ma = (int *)take(n * 4);
+  R.mb = (int *)take(n * 4);
+  return p;
+}
+inline size_t tail_rec_bytes(int n) { return (size_t)n * 52 + 11 * 16; }
+
+// One round's reciprocal pairs: rows, merged records (value, size, node, eff)
+// and the new active list; the clusters that search again. Every thread holds
+// at most one cluster. Returns the number of merges.
+template <int LINK>
+__device__ __forceinline__ int tail_book(State &S, TailRec &R, TailShared &T, int &nact, int &base, int &nterm) {
+  const int t = threadIdx.x;
+  const int a = t < nact ? R.act[t] : -1;
+  int b = -1;
+  bool drop = false;
+  if (a >= 0) {
+    const int j = R.nni[a];
+    if (j >= 0 && R.nni[j] == a) {
+      if (R.cid[j] < R.cid[a]) drop = true;
+      else b = j;
+    }
+    if (j < 0) T.err = 1;
+  }
+  int merged, kept;
+  const int m = tail_rank(b >= 0, T.ws, merged);
+  const int k = tail_rank(a >= 0 && !drop, T.ws, kept);
+  if (a >= 0) {
+    R.st[a] = drop ? -2 : (b >= 0 ? m : -1);
+    if (!drop) R.act[k] = a;  // (every thread has read its own entry)
+    if (b >= 0) {
+      const int mr = base + m;
+      const double h = key_to_height(LINK, R.nnv[a]);
+      const int sz = R.size[a] + R.size[b];
+      const double e = fmax(fmax(R.eff[a], R.eff[b]), h);
+      S.row_na[mr] = R.node[a];
+      S.row_nb[mr] = R.node[b];
+      S.row_h[mr] = h;
+      S.row_lo[mr] = R.cid[a];
+      S.row_size[mr] = sz;
+      S.row_eff[mr] = e;
+      R.ma[m] = a;
+      R.mb[m] = b;
+    }
+  }
+  __syncthreads();
+  const bool again = a >= 0 && !drop && (merged == 0 || b >= 0 || R.st[max(R.nni[a], 0)] != -1);
+  const int q = tail_rank(again, T.ws, nterm);
+  if (again) R.term[q] = a;
+  nact = kept;
+  base += merged;
+  return merged;
+}
+
+// size, node and eff of the merged clusters, once their old values are read
+template <int LINK>
+__device__ __forceinline__ void tail_merge_rec(const State &S, TailRec &R, int m, int base) {
+  const int a = R.ma[m], b = R.mb[m];
+  R.eff[a] = fmax(fmax(R.eff[a], R.eff[b]), key_to_height(LINK, R.nnv[a]));
+  R.size[a] += R.size[b];
+  R.node[a] = S.n + base + m;
+}
+
+// Lanes per searching cluster: a power of two that gives every thread work.
+__device__ __forceinline__ int tail_group(int nterm) {
+  int g = 1;
+  while (g < kWave && nterm * g * 2 <= kTailThreads) g *= 2;
+  return g;
+}
+__device__ __forceinline__ void tail_near(TailRec &R, int p, Near b, int g, bool in) {
+  for (int o = g / 2; o > 0; o >>= 1) {
+    const double ov = __shfl_xor(b.v, o, kWave);
+    const int oc = __shfl_xor(b.cid, o, kWave), oq = __shfl_xor(b.q, o, kWave);
+    nearer(b, ov, oc, oq);
+  }
+  if (in && (threadIdx.x & (g - 1)) == 0) {
+    R.nnv[p] = b.v;
+    R.nni[p] = b.q;
+  }
+}
+
+__device__ __forceinline__ void tail_begin(const Mx &X, TailRec &R, int src, int n) {
+  const int t = threadIdx.x;
+  if (t < n) {
+    const int4 o = X.c[src].id[t];
+    R.cid[t] = o.x;
+    R.size[t] = o.y;
+    R.node[t] = o.z;
+    R.eff[t] = X.c[src].eff[t];
+    R.nnv[t] = X.nnv[src][t];
+    R.nni[t] = X.nni[src][t];
+    R.act[t] = t;
+  }
+}
+__device__ __forceinline__ void tail_end(Counters *cnt, int err, int nact, int base, int rounds, long long terms,
+                                         long long evals) {
+  cnt->mx_err = err;
+  cnt->n_act = nact;
+  cnt->mx_merges = base;
+  cnt->mx_rounds += rounds;
+  cnt->mx_terms += terms;
+  if (evals) {
+    cnt->cluster_evals += evals;
+    cnt->refined += evals;
+    cnt->visits[1] += evals;
+  }
+}
+
+// complete, average: the matrix's lower triangle in LDS
+template <int LINK>
+__global__ __launch_bounds__(kTailThreads) void k_mx_tail(State S, Mx X, int stop) {
+  Counters *cnt = S.cnt;
+  int nact = cnt->n_act;
+  if (nact <= 1 || nact > stop || cnt->mx_err) return;
+  extern __shared__ __attribute__((aligned(16))) char sm[];
+  __shared__ TailShared T;
+  const int n = nact, src = cnt->mx_rounds & 1;
+  const long long ld = mx_ld(n);
+  TailRec R;
+  double *K = (double *)tail_carve(R, sm, stop);
+  auto at = [](int i, int j) { return i > j ? i * (i - 1) / 2 + j : j * (j - 1) / 2 + i; };
+  tail_begin(X, R, src, n);
+  if (threadIdx.x == 0) T.err = 0;
+  for (int e = threadIdx.x; e < n * n; e += kTailThreads) {
+    const int i = e / n, j = e - i * n;
+    if (j < i) K[at(i, j)] = X.k[src][i * ld + j];
+  }
+  int base = cnt->mx_merges, rounds = 0, before = cnt->mx_merged;
+  long long terms = 0;
+  __syncthreads();
+  // a round of m merges leaves n - m clusters: at most (kMatTail / 2)^2 new values
+  constexpr int kHeld = (kMatTail / 2 * (kMatTail / 2) + kTailThreads - 1) / kTailThreads;
+  while (nact > 1) {
+    int nterm;
+    const int was = base;
+    const int merged = tail_book<LINK>(S, R, T, nact, base, nterm);
+    if (T.err || (merged == 0 && before == 0 && rounds > 0)) break;  // uniform
+    before = merged;
+    // new rows from the old values, held in registers until all are read
+    double v[kHeld];
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+      const int e = u * kTailThreads + threadIdx.x;
+      v[u] = -1.0;
+      if (e >= merged * nact) continue;
+      const int m = e / nact, c = R.act[e - m * nact];
+      const int a = R.ma[m], b = R.mb[m];
+      if (c == a) continue;
+      const int cm = R.st[c];
+      const double x = K[at(a, c)], y = K[at(b, c)];
+      if (cm < 0) {
+        v[u] = LINK == kComplete ? (y > x ? y : x) : x + y;
+      } else {
+        const int cb = R.mb[cm];
+        const double z = K[at(a, cb)], w = K[at(b, cb)];
+        if (LINK == kComplete) {
+          const double p = y > x ? y : x, q = w > z ? w : z;
+          v[u] = q > p ? q : p;
+        } else {
+          v[u] = a < c ? (x + y) + (z + w) : (x + z) + (y + w);  // the same on both sides
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+      const int e = u * kTailThreads + threadIdx.x;
+      if (e >= merged * nact || v[u] < 0.0) continue;
+      const int m = e / nact;
+      K[at(R.ma[m], R.act[e - m * nact])] = v[u];
+    }
+    for (int m = threadIdx.x; m < merged; m += kTailThreads) tail_merge_rec<LINK>(S, R, m, was);
+    __syncthreads();
+    const int g = tail_group(nterm);
+    for (int e0 = 0; e0 < nterm * g; e0 += kTailThreads) {
+      const int e = e0 + threadIdx.x;
+      const bool in = e < nterm * g;
+      const int p = R.term[in ? e / g : 0];
+      Near b{INFINITY, 0x7fffffff, -1};
+      if (in) {
+        const double sz = (double)R.size[p];
+        for (int i = e & (g - 1); i < nact; i += g) {
+          const int c = R.act[i];
+          if (c == p) continue;
+          double key = K[at(p, c)];
+          if (LINK == kAverage) key = key / (sz * (double)R.size[c]);
+          nearer(b, key, R.cid[c], c);
+        }
+      }
+      tail_near(R, p, b, g, in);
+    }
+    ++rounds;
+    terms += nact > 1 ? nact : 0;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) tail_end(cnt, T.err ? 1 : (nact > 1 ? 2 : 0), nact, base, rounds, terms, 0);
+}
+
+// Ward, avg-2: centroids and coordinate sums in LDS
+template <int LINK>
+__global__ __launch_bounds__(kTailThreads) void k_sc_tail(State S, Mx X, int stop) {
+  Counters *cnt = S.cnt;
+  int nact = cnt->n_act;
+  if (nact <= 1 || nact > stop || cnt->mx_err) return;
+  extern __shared__ __attribute__((aligned(16))) char sm[];
+  __shared__ TailShared T;
+  const int n = nact, src = cnt->mx_rounds & 1, d = S.d;
+  TailRec R;
+  double *cen = (double *)tail_carve(R, sm, stop);
+  double *sum = cen + (size_t)stop * d, *var = sum + (size_t)stop * d, *mv = var + stop;
+  if (X.parts > 1) {
+    // the best of the column parts of the last scan
+    const int nt = cnt->mx_nterm;
+    for (int i = threadIdx.x; i < nt; i += kTailThreads) {
+      Near b{INFINITY, 0x7fffffff, -1};
+      for (int k = 0; k < X.parts; ++k) {
+        const int2 c = X.pc[(size_t)k * X.cap + i];
+        nearer(b, X.pv[(size_t)k * X.cap + i], c.x, c.y);
+      }
+      const int p = X.term[i];
+      X.nnv[src][p] = b.v;
+      X.nni[src][p] = b.q;
+    }
+    __syncthreads();
+  }
+  tail_begin(X, R, src, n);
+  if (threadIdx.x == 0) T.err = 0;
+  for (int e = threadIdx.x; e < n * d; e += kTailThreads) {
+    const int i = e / d, k = e - i * d;
+    const size_t o = (size_t)X.c[src].id[i].w * d + k;
+    cen[e] = S.wcen[o];
+    sum[e] = S.wsum[o];
+  }
+  if (LINK == kAvgSq && threadIdx.x < n) {
+    const int s = X.c[src].id[threadIdx.x].w;
+    var[threadIdx.x] = S.cvar[s];
+    mv[threadIdx.x] = S.cmv[s];
+  }
+  int base = cnt->mx_merges, rounds = 0, before = cnt->mx_merged;
+  long long terms = 0, evals = 0;
+  __syncthreads();
+  while (nact > 1) {
+    int nterm;
+    const int was = base;
+    const int merged = tail_book<LINK>(S, R, T, nact, base, nterm);
+    if (T.err || (merged == 0 && before == 0 && rounds > 0)) break;  // uniform
+    before = merged;
+    if (LINK == kAvgSq && (int)threadIdx.x < merged) {
+      const int a = R.ma[threadIdx.x], b = R.mb[threadIdx.x];
+      double cab = 0.0;
+      for (int k = 0; k < d; ++k) {
+        const double u = cen[a * d + k] - cen[b * d + k];
+        cab += u * u;
+      }
+      const double sa = (double)R.size[a], sb = (double)R.size[b], ns = (double)(R.size[a] + R.size[b]);
+      var[a] = var[a] + var[b] + (sa * sb / ns) * cab;
+      mv[a] = var[a] / ns;
+    }
+    if (LINK == kAvgSq) __syncthreads();
+    for (int e = threadIdx.x; e < merged * d; e += kTailThreads) {
+      const int m = e / d, k = e - m * d, a = R.ma[m], b = R.mb[m];
+      const double s = sum[a * d + k] + sum[b * d + k];
+      sum[a * d + k] = s;
+      cen[a * d + k] = s / (double)(R.size[a] + R.size[b]);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < merged) tail_merge_rec<LINK>(S, R, threadIdx.x, was);
+    __syncthreads();
+    const int g = tail_group(nterm);
+    for (int e0 = 0; e0 < nterm * g; e0 += kTailThreads) {
+      const int e = e0 + threadIdx.x;
+      const bool in = e < nterm * g;
+      const int p = R.term[in ? e / g : 0];
+      Near b{INFINITY, 0x7fffffff, -1};
+      if (in) {
+        const double sz = (double)R.size[p];
+        const double vp = LINK == kAvgSq ? mv[p] : 0.0;
+        const double *cp = cen + p * d;
+        for (int i = e & (g - 1); i < nact; i += g) {
+          const int c = R.act[i];
+          if (c == p) continue;
+          const double *cc = cen + c * d;
+          double q = 0.0;
+          for (int k = 0; k < d; ++k) {
+            const double u = cp[k] - cc[k];
+            q += u * u;
+          }
+          const double x = LINK == kAvgSq ? mv[c] : (double)R.size[c];
+          const double key = LINK == kWard ? ((2.0 * sz * x) / (sz + x)) * q : q + (vp + x);
+          nearer(b, key, R.cid[c], c);
+        }
+      }
+      tail_near(R, p, b, g, in);
+    }
+    ++rounds;
+    terms += nterm;
+    evals += (long long)nterm * (nact - 1);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) tail_end(cnt, T.err ? 1 : (nact > 1 ? 2 : 0), nact, base, rounds, terms, evals);
+}
+
 inline int nblk(long long n, int cap = 4096) {
   const long long b = (n + kBlock - 1) / kBlock;
   return (int)(b < 1 ? 1 : (b < cap ? b : cap));
 }
 
 template <int LINK, bool FIRST>
-void launch_pass(State &S, Mx &X, int bound, int src, hipStream_t s) {
+void launch_pass(State &S, Mx &X, int bound, hipStream_t s) {
   // a wavefront per row while that fills the chip, else a block: wider rows
   // then have four times the loads in flight
-  if (bound <= 2048) k_mx_pass<LINK, FIRST, kWave><<<(bound + 3) / 4, kBlock, 0, s>>>(X, src, S.cnt);
-  else k_mx_pass<LINK, FIRST, kBlock><<<bound, kBlock, 0, s>>>(X, src, S.cnt);
+  if (bound <= 2048) k_mx_pass<LINK, FIRST, kWave><<<(bound + 3) / 4, kBlock, 0, s>>>(X, S.cnt);
+  else k_mx_pass<LINK, FIRST, kBlock><<<bound, kBlock, 0, s>>>(X, S.cnt);
 }
 
 template <int LINK>
@@ -988,23 +1350,22 @@ void launch_build(State &S, Mx &X, const float *px, int m, hipStream_t s) {
 constexpr int kScanParts = 8;
 
 template <int LINK>
-void launch_scan(State &S, Mx &X, int bound, int dst, hipStream_t s) {
+void launch_scan(State &S, Mx &X, int bound, bool first, hipStream_t s) {
   const int tiles = (bound + kWave - 1) / kWave;
-  const bool first = dst == X.cur;
   tmark(S, 1, false, s);
   if (S.d <= kScanMaxDim) {
     const int chunks = (bound + kWave - 1) / kWave, per = kScanThreads / kWave;
     X.parts = std::max(1, std::min(kScanParts, std::min(chunks / per, 512 / tiles)));
     const dim3 g(tiles, X.parts);
-    if (S.d <= 2) k_sc_scan<LINK, 2><<<g, kScanThreads, 0, s>>>(S, X, dst);
-    else if (S.d <= 3) k_sc_scan<LINK, 3><<<g, kScanThreads, 0, s>>>(S, X, dst);
-    else if (S.d <= 5) k_sc_scan<LINK, 5><<<g, kScanThreads, 0, s>>>(S, X, dst);
-    else k_sc_scan<LINK, 8><<<g, kScanThreads, 0, s>>>(S, X, dst);
+    if (S.d <= 2) k_sc_scan<LINK, 2><<<g, kScanThreads, 0, s>>>(S, X);
+    else if (S.d <= 3) k_sc_scan<LINK, 3><<<g, kScanThreads, 0, s>>>(S, X);
+    else if (S.d <= 5) k_sc_scan<LINK, 5><<<g, kScanThreads, 0, s>>>(S, X);
+    else k_sc_scan<LINK, 8><<<g, kScanThreads, 0, s>>>(S, X);
   } else {
     if (!first) k_sc_merge<LINK><<<std::min(1024, bound / 8 + 1), kBlock,
                                    LINK == kAvgSq ? S.d * sizeof(double) * (kBlock / kWave) : 0, s>>>(S, X);
     X.parts = std::max(1, std::min(kScanParts, std::min(tiles, 2048 / tiles)));
-    k_sc_scan_hi<LINK><<<dim3(tiles, X.parts), kBlock, 0, s>>>(S, X, dst);
+    k_sc_scan_hi<LINK><<<dim3(tiles, X.parts), kBlock, 0, s>>>(S, X);
   }
   tmark(S, 1, true, s);
 }
@@ -1030,6 +1391,7 @@ __global__ void k_sc_enter(State S, Mx X, int merges, int direct) {
     c->n_act = n;
     c->mx_merges = merges;
     c->mx_nterm = n;
+    c->mx_ran = 1;
     c->mx_terms += n;
     const long long pairs = (long long)n * (n - 1);
     c->cluster_evals += pairs;
@@ -1038,7 +1400,15 @@ __global__ void k_sc_enter(State S, Mx X, int merges, int direct) {
   }
 }
 
+inline size_t mat_tail_bytes(int stop) { return tail_rec_bytes(stop) + (size_t)stop * (stop - 1) / 2 * sizeof(double); }
+inline size_t cen_tail_bytes(int stop, int d) { return tail_rec_bytes(stop) + (size_t)stop * (2 * d + 2) * sizeof(double); }
+
 }  // namespace
+
+int mx_tail_max(int linkage, int d) {
+  if (!centroid_link(linkage)) return kMatTail;
+  return std::max(1, std::min(kCenTail, kCenTailNd / d));
+}
 
 size_t mx_layout(Mx &X, char *base, int m, int n) {
   size_t off = 0;
@@ -1062,7 +1432,6 @@ size_t mx_layout(Mx &X, char *base, int m, int n) {
   X.place = (int *)take((size_t)m * sizeof(int));
   X.beg = (int *)take((size_t)m * sizeof(int));
   X.own = (int *)take((size_t)n * sizeof(int));
-  X.cur = 0;
   return off + 256;
 }
 
@@ -1075,8 +1444,8 @@ void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_
   else launch_build<kAverage>(S, X, px, m, s);
   tmark(S, 2, true, s);
   tmark(S, 1, false, s);
-  if (S.linkage == kComplete) launch_pass<kComplete, true>(S, X, m, 0, s);
-  else launch_pass<kAverage, true>(S, X, m, 0, s);
+  if (S.linkage == kComplete) launch_pass<kComplete, true>(S, X, m, s);
+  else launch_pass<kAverage, true>(S, X, m, s);
   tmark(S, 1, true, s);
 }
 
@@ -1102,41 +1471,50 @@ size_t sc_layout(Mx &X, char *base, int m) {
   X.mpair = (int4 *)take((size_t)(m / 2 + 1) * sizeof(int4));
   X.pv = (double *)take((size_t)kScanParts * m * sizeof(double));
   X.pc = (int2 *)take((size_t)kScanParts * m * sizeof(int2));
-  X.cur = 0;
   return off + 256;
 }
 
 void launch_sc_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s) {
   k_sc_enter<<<nblk(direct ? (long long)m * S.d : m), kBlock, 0, s>>>(S, X, merges, direct ? 1 : 0);
-  if (S.linkage == kWard) launch_scan<kWard>(S, X, m, 0, s);
-  else launch_scan<kAvgSq>(S, X, m, 0, s);
+  if (S.linkage == kWard) launch_scan<kWard>(S, X, m, true, s);
+  else launch_scan<kAvgSq>(S, X, m, true, s);
 }
 
-void launch_mx_book(State &S, Mx &X, hipStream_t s) {
+void launch_mx_round(State &S, Mx &X, int bound, hipStream_t s) {
+  const int stop = mx_tail_max(S.linkage, S.d);
   switch (S.linkage) {
-  case kComplete: k_mx_book<kComplete><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
-  case kAverage: k_mx_book<kAverage><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
-  case kWard: k_mx_book<kWard><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
-  default: k_mx_book<kAvgSq><<<1, kBookThreads, 0, s>>>(S, X, X.cur); break;
+  case kComplete: k_mx_book<kComplete><<<1, kBookThreads, 0, s>>>(S, X, stop); break;
+  case kAverage: k_mx_book<kAverage><<<1, kBookThreads, 0, s>>>(S, X, stop); break;
+  case kWard: k_mx_book<kWard><<<1, kBookThreads, 0, s>>>(S, X, stop); break;
+  default: k_mx_book<kAvgSq><<<1, kBookThreads, 0, s>>>(S, X, stop); break;
   }
-}
-
-void launch_mx_pass(State &S, Mx &X, int bound, hipStream_t s) {
+  if (S.phases) (void)hipEventRecord(S.rev[3], s);
   switch (S.linkage) {
   case kComplete:
     tmark(S, 1, false, s);
-    launch_pass<kComplete, false>(S, X, bound, X.cur, s);
+    launch_pass<kComplete, false>(S, X, bound, s);
     tmark(S, 1, true, s);
     break;
   case kAverage:
     tmark(S, 1, false, s);
-    launch_pass<kAverage, false>(S, X, bound, X.cur, s);
+    launch_pass<kAverage, false>(S, X, bound, s);
     tmark(S, 1, true, s);
     break;
-  case kWard: launch_scan<kWard>(S, X, bound, X.cur ^ 1, s); break;
-  default: launch_scan<kAvgSq>(S, X, bound, X.cur ^ 1, s); break;
+  case kWard: launch_scan<kWard>(S, X, bound, false, s); break;
+  default: launch_scan<kAvgSq>(S, X, bound, false, s); break;
   }
-  X.cur ^= 1;
+}
+
+void launch_mx_tail(State &S, Mx &X, hipStream_t s) {
+  const int stop = mx_tail_max(S.linkage, S.d);
+  tmark(S, 1, false, s);
+  switch (S.linkage) {
+  case kComplete: k_mx_tail<kComplete><<<1, kTailThreads, mat_tail_bytes(stop), s>>>(S, X, stop); break;
+  case kAverage: k_mx_tail<kAverage><<<1, kTailThreads, mat_tail_bytes(stop), s>>>(S, X, stop); break;
+  case kWard: k_sc_tail<kWard><<<1, kTailThreads, cen_tail_bytes(stop, S.d), s>>>(S, X, stop); break;
+  default: k_sc_tail<kAvgSq><<<1, kTailThreads, cen_tail_bytes(stop, S.d), s>>>(S, X, stop); break;
+  }
+  tmark(S, 1, true, s);
 }
 
 }  // namespace pc
