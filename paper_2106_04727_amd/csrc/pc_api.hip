@@ -774,9 +774,13 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   if (points_on_device) {
     launch_check_finite(xdev, (long long)n * d, S.cnt, s);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(ctx->hcnt, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    if (ctx->hcnt->nonfinite) return fail(PC_ERR_NONFINITE_INPUT, "non-finite coordinate");
+    // (a direct call reads the flag with its first rounds: their kernels end on
+    // any input)
+    if (!direct) {
+      HIPCHK(hipMemcpyAsync(ctx->hcnt, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+      if (ctx->hcnt->nonfinite) return fail(PC_ERR_NONFINITE_INPUT, "non-finite coordinate");
+    }
   }
   if (!direct) launch_init(S, xdev, s);
   HIPCHK(hipGetLastError());
@@ -838,6 +842,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
         HIPCHK(hipMemcpyAsync(&h, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         take_times();
+        if (h.nonfinite == 1) return fail(PC_ERR_NONFINITE_INPUT, "non-finite coordinate");
         if (h.mx_err == 1) return fail(PC_ERR_DEVICE, "a cluster found no neighbour");
         if (h.mx_err) return fail(PC_ERR_DEVICE, "round merged nothing");
         if (S.phases) {

@@ -3998,6 +3998,61 @@ __global__ void k_write_rows(State S, int m, OutRow *out) {
   out[i] = o;
 }
 
+// Few rows: a row's place is the number of rows with smaller keys, counted
+// against all of them (the keys differ: clusters with the same lowest point
+// differ in size). Two launches instead of the radix sorts' forty; the m^2
+// comparisons are cheaper up to kRankMax rows (2,000 rows 8 us against 130,
+// 16,000 rows 95 us against 190). A block counts 16 rows, 4 per wavefront, over
+// chunks of 256 keys staged in LDS.
+constexpr int kRankMax = 16384;
+constexpr int kRankRows = 4;  // per wavefront
+__global__ __launch_bounds__(kBlock) void k_row_rank(State S, int m, int lob) {
+  __shared__ unsigned long long k1[kBlock], k2[kBlock];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int r0 = blockIdx.x * kRankRows * (kBlock / kWave) + w * kRankRows;
+  auto key2 = [&](int r) { return ((unsigned long long)(unsigned)S.row_size[r] << lob) | (unsigned)S.row_lo[r]; };
+  unsigned long long a1[kRankRows], a2[kRankRows];
+  int cnt[kRankRows];
+#pragma unroll
+  for (int j = 0; j < kRankRows; ++j) {
+    const int r = min(r0 + j, m - 1);
+    a1[j] = pos_bits(S.row_eff[r]);
+    a2[j] = key2(r);
+    cnt[j] = 0;
+  }
+  for (int c = 0; c < m; c += kBlock) {
+    __syncthreads();
+    const int r = c + threadIdx.x;
+    k1[threadIdx.x] = r < m ? pos_bits(S.row_eff[r]) : ~0ull;  // (past the end: larger than every key)
+    k2[threadIdx.x] = r < m ? key2(r) : ~0ull;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kBlock; t += kWave) {
+      const unsigned long long x = k1[t + lane], y = k2[t + lane];
+#pragma unroll
+      for (int j = 0; j < kRankRows; ++j)
+        cnt[j] += __popcll(__ballot(x < a1[j] || (x == a1[j] && y < a2[j])));
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kRankRows; ++j)
+    if (lane == j && r0 + j < m) S.scan[r0 + j] = cnt[j];
+}
+__global__ void k_write_ranked(State S, int m, OutRow *out) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= m) return;
+  const int n = S.n;
+  int a = S.row_na[r], b = S.row_nb[r];
+  a = a < n ? a : n + S.scan[a - n];
+  b = b < n ? b : n + S.scan[b - n];
+  OutRow o;
+  o.a = a < b ? a : b;
+  o.b = a < b ? b : a;
+  o.h = S.row_h[r];
+  o.size = S.row_size[r];
+  out[S.scan[r]] = o;
+}
+
 inline int nblk(long long n, int cap = 4096) {
   long long b = (n + kBlock - 1) / kBlock;
   if (b < 1) b = 1;
@@ -4459,6 +4514,12 @@ void launch_finalize(State &S, void *out_rows, hipStream_t s) {
   // sizes and point indices are at most n: the key needs 2 lob bits only
   int lob = 1;
   while ((1LL << lob) <= (long long)S.n) ++lob;
+  if (m <= kRankMax) {
+    const int rows = kRankRows * (kBlock / kWave);
+    k_row_rank<<<(m + rows - 1) / rows, kBlock, 0, s>>>(S, m, lob);
+    k_write_ranked<<<b, kBlock, 0, s>>>(S, m, (OutRow *)out_rows);
+    return;
+  }
   k_row_keys2<<<b, kBlock, 0, s>>>(S, m, lob);
   radix_sort_pairs(S.sk0, S.sk1, S.sv0, S.sv1, m, 2 * lob, S.hist, S.sws, s);
   k_row_keys1<<<b, kBlock, 0, s>>>(S, m);

@@ -85,3 +85,11 @@ def test_matrix_without_room(pc, link):
         assert np.array_equal(Za[:, [0, 1, 3]], Zb[:, [0, 1, 3]])
         assert np.allclose(Za[:, 2], Zb[:, 2], rtol=RTOL[link], atol=0.0)
         ctx.close()
+
+
+@pytest.mark.parametrize("n", [16385, 16386])
+def test_row_order_by_rank_and_by_sort(pc, n):
+    """16384 rows are ordered by counting, one row more by the radix sorts."""
+    x = synth.blobs(n, 2, 300, 0.01, 31)
+    Zo, _ = oracle.nnchain(x, "ward", threads=8)
+    assert np.array_equal(pc.hac(x, "ward"), oracle.canonical(Zo, n))
