@@ -597,6 +597,31 @@ static bool matrix_room(pc_context *ctx, Mx &X, int m, int n, int linkage) {
   return true;
 }
 
+}  // extern "C"
+
+namespace pc {
+// Device bytes beyond pc_hac_workspace_bytes with which a call can keep its
+// matrix or scan records (it runs without them too). The serving layer adds
+// them to a request's reservation where its budget has the room.
+size_t matrix_extra_bytes(int64_t n, int32_t d, int32_t linkage, const pc_options *opt) {
+  if (opt && (!opt->prune || (opt->cache_slots >= 0 && !centroid_link(linkage)))) return 0;
+  if (search_pinned()) return 0;
+  const int m = (int)std::min<int64_t>(n, matrix_max(linkage, d, n));
+  if (m < 2) return 0;
+  Mx X;
+  const size_t need = centroid_link(linkage) ? sc_layout(X, nullptr, m) : mx_layout(X, nullptr, m, (int)n);
+  if (m < n) return need;
+  // a call that starts with the matrix grows no candidate, pair or cache buffers
+  State S;
+  const size_t ws = layout(S, nullptr, n, d, linkage, true, opt ? opt->precision : 0);
+  const size_t part = (2 * ((size_t)(2 * n + 64) / 1024 + 1024) + 1) * sizeof(long long);
+  const size_t model = pc_hac_workspace_bytes(n, d, linkage, opt);
+  return ws + part + need > model ? ws + part + need - model : 0;
+}
+}  // namespace pc
+
+extern "C" {
+
 static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32_t d, int points_on_device,
                           int32_t linkage, const pc_options *opt, pc_merge *out, int out_on_device, void *stream,
                           pc_stats *stats, bool noalloc) {

@@ -36,6 +36,7 @@
 namespace pc {
 size_t context_bytes(const pc_context *c);
 void context_trim(pc_context *c);
+size_t matrix_extra_bytes(int64_t n, int32_t d, int32_t linkage, const pc_options *opt);
 void context_set_budget(pc_context *c, size_t bytes);
 bool context_over_budget(const pc_context *c);
 int context_device(const pc_context *c);
@@ -296,6 +297,11 @@ pc_status pc_server_submit(pc_server *s, const float *points, int64_t n, int32_t
   j->out = out;
   j->model = bytes;
   j->bytes = bytes;
+  if (s->fake_us <= 0.0) {
+    // room for the matrix of the late rounds, if a slot's share of the budget has it
+    const size_t want = bytes + pc::matrix_extra_bytes(n, d, linkage, opt);
+    if (want <= s->budget / (uint64_t)s->slots) j->bytes = want;
+  }
   {
     std::lock_guard<std::mutex> lk(s->mu);
     ++s->submitted;
