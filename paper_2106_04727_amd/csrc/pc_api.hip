@@ -118,14 +118,24 @@ size_t layout(State &S, char *base, int64_t n64, int d, int linkage, bool host_p
   S.gmin = c.take<unsigned long long>(gram ? d : 1);
   S.gmax = c.take<unsigned long long>(gram ? d : 1);
   S.gscale = c.take<double>(1);
-  // box tree: Ward / avg-2 at 3 <= d <= kTreeMaxDim (the call may still use another search)
-  const bool tree = centroid_link(linkage) && d >= 3 && d <= kTreeMaxDim;
-  S.term_pos = c.take<int>(gram || tree ? n : 1);
-  const size_t tnodes = n / 15 + 16;  // a 16-ary tree over n / 16 leaves (8 levels at most)
-  S.tree_lo = c.take<double>(tree ? tnodes * d : 1);
-  S.tree_hi = c.take<double>(tree ? tnodes * d : 1);
-  S.tree_nmin = c.take<int>(tree ? tnodes : 1);
-  S.tree_vmin = c.take<double>(tree ? tnodes : 1);
+  // box tree: Ward / avg-2 at d <= kTreeMaxDim (the call may still use another
+  // search). Up to d = 2 its arrays lie over the grid's, of which a call uses
+  // one or the other.
+  const bool tree = centroid_link(linkage) && d <= kTreeMaxDim;
+  const size_t tnodes = n / 15 + 16;  // (a 64-ary tree over n / 64 leaves needs fewer)
+  if (tree && d <= 2 && n >= 64) {
+    S.term_pos = S.cell_of;
+    S.tree_lo = (double *)S.cell_cnt;
+    S.tree_hi = (double *)S.cell_start;
+    S.tree_vmin = (double *)S.cell_nmin;
+    S.tree_nmin = (int *)(S.tree_vmin + tnodes);
+  } else {
+    S.term_pos = c.take<int>(gram || tree ? n : 1);
+    S.tree_lo = c.take<double>(tree ? tnodes * d : 1);
+    S.tree_hi = c.take<double>(tree ? tnodes * d : 1);
+    S.tree_nmin = c.take<int>(tree ? tnodes : 1);
+    S.tree_vmin = c.take<double>(tree ? tnodes : 1);
+  }
   S.t_best = c.take<double>(n);
   S.t_key = c.take<unsigned long long>(n);
   S.t_beta = c.take<double>(n);
@@ -524,16 +534,14 @@ static long long initial_cap(const pc_context *ctx, const Buf &b, long long want
 // Largest number of active clusters that Ward's and avg-2's scan rounds take: a
 // scan costs about m^2 / 2 keys of d terms, the other searches of those rounds
 // little but their launches and host reads. Measured (whole calls, Ward, ms):
-//   65K points d = 2: none 5.9, 4096 clusters 3.9, 8192 3.7, 16384 3.8, 32768 4.0
-//   65K points d = 3 (box tree before): none 23.1, 8192 14.4, 16384 11.2, 32768 8.7
-//   65K points d = 5: none 18.7, 8192 13.2, 16384 12.8, 32768 13.3
-//   20K points d = 16: none 11.9, 4096 6.5, 8192 6.1, 16384 6.0, all 7.2
+//   65K points d = 2: none 4.9, 4096 clusters 2.5, 8192 2.4, 12288 2.5, 16384 2.9
+//   65K points d = 3: none 5.1, 4096 3.0, 8192 2.9, 12288 3.2, 32768 5.1
+//   65K points d = 8: none 7.2, 4096 4.9, 8192 4.9, 16384 5.5
+//   20K points d = 16 (Gram search before): none 11.9, 4096 6.5, 8192 6.1, 16384 6.0, all 7.2
 //   20K points d = 64: none 17.5, 4096 11.1, 8192 11.1, 16384 14.4
 //   20K points d = 128: none 23.5, 4096 16.9, 8192 17.5, 16384 24.8
 static int scan_max(int d) {
-  if (d <= 2) return 12288;
-  if (d == 3) return 32768;
-  if (d <= 8) return 16384;
+  if (d <= 8) return 8192;
   if (d <= 16) return 12288;
   if (d <= 48) return 8192;
   return d <= 96 ? 6144 : 4096;
@@ -695,22 +703,25 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   S.prune = prune;
   S.timing = (opt && (opt->timing & PC_TIME_KERNELS)) ? 1 : 0;
   S.phases = (opt && (opt->timing & PC_TIME_PHASES)) ? 1 : 0;
-  // Ward and avg-2 at 3 <= d <= 5 search a box tree over Morton-ordered
-  // centroids while many clusters are active and the Gram search once at most
-  // tree_gram_switch are (at d = 3, where there is no Gram search, the tree
-  // throughout); from d = 6 the Gram search alone (measured faster at 8-D).
-  // Without the tree: the centroid grid up to d = 5, the Gram search above.
-  // Tuning knobs: PC_TREE_MAX_DIM (0 = no tree, at most 8),
-  // PC_TREE_GRAM_SWITCH (0 = tree in every round), PC_GRAM_MIN_DIM.
-  int tree_max = 5;
+  // Ward and avg-2 up to d = 8 search a box tree over centroids in Hilbert
+  // order (whole calls, 1M points, ms: d = 2 Ward grid 10.8, tree 7.0; d = 1
+  // 124 / 5.2; 200K points: d = 3 14.4 / 6.5, d = 5 Gram search 84.9, tree 6.8,
+  // d = 8 96 / 10.6 on mixtures, 87 / 32 on uniform points), the Gram search
+  // above. Without the tree: the centroid grid up to d = 5, the Gram search above.
+  // Tuning knobs: PC_TREE_MAX_DIM (0 = no tree, at most 8), PC_TREE_GRAM_SWITCH
+  // (rounds with at most that many active clusters take the Gram search from
+  // d = 4 on; 0, the default: none), PC_GRAM_MIN_DIM.
+  int tree_max = kTreeMaxDim;
   if (const char *e = getenv("PC_TREE_MAX_DIM")) tree_max = std::min(kTreeMaxDim, atoi(e));
-  const bool tree_ok = prune && centroid_link(linkage) && d >= 3 && d <= tree_max;
+  const bool tree_ok = prune && centroid_link(linkage) && d <= tree_max && n < (1LL << 30);
   int gram_min = centroid_link(linkage) && !tree_ok ? 6 : kGramMinDim;
   if (const char *e = getenv("PC_GRAM_MIN_DIM")) gram_min = std::max(kGramMinDim, atoi(e));
   const bool gram_ok = prune && d >= gram_min && d <= kGramMaxDim;
-  long long tree_gram_switch = 200000;  // measured on the paper's 1M-point 5-D sets (flat from 150K to 250K)
+  long long tree_gram_switch = 0;
   if (const char *e = getenv("PC_TREE_GRAM_SWITCH")) tree_gram_switch = atoll(e);
-  // the first round's search (tree_ok also fixes the Morton order of the init)
+  // no Gram search in any round of a call that searches the tree in all of them
+  const bool gram_used = gram_ok && (!tree_ok || tree_gram_switch > 0);
+  // the first round's search (tree_ok also fixes the axes of the initial order)
   S.tree = tree_ok ? 1 : 0;
   S.gram = (!tree_ok && gram_ok) ? 1 : 0;
   S.kt = &ctx->ktimer;
@@ -750,7 +761,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     ctx->mat_used = true;
     cache_slots = 0;
   }
-  if (centroid_link(linkage) && gram_ok && !direct) {
+  if (centroid_link(linkage) && gram_used && !direct) {
     pc_status st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, std::max<long long>(1 << 22, 4 * n),
                                                  kCandBytes, 1024));
     if (st != PC_OK) return st;
@@ -886,7 +897,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     }
     if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
     if (tree_ok) {
-      const bool use_tree = !gram_ok || tree_gram_switch <= 0 || nact > tree_gram_switch;
+      const bool use_tree = !gram_used || nact > tree_gram_switch;
       S.tree = use_tree ? 1 : 0;
       S.gram = use_tree ? 0 : 1;
     }

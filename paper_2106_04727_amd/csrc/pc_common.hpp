@@ -23,8 +23,8 @@ constexpr int kBlkMaxDim = 16;     // complete: 64-point block boxes prune inter
 constexpr int kSupDirs = 64;       // d == 2, complete: support points in 64 fixed directions
 constexpr int kGramMinDim = 4;     // Gram (MFMA) search from this d on
 constexpr int kGramMaxDim = 128;   // largest d of the Gram search (K = 128 in LDS)
-constexpr int kTreeMaxDim = 8;     // Ward / avg-2: box-tree search over Morton-ordered centroids up to this d
-constexpr int kMortonAxes = 8;     // at most this many axes in the initial Morton order
+constexpr int kTreeMaxDim = 8;     // Ward / avg-2: box-tree search over centroids in curve order up to this d
+constexpr int kCurveAxes = 8;      // at most this many axes in the initial Hilbert order
 // MFMA depth of the Gram tiles: the dimension plus two augmented
 // coordinates (the norm terms of the bound pass), in steps of 16
 inline int gram_kp(int d) {
@@ -125,8 +125,8 @@ struct Counters {
   long long n_pairs;
   long long n_cand;
   long long n_pend;
-  unsigned long long bb_lo[kMortonAxes];  // ordered bits of the per-axis range
-  unsigned long long bb_hi[kMortonAxes];  // (points at init, active centroids per round)
+  unsigned long long bb_lo[kCurveAxes];  // ordered bits of the per-axis range
+  unsigned long long bb_hi[kCurveAxes];  // (points at init, active centroids per round)
   long long cluster_evals;
   long long point_pairs;
   long long n_tiles;
@@ -335,14 +335,16 @@ struct State {
   unsigned long long *gmin, *gmax;  // per-dimension ordered bits of the centroid range
   double *gscale;       // 1 value
   int *term_pos;        // active-list index of each terminal
-  // box tree (Ward / avg-2, 3 <= d <= kTreeMaxDim): an implicit 16-ary tree
-  // over the active list (leaves of 16 consecutive clusters); per node the FP64
-  // box of the centroids below it, the smallest size and smallest spread term.
-  // Level l holds tree_cnt[l] nodes from node tree_off[l]; level tree_top is the root.
+  // box tree (Ward / avg-2, d <= kTreeMaxDim): an implicit 64-ary tree over the
+  // active list (leaves of 64 consecutive clusters); per node the FP64 box of
+  // the centroids below it, the smallest size and smallest spread term. Level l
+  // holds tree_cnt[l] nodes from node tree_off[l]; level tree_top, of at most 64
+  // nodes, is the first tested. With the tree, item_cen and the boxes are
+  // coordinate-major.
   int tree;
   int tree_top;
   int tree_cnt[8], tree_off[8];
-  double *tree_lo, *tree_hi;  // d per node
+  double *tree_lo, *tree_hi;
   int *tree_nmin;
   double *tree_vmin;
   int tb0, tb1;      // terminals [tb0, tb1) of the current Gram batch

@@ -1,6 +1,6 @@
 // Device-wide primitives: exclusive scan (the prefix sums behind every
 // parallel filter of Alg. 1) and a stable LSD radix sort of (key, value)
-// pairs (initial Morton layout and the final row order).
+// pairs (initial curve order and the final row order).
 #include "pc_common.hpp"
 
 namespace pc {

@@ -71,6 +71,28 @@ __device__ __forceinline__ long long wave_sum_ll(long long v) {
   return v;
 }
 
+// the smallest of 64 lanes' doubles, for all lanes: rotations within the rows
+// of 16 lanes (no trip through LDS), then the four rows through scalars
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_min_f64(double v) {
+  v = fmin(v, dpp_f64<0x128>(v));  // row_ror:8
+  v = fmin(v, dpp_f64<0x124>(v));
+  v = fmin(v, dpp_f64<0x122>(v));
+  v = fmin(v, dpp_f64<0x121>(v));
+  return fmin(fmin(lane_f64(v, 0), lane_f64(v, 16)), fmin(lane_f64(v, 32), lane_f64(v, 48)));
+}
+
 // block-wide: add a per-thread count into a global counter with one atomic per wave
 __device__ __forceinline__ void count_add(long long *dst, long long v) {
   v = wave_sum_ll(v);
@@ -109,7 +131,7 @@ __global__ void k_reset_round(Counters *c) {
   c->n_pairs = 0;
   c->pair_overflow = 0;
   c->n_min = 0x7fffffff;
-  for (int a = 0; a < kMortonAxes; ++a) {
+  for (int a = 0; a < kCurveAxes; ++a) {
     c->bb_lo[a] = ~0ull;
     c->bb_hi[a] = 0ull;
   }
@@ -137,22 +159,22 @@ __global__ void k_check_finite(const float *x, long long count, Counters *c) {
 }
 
 __global__ void k_point_bbox(const float *x, int n, int d, int axes, Counters *c) {
-  unsigned long long lo[kMortonAxes], hi[kMortonAxes];
+  unsigned long long lo[kCurveAxes], hi[kCurveAxes];
 #pragma unroll
-  for (int a = 0; a < kMortonAxes; ++a) {
+  for (int a = 0; a < kCurveAxes; ++a) {
     lo[a] = ~0ull;
     hi[a] = 0ull;
   }
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
 #pragma unroll
-    for (int a = 0; a < kMortonAxes; ++a)
+    for (int a = 0; a < kCurveAxes; ++a)
       if (a < axes) {
         unsigned long long b = ordered_bits((double)x[(size_t)i * d + a]);
         lo[a] = b < lo[a] ? b : lo[a];
         hi[a] = b > hi[a] ? b : hi[a];
       }
 #pragma unroll
-  for (int a = 0; a < kMortonAxes; ++a) {
+  for (int a = 0; a < kCurveAxes; ++a) {
     if (a >= axes) break;  // uniform: axes is a kernel argument
     unsigned long long l = block_reduce<unsigned long long, true>(lo[a]);
     unsigned long long h = block_reduce<unsigned long long, false>(hi[a]);
@@ -163,48 +185,53 @@ __global__ void k_point_bbox(const float *x, int n, int d, int axes, Counters *c
   }
 }
 
-__device__ __forceinline__ unsigned spread16(unsigned v) {
-  v &= 0xffffu;
-  v = (v | (v << 8)) & 0x00ff00ffu;
-  v = (v | (v << 4)) & 0x0f0f0f0fu;
-  v = (v | (v << 2)) & 0x33333333u;
-  v = (v | (v << 1)) & 0x55555555u;
-  return v;
-}
+// Hilbert code of the first `axes` coordinates: clusters close in the list are
+// close in space, and 64 consecutive ones lie in one compact box (a Morton run
+// jumps across the cell borders it crosses, and its box with it). Transform of
+// the quantised coordinates by J. Skilling, "Programming the Hilbert curve"
+// (AIP Conf. Proc. 707, 2004), then their bits interleaved. One or two axes: 16
+// bits each; three to eight axes: 64 / axes bits each.
+__device__ __forceinline__ int curve_bits(int axes) { return axes <= 2 ? 16 : 64 / axes; }
 
-// Morton (Z-order) code of the first `axes` coordinates: spatially close
-// clusters get close slots, so one wavefront's terminals search nearby cells
-// (grid) or lie in one small box (box tree). One or two axes: 16 bits each;
-// three to eight axes: 64 / axes bits each, interleaved into 64 bits.
-__device__ __forceinline__ int morton_bits(int axes) { return axes <= 2 ? 16 : 64 / axes; }
-
-__global__ void k_morton(const float *x, int n, int d, int axes, const Counters *c,
-                         unsigned long long *key, unsigned *val) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int bits = morton_bits(axes);
-  const double top = (double)((1u << bits) - 1u);
-  unsigned q[kMortonAxes];
+template <int AXES>
+__device__ __forceinline__ unsigned long long curve_code(unsigned *q, int bits) {
+  for (unsigned m = 1u << (bits - 1); m > 1; m >>= 1) {
+    const unsigned low = m - 1;
 #pragma unroll
-  for (int a = 0; a < kMortonAxes; ++a) {
-    q[a] = 0;
-    if (a < axes) {
-      double lo = from_ordered_bits(c->bb_lo[a]), hi = from_ordered_bits(c->bb_hi[a]);
-      double t = hi > lo ? ((double)x[(size_t)i * d + a] - lo) / (hi - lo) : 0.0;
-      t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
-      q[a] = (unsigned)(t * top);
+    for (int a = 0; a < AXES; ++a) {
+      // a set bit inverts the lower bits of axis 0, a clear one exchanges them
+      const unsigned t = (q[a] & m) ? low : 0u, x = (q[a] & m) ? 0u : (q[0] ^ q[a]) & low;
+      q[0] ^= t ^ x;
+      q[a] ^= x;
     }
   }
-  if (axes <= 2) {
-    key[i] = axes == 2 ? (unsigned long long)(spread16(q[0]) | (spread16(q[1]) << 1)) : q[0];
-  } else {
-    unsigned long long k = 0;
-    for (int b = bits - 1; b >= 0; --b)
 #pragma unroll
-      for (int a = 0; a < kMortonAxes; ++a)
-        if (a < axes) k = (k << 1) | (unsigned long long)((q[a] >> b) & 1u);
-    key[i] = k;
+  for (int a = 1; a < AXES; ++a) q[a] ^= q[a - 1];
+  unsigned t = 0;
+  for (unsigned m = 1u << (bits - 1); m > 1; m >>= 1)
+    if (q[AXES - 1] & m) t ^= m - 1;
+  unsigned long long k = 0;
+  for (int b = bits - 1; b >= 0; --b)
+#pragma unroll
+    for (int a = 0; a < AXES; ++a) k = (k << 1) | (unsigned long long)(((q[a] ^ t) >> b) & 1u);
+  return k;
+}
+
+template <int AXES>
+__global__ void k_curve(const float *x, int n, int d, const Counters *c, unsigned long long *key, unsigned *val) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int bits = curve_bits(AXES);
+  const double top = (double)((1u << bits) - 1u);
+  unsigned q[AXES];
+#pragma unroll
+  for (int a = 0; a < AXES; ++a) {
+    const double lo = from_ordered_bits(c->bb_lo[a]), hi = from_ordered_bits(c->bb_hi[a]);
+    double t = hi > lo ? ((double)x[(size_t)i * d + a] - lo) / (hi - lo) : 0.0;
+    t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
+    q[a] = (unsigned)(t * top);
   }
+  key[i] = AXES == 1 ? q[0] : curve_code<AXES>(q, bits);
   val[i] = (unsigned)i;
 }
 
@@ -1724,190 +1751,275 @@ __global__ __launch_bounds__(kBlock) void k_nn_full(State S, const int *list, co
 }
 
 // ------------------------------------------------------ box-tree search ----
-// Ward and avg-2 at 3 <= d <= kTreeMaxDim. The active list is in slot order,
-// a Morton order over up to eight axes (clusters inherit the slot of their
+// Ward and avg-2 at d <= kTreeMaxDim. The active list is in slot order, a
+// Hilbert order over up to eight axes (clusters inherit the slot of their
 // lower-ID child, so the order stays spatially coherent as they merge). An
-// implicit 16-ary tree is built over it every round: leaves of kTreeFan
-// consecutive clusters, each level above grouping kTreeFan nodes, every node
-// with the FP64 box of its centroids, its smallest size and smallest spread
-// term (the range query of Alg. 3 over a bounding-box tree instead of a k-d
-// tree). One thread per terminal evaluates its own leaf first (a near
-// neighbour and a tight bound), then walks outward, bottom up, depth first
-// and without a stack (a node's parent is its index / 16), entering a node
-// only if its lower bound does not exceed the thread's bound (Sec. 4.1, 4.2:
-// the Ward and avg-2 keys grow with the centroid distance). Every loop step
-// does one box test or one candidate, so lanes of a wavefront stay in step.
-// A bound takes the key's FP64 operations in the same order on values no
+// implicit 64-ary tree is built over it every round: leaves of 64 consecutive
+// clusters, each level above grouping 64 nodes, every node with the FP64 box of
+// its centroids, its smallest size and smallest spread term (the range query of
+// Alg. 3 over a bounding-box tree instead of a k-d tree). One wavefront takes
+// kTreeTerms neighbouring terminals: it evaluates their own leaves first (near
+// neighbours and tight bounds), then walks the tree from the top, its 64 lanes
+// testing the 64 children of a node, or evaluating the 64 clusters of a leaf,
+// for each terminal that has not ruled the node out (Sec. 4.1, 4.2: the Ward
+// and avg-2 keys grow with the centroid distance). All loads are contiguous
+// and shared by the wavefront's terminals, and no lane waits for another's
+// walk. A bound takes the key's FP64 operations in the same order on values no
 // larger than the key's operands, so it never exceeds a key (rounding is
 // monotone); pruning is strict, so equal keys reach the tie-break.
-constexpr int kTreeFan = 16;
+constexpr int kTreeFan = 64;
+constexpr int kTreeTerms = 4;
 
-__global__ void k_tree_items(State S) {
+__device__ __forceinline__ size_t tree_stride(const State &S) { return (size_t)S.n / 15 + 16; }  // nodes per coordinate
+
+// items in active-list order (coordinate-major) and the leaves' boxes: a
+// wavefront per leaf
+__global__ __launch_bounds__(kBlock) void k_tree_items(State S) {
   const int nact = S.cnt->n_act, d = S.d;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x) {
-    const int s = S.act[i];
-    S.item_meta[i] = make_int4(s, S.csize[s], S.cid[s], 0);
-    for (int k = 0; k < d; ++k) S.item_cen[(size_t)i * d + k] = S.wcen[(size_t)s * d + k];
-    if (S.linkage == kAvgSq) S.item_v[i] = S.cmv[s];
-  }
-}
-
-// one thread per node of level `lev`: the box of its (up to kTreeFan)
-// children, which are items for the leaves (lev 0)
-__global__ void k_tree_level(State S, int lev) {
-  const int d = S.d;
-  const int cnt = S.tree_cnt[lev];
-  const int nsrc = lev == 0 ? S.cnt->n_act : S.tree_cnt[lev - 1];
-  const int src0 = lev == 0 ? 0 : S.tree_off[lev - 1];
-  const int dst0 = S.tree_off[lev];
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < cnt; j += gridDim.x * blockDim.x) {
-    const int c0 = j * kTreeFan, c1 = min(c0 + kTreeFan, nsrc);
-    int nm = 0x7fffffff;
-    double vm = INFINITY;
-    for (int c = c0; c < c1; ++c) {
-      const int sz = lev == 0 ? S.item_meta[c].y : S.tree_nmin[src0 + c];
-      nm = sz < nm ? sz : nm;
-      if (S.linkage == kAvgSq) {
-        const double v = lev == 0 ? S.item_v[c] : S.tree_vmin[src0 + c];
-        vm = v < vm ? v : vm;
-      }
+  const int lane = threadIdx.x & (kWave - 1);
+  const size_t tn = tree_stride(S);
+  for (int leaf = (blockIdx.x * kBlock + threadIdx.x) / kWave; leaf * kTreeFan < nact; leaf += gridDim.x * kBlock / kWave) {
+    const int i = leaf * kTreeFan + lane;
+    const bool in = i < nact;
+    const int s = S.act[in ? i : nact - 1];
+    const int sz = S.csize[s];
+    const double v = S.linkage == kAvgSq ? S.cmv[s] : 0.0;
+    if (in) {
+      S.item_meta[i] = make_int4(s, sz, S.cid[s], 0);
+      if (S.linkage == kAvgSq) S.item_v[i] = v;
     }
     for (int k = 0; k < d; ++k) {
-      double lo = INFINITY, hi = -INFINITY;
-      for (int c = c0; c < c1; ++c) {
-        const double a = lev == 0 ? S.item_cen[(size_t)c * d + k] : S.tree_lo[(size_t)(src0 + c) * d + k];
-        const double b = lev == 0 ? a : S.tree_hi[(size_t)(src0 + c) * d + k];
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
+      const double c = S.wcen[(size_t)s * d + k];
+      if (in) S.item_cen[(size_t)k * S.n + i] = c;
+      const double lo = wave_min(c), hi = wave_max(c);  // (lanes past the end repeat the last item)
+      if (lane == 0) {
+        S.tree_lo[k * tn + leaf] = lo;
+        S.tree_hi[k * tn + leaf] = hi;
       }
-      S.tree_lo[(size_t)(dst0 + j) * d + k] = lo;
-      S.tree_hi[(size_t)(dst0 + j) * d + k] = hi;
     }
-    S.tree_nmin[dst0 + j] = nm;
-    S.tree_vmin[dst0 + j] = vm;
+    const int nm = wave_min(sz);
+    const double vm = wave_min(v);
+    if (lane == 0) {
+      S.tree_nmin[leaf] = nm;
+      S.tree_vmin[leaf] = vm;
+    }
   }
 }
 
-// lower bound of the key of the terminal (centroid ct, size nt, spread term
-// vt) and any cluster inside node `node`
+// boxes of the nodes of level `lev` >= 1 from their children: a wavefront per node
+__global__ __launch_bounds__(kBlock) void k_tree_level(State S, int lev) {
+  const int d = S.d, cnt = S.tree_cnt[lev], nsrc = S.tree_cnt[lev - 1];
+  const int src0 = S.tree_off[lev - 1], dst0 = S.tree_off[lev];
+  const int lane = threadIdx.x & (kWave - 1);
+  const size_t tn = tree_stride(S);
+  for (int j = (blockIdx.x * kBlock + threadIdx.x) / kWave; j < cnt; j += gridDim.x * kBlock / kWave) {
+    const int c = src0 + min(j * kTreeFan + lane, nsrc - 1);
+    for (int k = 0; k < d; ++k) {
+      const double lo = wave_min(S.tree_lo[k * tn + c]), hi = wave_max(S.tree_hi[k * tn + c]);
+      if (lane == 0) {
+        S.tree_lo[k * tn + dst0 + j] = lo;
+        S.tree_hi[k * tn + dst0 + j] = hi;
+      }
+    }
+    const int nm = wave_min(S.tree_nmin[c]);
+    const double vm = wave_min(S.tree_vmin[c]);
+    if (lane == 0) {
+      S.tree_nmin[dst0 + j] = nm;
+      S.tree_vmin[dst0 + j] = vm;
+    }
+  }
+}
+
+// The wavefront's terminals (uniform but for bv, bk: each lane's own best).
+template <int MAXD>
+struct TreeTerms {
+  double ct[kTreeTerms][MAXD], nt[kTreeTerms], vt[kTreeTerms], beta[kTreeTerms];
+  int pos[kTreeTerms];
+  double bv[kTreeTerms];
+  unsigned long long bk[kTreeTerms];
+  int l0, l1;  // leaves evaluated at the start
+  long long evals, boxes;
+};
+
+// the 64 clusters of a leaf, for the terminals of `want`
 template <int LINK, int MAXD>
-__device__ __forceinline__ double tree_lb(const State &S, int node, const double *ct, double nt, double vt, int d) {
-  double q = 0.0;
+__device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD> &W, int leaf, unsigned want, int nact) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int i = min(leaf * kTreeFan + lane, nact - 1);  // (past the end: the last item again)
+  double cv[MAXD];
 #pragma unroll
-  for (int k = 0; k < MAXD; ++k)
-    if (k < d) {
-      const double lo = S.tree_lo[(size_t)node * d + k], hi = S.tree_hi[(size_t)node * d + k];
-      const double g = lo > ct[k] ? lo - ct[k] : (ct[k] > hi ? ct[k] - hi : 0.0);
+  for (int k = 0; k < MAXD; ++k) cv[k] = k < S.d ? S.item_cen[(size_t)k * S.n + i] : 0.0;
+  const int4 mt = S.item_meta[i];
+  const double nc = (double)mt.y, vc = LINK == kAvgSq ? S.item_v[i] : 0.0;
+#pragma unroll
+  for (int j = 0; j < kTreeTerms; ++j) {
+    if (!((want >> j) & 1u)) continue;  // uniform
+    double q = 0.0;
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k) {
+      const double u = W.ct[j][k] - cv[k];
+      q += u * u;
+    }
+    bool near;
+    double key = 0.0;
+    if (LINK == kWard) {
+      // Ward's division only where the cross-multiplied test leaves a chance
+      near = q * (2.0 * W.nt[j] * nc) <= W.beta[j] * (1.0 + 0x1p-46) * (W.nt[j] + nc);
+    } else {
+      key = q + (W.vt[j] + vc);
+      near = key <= W.beta[j];
+    }
+    near = near && i != W.pos[j];
+    if (__ballot(near)) {
+      if (near) {
+        if (LINK == kWard) key = ((2.0 * W.nt[j] * nc) / (W.nt[j] + nc)) * q;
+        const unsigned long long ck = make_key(mt.z, mt.x);
+        if (key <= W.beta[j] && better(key, ck, W.bv[j], W.bk[j])) {
+          W.bv[j] = key;
+          W.bk[j] = ck;
+        }
+      }
+      W.beta[j] = fmin(W.beta[j], wave_min_f64(W.bv[j]));
+    }
+    W.evals += kTreeFan;
+  }
+}
+
+// which of the children [c0, c0 + 64) of level `lev` each terminal of `want`
+// has to enter; returns the union
+template <int LINK, int MAXD>
+__device__ __forceinline__ unsigned long long tree_test(const State &S, TreeTerms<MAXD> &W, int lev, int c0,
+                                                        unsigned want, unsigned long long *enter) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int cnt = S.tree_cnt[lev];
+  const bool in = c0 + lane < cnt;
+  const size_t c = (size_t)S.tree_off[lev] + (in ? c0 + lane : cnt - 1);
+  const size_t tn = tree_stride(S);
+  double lo[MAXD], hi[MAXD];
+#pragma unroll
+  for (int k = 0; k < MAXD; ++k) {
+    lo[k] = k < S.d ? S.tree_lo[k * tn + c] : 0.0;
+    hi[k] = k < S.d ? S.tree_hi[k * tn + c] : 0.0;
+  }
+  const double nm = LINK == kWard ? (double)S.tree_nmin[c] : 0.0, vm = LINK == kAvgSq ? S.tree_vmin[c] : 0.0;
+  unsigned long long any = 0ull;
+#pragma unroll
+  for (int j = 0; j < kTreeTerms; ++j) {
+    enter[j] = 0ull;
+    if (!((want >> j) & 1u)) continue;  // uniform
+    double q = 0.0;
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k) {
+      // (gaps rounded like the key's differences; coordinates past d add zero)
+      const double g = fmax(fmax(lo[k] - W.ct[j][k], W.ct[j][k] - hi[k]), 0.0);
       q += g * g;
     }
-  if (LINK == kWard) {
-    const double nm = (double)S.tree_nmin[node];
-    return ((2.0 * nt * nm) / (nt + nm)) * q;
+    bool near;
+    if (LINK == kWard) near = q * (2.0 * W.nt[j] * nm) <= W.beta[j] * (1.0 + 0x1p-46) * (W.nt[j] + nm);
+    else near = q + (W.vt[j] + vm) <= W.beta[j];
+    enter[j] = __ballot(in && near);
+    any |= enter[j];
+    W.boxes += kTreeFan;
   }
-  return q + (vt + S.tree_vmin[node]);
+  return any;
 }
 
-template <int LINK, int MAXD>
-__global__ __launch_bounds__(kBlock) void k_nn_tree(State S) {
-  const int nterm = S.cnt->n_term, nact = S.cnt->n_act, d = S.d;
-  const int ti = blockIdx.x * blockDim.x + threadIdx.x;
-  long long evals = 0, boxes = 0;
-  if (ti < nterm) {
-    const int t = S.term[ti];
-    double ct[MAXD];
+template <int LINK, int MAXD, int LEV>
+__device__ __forceinline__ void tree_visit(const State &S, TreeTerms<MAXD> &W, int c0, unsigned long long any,
+                                           const unsigned long long *enter, int nact) {
+  while (any) {
+    const int b = __ffsll((unsigned long long)any) - 1;
+    any &= any - 1;
+    unsigned want = 0;
 #pragma unroll
-    for (int k = 0; k < MAXD; ++k) ct[k] = k < d ? S.wcen[(size_t)t * d + k] : 0.0;
-    const double nt = (double)S.csize[t];
-    const double vt = LINK == kAvgSq ? S.cmv[t] : 0.0;
-    const double bound = beta_key<LINK>(S.predd[t]);
-    double bestv = INFINITY;
-    unsigned long long bestk = kNoKey;
-    const int own = S.term_pos[ti] / kTreeFan;  // the terminal's own leaf
-    const int top = S.tree_top;
-    // Bottom up: the own leaf, then the subtrees of its siblings, then those
-    // of its parent's siblings, ... (nearest in Morton order first, so the
-    // bound tightens early). (al, anc): the ancestor whose subtree is done;
-    // sib: the sibling subtree being walked (-1: none yet at this level);
-    // (level, idx): the node to test next, item >= 0: walking leaf idx.
-    int al = 0, anc = own, sib = -1;
-    int level = 0, idx = own, item = 0;
-    bool done = false;
-    while (!done) {
-      if (item >= 0) {
-        const int i = idx * kTreeFan + item;
-        const int4 mt = S.item_meta[i];
-        double cv[MAXD];
-#pragma unroll
-        for (int k = 0; k < MAXD; ++k) cv[k] = k < d ? S.item_cen[(size_t)i * d + k] : 0.0;
-        const double v = cen_key<LINK, MAXD>(ct, nt, vt, cv, (double)mt.y, LINK == kAvgSq ? S.item_v[i] : 0.0, d);
-        ++evals;
-        const unsigned long long key = make_key(mt.z, mt.x);
-        if (mt.x != t && v <= bound && better(v, key, bestv, bestk)) {
-          bestv = v;
-          bestk = key;
-        }
-        if (++item < kTreeFan && i + 1 < nact) continue;
-        item = -1;
-      } else {
-        ++boxes;
-        const double lb = tree_lb<LINK, MAXD>(S, S.tree_off[level] + idx, ct, nt, vt, d);
-        if (!(lb > fmin(bound, bestv))) {
-          if (level > 0) {
-            --level;
-            idx *= kTreeFan;  // first child
-          } else {
-            item = 0;
-          }
-          continue;
-        }
-      }
-      // the node (level, idx) is finished: next node of the walk
-      for (;;) {
-        if (level == al) {
-          // a subtree at level al is finished: the next sibling of anc
-          const int p0 = (anc / kTreeFan) * kTreeFan, p1 = min(p0 + kTreeFan, S.tree_cnt[al]);
-          int nx = sib < 0 ? p0 : sib + 1;
-          if (nx == anc) ++nx;
-          if (nx < p1) {
-            sib = nx;
-            idx = nx;
-            break;
-          }
-          // every sibling done: the parent's subtree is done
-          if (al == top) {
-            done = true;
-            break;
-          }
-          anc /= kTreeFan;
-          ++al;
-          sib = -1;
-          level = al;
-          if (al == top) {  // the root has no siblings
-            done = true;
-            break;
-          }
-          continue;
-        }
-        if ((idx & (kTreeFan - 1)) != kTreeFan - 1 && idx + 1 < S.tree_cnt[level]) {
-          ++idx;
-          break;
-        }
-        idx /= kTreeFan;
-        ++level;
-      }
-    }
-    if (bestk == kNoKey) {
-      // the predecessor bound held nothing (cannot happen for an exact bound):
-      // the full scan takes the terminal without a bound
-      const int o = atomicAdd(&S.cnt->n_ovf, 1);
-      S.ovf[o] = ti;
+    for (int j = 0; j < kTreeTerms; ++j) want |= (unsigned)((enter[j] >> b) & 1ull) << j;
+    if constexpr (LEV == 0) {
+      const int leaf = c0 + b;
+      if (leaf < W.l0 || leaf > W.l1) tree_leaf<LINK, MAXD>(S, W, leaf, want, nact);
     } else {
-      S.t_best[ti] = bestv;
-      S.t_key[ti] = bestk;
+      unsigned long long sub[kTreeTerms];
+      const int n0 = (c0 + b) * kTreeFan;
+      const unsigned long long a = tree_test<LINK, MAXD>(S, W, LEV - 1, n0, want, sub);
+      tree_visit<LINK, MAXD, LEV - 1>(S, W, n0, a, sub, nact);
     }
   }
-  count_add(&S.cnt->cluster_evals, evals);
-  count_add(&S.cnt->visits[0], evals + boxes);
+}
+
+// TOP: the level whose (at most 64) nodes the walk starts with
+template <int LINK, int MAXD, int TOP>
+__global__ __launch_bounds__(kBlock) void k_nn_tree(State S) {
+  const int nterm = S.cnt->n_term, nact = S.cnt->n_act;
+  const int lane = threadIdx.x & (kWave - 1);
+  // each XCD (blocks are dealt out to the 8 in turn) takes a contiguous range
+  // of the terminals, its wavefronts in turn: their leaves stay in its own L2
+  const int groups = (nterm + kTreeTerms - 1) / kTreeTerms;
+  const int per = (groups + 7) / 8, xcd = blockIdx.x & 7;
+  const int step = (int)(gridDim.x >> 3) * (kBlock / kWave);
+  const int g1 = min(groups, (xcd + 1) * per);
+  int g = __builtin_amdgcn_readfirstlane(xcd * per + (int)(blockIdx.x >> 3) * (kBlock / kWave) +
+                                         (int)threadIdx.x / kWave);
+  TreeTerms<MAXD> W;
+  W.evals = W.boxes = 0;
+  for (; g < g1; g += step) {
+    const long long t0 = (long long)g * kTreeTerms;
+    unsigned all = 0;
+#pragma unroll
+    for (int j = 0; j < kTreeTerms; ++j) {
+      const int ti = (int)min(t0 + j, (long long)nterm - 1);
+      if (t0 + j < nterm) all |= 1u << j;
+      const int t = S.term[ti];
+#pragma unroll
+      for (int k = 0; k < MAXD; ++k) W.ct[j][k] = k < S.d ? S.wcen[(size_t)t * S.d + k] : 0.0;
+      W.nt[j] = (double)S.csize[t];
+      W.vt[j] = LINK == kAvgSq ? S.cmv[t] : 0.0;
+      W.beta[j] = beta_key<LINK>(S.predd[t]);
+      W.pos[j] = S.term_pos[ti];
+      W.bv[j] = INFINITY;
+      W.bk[j] = kNoKey;
+    }
+    W.l0 = W.pos[0] / kTreeFan;
+    W.l1 = W.pos[kTreeTerms - 1] / kTreeFan;
+    if (W.l1 > W.l0 + 3) W.l1 = W.l0;  // terminals far apart in the list
+    for (int l = W.l0; l <= W.l1; ++l) tree_leaf<LINK, MAXD>(S, W, l, all, nact);
+    unsigned long long enter[kTreeTerms];
+    const unsigned long long any = tree_test<LINK, MAXD>(S, W, TOP, 0, all, enter);
+    tree_visit<LINK, MAXD, TOP>(S, W, 0, any, enter, nact);
+#pragma unroll
+    for (int j = 0; j < kTreeTerms; ++j) {
+      if (!((all >> j) & 1u)) continue;
+      // the lane with the smallest value; equal values: the lowest key
+      const double v = wave_min_f64(W.bv[j]);
+      const unsigned long long at = __ballot(W.bv[j] == v);
+      unsigned long long k = (unsigned long long)__shfl((long long)W.bk[j], __ffsll(at) - 1, kWave);
+      if (at & (at - 1)) k = wave_min(W.bv[j] == v ? W.bk[j] : kNoKey);  // uniform
+      if (lane == 0) {
+        const int ti = (int)(t0 + j);
+        if (k == kNoKey) {
+          // the predecessor bound held nothing (cannot happen for an exact bound):
+          // the full scan takes the terminal without a bound
+          const int o = atomicAdd(&S.cnt->n_ovf, 1);
+          S.ovf[o] = ti;
+        } else {
+          S.t_best[ti] = v;
+          S.t_key[ti] = k;
+        }
+      }
+    }
+  }
+  // one addition per block: the counters are single addresses
+  __shared__ long long work[2][kBlock / kWave];
+  if (lane == 0) {
+    work[0][threadIdx.x / kWave] = W.evals;
+    work[1][threadIdx.x / kWave] = W.evals + W.boxes;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    long long v = 0;
+    for (int w = 0; w < kBlock / kWave; ++w) v += work[threadIdx.x][w];
+    if (v)
+      atomicAdd((unsigned long long *)(threadIdx.x == 0 ? &S.cnt->cluster_evals : &S.cnt->visits[0]),
+                (unsigned long long)v);
+  }
 }
 
 // ---------------------------------------------------------- pair tiles ----
@@ -4116,8 +4228,15 @@ void launch_search(State &S, int nact, hipStream_t s, int *t_ovf) {
   }
 }
 
-// box tree: items in active-list order, the node boxes level by level, the
+// box tree: items and leaf boxes, the other node boxes level by level, the
 // search, then the full scan for any terminal it handed back
+template <int LINK, int MAXD>
+void launch_tree_walk(State &S, int nact, hipStream_t s) {
+  const int grid = (nblk(((long long)nact + kTreeTerms - 1) / kTreeTerms * kWave, 4096) + 7) / 8 * 8;
+  if (S.tree_top <= 1) k_nn_tree<LINK, MAXD, 1><<<grid, kBlock, 0, s>>>(S);
+  else if (S.tree_top == 2) k_nn_tree<LINK, MAXD, 2><<<grid, kBlock, 0, s>>>(S);
+  else k_nn_tree<LINK, MAXD, 3><<<grid, kBlock, 0, s>>>(S);
+}
 template <int LINK>
 void launch_tree_search(State &S, int nact, hipStream_t s) {
   int cnt = (nact + kTreeFan - 1) / kTreeFan, off = 0, lev = 0;
@@ -4125,16 +4244,19 @@ void launch_tree_search(State &S, int nact, hipStream_t s) {
     S.tree_cnt[lev] = cnt;
     S.tree_off[lev] = off;
     off += cnt;
-    if (cnt == 1) break;
+    if (cnt <= kTreeFan && lev >= 1) break;  // (the walk starts at level 1 at least)
     cnt = (cnt + kTreeFan - 1) / kTreeFan;
     ++lev;
   }
   S.tree_top = lev;
-  k_tree_items<<<nblk(nact, 1 << 20), kBlock, 0, s>>>(S);
-  for (int l = 0; l <= S.tree_top; ++l) k_tree_level<<<nblk(S.tree_cnt[l], 1 << 20), kBlock, 0, s>>>(S, l);
+  k_tree_items<<<nblk((long long)S.tree_cnt[0] * kWave, 1 << 16), kBlock, 0, s>>>(S);
+  for (int l = 1; l <= S.tree_top; ++l)
+    k_tree_level<<<nblk((long long)S.tree_cnt[l] * kWave, 1 << 16), kBlock, 0, s>>>(S, l);
   tmark(S, 0, false, s);
-  if (S.d <= 4) k_nn_tree<LINK, 4><<<nblk(nact, 1 << 20), kBlock, 0, s>>>(S);
-  else k_nn_tree<LINK, 8><<<nblk(nact, 1 << 20), kBlock, 0, s>>>(S);
+  if (S.d <= 2) launch_tree_walk<LINK, 2>(S, nact, s);
+  else if (S.d <= 3) launch_tree_walk<LINK, 3>(S, nact, s);
+  else if (S.d <= 5) launch_tree_walk<LINK, 5>(S, nact, s);
+  else launch_tree_walk<LINK, 8>(S, nact, s);
   tmark(S, 0, true, s);
   tmark(S, 1, false, s);
   const size_t sm = (size_t)S.d * (sizeof(double) + 2 * sizeof(float));
@@ -4323,11 +4445,21 @@ void launch_check_finite(const float *x, long long count, Counters *cnt, hipStre
 void launch_init(State &S, const float *x, hipStream_t s) {
   const int n = S.n;
   // the box tree orders points over all (up to 8) axes, the grid over two
-  const int axes = S.tree ? std::min(S.d, kMortonAxes) : (S.d >= 2 ? 2 : 1);
+  const int axes = S.tree ? std::min(S.d, kCurveAxes) : (S.d >= 2 ? 2 : 1);
   const int key_bits = axes <= 2 ? 16 * axes : axes * (64 / axes);
   k_reset_round<<<1, 1, 0, s>>>(S.cnt);
   k_point_bbox<<<nblk(n, 1024), kBlock, 0, s>>>(x, n, S.d, axes, S.cnt);
-  k_morton<<<nblk(n, 1 << 22), kBlock, 0, s>>>(x, n, S.d, axes, S.cnt, S.sk0, S.sv0);
+  const int cb = nblk(n, 1 << 24);
+  switch (axes) {
+  case 1: k_curve<1><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  case 2: k_curve<2><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  case 3: k_curve<3><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  case 4: k_curve<4><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  case 5: k_curve<5><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  case 6: k_curve<6><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  case 7: k_curve<7><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  default: k_curve<8><<<cb, kBlock, 0, s>>>(x, n, S.d, S.cnt, S.sk0, S.sv0); break;
+  }
   radix_sort_pairs(S.sk0, S.sk1, S.sv0, S.sv1, n, key_bits, S.hist, S.sws, s);
   k_init_slots<<<nblk(n, 1 << 22), kBlock, 0, s>>>(S, x, S.sv0);
   k_set_nact<<<1, 1, 0, s>>>(S.cnt, n);
@@ -4353,7 +4485,7 @@ void launch_round(State &S, int round, int nact, hipStream_t s, bool &need_pairs
   // are the same), which beats a thread walking grid rings in latency; the
   // grid is then not built.
   const bool full = S.full_scan_max > 0 && nact <= S.full_scan_max && round > 0 && S.d <= kGridMaxDim &&
-                    S.prune && !S.gram && !S.tree;
+                    S.prune && !S.gram;
   if (S.d <= kGridMaxDim && S.prune && !S.gram && !S.tree && !full) {
     k_grid_params<<<1, 1, 0, s>>>(S, S.cell_cap);
     k_zero_cells<<<nblk(nact + 1, 2048), kBlock, 0, s>>>(S);
@@ -4372,7 +4504,7 @@ void launch_round(State &S, int round, int nact, hipStream_t s, bool &need_pairs
     need_pairs = !centroid_link(S.linkage);
     return;
   }
-  if (S.tree) {
+  if (S.tree && !full) {
     k_term_pos<<<gb, kBlock, 0, s>>>(S);
     if (S.linkage == kWard) launch_tree_search<kWard>(S, nact, s);
     else launch_tree_search<kAvgSq>(S, nact, s);

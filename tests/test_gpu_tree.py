@@ -1,0 +1,59 @@
+"""The box-tree search of Ward and avg-2 at the sizes where it can go wrong:
+leaves of 64 clusters and one more or less, one and two levels above them,
+groups of four terminals with a remainder, every width of the coordinate loops,
+ties, outliers and flat inputs. Ward heights are the oracle's bit for bit, avg-2
+heights within 1e-10 (spreads by an equivalent merge rule)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests import _trees
+
+pytestmark = pytest.mark.gpu
+
+RTOL = {"ward": 0.0, "avgsq": 1e-10}
+
+
+@pytest.fixture
+def pc(monkeypatch):
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2106_04727_amd as pc
+
+    pc.load_library()
+    monkeypatch.setenv("PC_TREE_MAX_DIM", "8")
+    monkeypatch.setenv("PC_FULL_SCAN_MAX", "0")  # the tree in every round
+    return pc
+
+
+@pytest.mark.parametrize("link", ["ward", "avgsq"])
+@pytest.mark.parametrize("n,d", [(2, 1), (5, 2), (63, 2), (64, 3), (65, 5), (130, 8), (700, 7), (4096, 2), (4097, 1),
+                                 (4100, 6), (5003, 4)])
+def test_tree_rounds(pc, link, n, d):
+    x = synth.blobs(n, d, max(1, n // 80), 0.03, 700 + n + d)
+    Zo, cert = oracle.nnchain(x, link, threads=8)
+    Z, st = pc.hac(x, link, return_stats=True)
+    assert st["kernels"]["ring_search"]["visits"] > 0
+    _trees.assert_valid(Z, n)
+    if cert["min_gap"] >= 1e-10 or n < 3:
+        assert _trees.same_tree(Z, Zo, n, rtol=RTOL[link])
+    else:
+        _trees.assert_valid_hac(x, Z, link, rtol=1e-9)
+
+
+@pytest.mark.parametrize("link", ["ward", "avgsq"])
+def test_tree_ties_outliers_and_flat_inputs(pc, link):
+    g = np.stack(np.meshgrid(np.arange(13.0), np.arange(9.0)), -1).reshape(-1, 2).astype(np.float32)
+    _trees.assert_valid_hac(g, pc.hac(g, link), link, rtol=1e-9)  # a lattice: equal keys everywhere
+    x = synth.uniform(150, 3, 8)
+    x = np.concatenate([x, x])  # every point twice
+    Z = pc.hac(x, link)
+    _trees.assert_valid_hac(x, Z, link, rtol=1e-9)
+    assert np.all(Z[:150, 2] == 0.0)
+    x = synth.uniform(900, 3, 9)
+    x[::90] *= 1e4  # far outliers stretch the curve's cells and the boxes
+    x[:, 1] = 0.5   # one axis without extent
+    Zo, _ = oracle.nnchain(x, link, threads=8)
+    assert _trees.same_tree(pc.hac(x, link), Zo, 900, rtol=RTOL[link])
