@@ -1757,8 +1757,8 @@ __global__ __launch_bounds__(kBlock) void k_nn_full(State S, const int *list, co
 // implicit 64-ary tree is built over it every round: leaves of 64 consecutive
 // clusters, each level above grouping 64 nodes, every node with the FP64 box of
 // its centroids, its smallest size and smallest spread term (the range query of
-// Alg. 3 over a bounding-box tree instead of a k-d tree). One wavefront takes
-// kTreeTerms neighbouring terminals: it evaluates their own leaves first (near
+// Alg. 3 over a bounding-box tree instead of a k-d tree). One wavefront takes a
+// few neighbouring terminals: it evaluates their own leaves first (near
 // neighbours and tight bounds), then walks the tree from the top, its 64 lanes
 // testing the 64 children of a node, or evaluating the 64 clusters of a leaf,
 // for each terminal that has not ruled the node out (Sec. 4.1, 4.2: the Ward
@@ -1768,7 +1768,6 @@ __global__ __launch_bounds__(kBlock) void k_nn_full(State S, const int *list, co
 // larger than the key's operands, so it never exceeds a key (rounding is
 // monotone); pruning is strict, so equal keys reach the tie-break.
 constexpr int kTreeFan = 64;
-constexpr int kTreeTerms = 4;
 
 __device__ __forceinline__ size_t tree_stride(const State &S) { return (size_t)S.n / 15 + 16; }  // nodes per coordinate
 
@@ -1830,20 +1829,21 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(State S, int lev) {
   }
 }
 
-// The wavefront's terminals (uniform but for bv, bk: each lane's own best).
-template <int MAXD>
+// The wavefront's T terminals and their best candidates, the same in all
+// lanes, and the box, smallest size and spread term and largest bound of all.
+template <int MAXD, int T>
 struct TreeTerms {
-  double ct[kTreeTerms][MAXD], nt[kTreeTerms], vt[kTreeTerms], beta[kTreeTerms];
-  int pos[kTreeTerms];
-  double bv[kTreeTerms];
-  unsigned long long bk[kTreeTerms];
+  double ct[T][MAXD], nt[T], vt[T], beta[T];
+  int pos[T];
+  unsigned long long bk[T];
+  double lo[MAXD], hi[MAXD], ntmin, vtmin, bmax;
   int l0, l1;  // leaves evaluated at the start
-  long long evals, boxes;
+  int leaves, nodes;
 };
 
 // the 64 clusters of a leaf, for the terminals of `want`
-template <int LINK, int MAXD>
-__device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD> &W, int leaf, unsigned want, int nact) {
+template <int LINK, int MAXD, int T>
+__device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD, T> &W, int leaf, unsigned want, int nact) {
   const int lane = threadIdx.x & (kWave - 1);
   const int i = min(leaf * kTreeFan + lane, nact - 1);  // (past the end: the last item again)
   double cv[MAXD];
@@ -1852,7 +1852,7 @@ __device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD> &W, in
   const int4 mt = S.item_meta[i];
   const double nc = (double)mt.y, vc = LINK == kAvgSq ? S.item_v[i] : 0.0;
 #pragma unroll
-  for (int j = 0; j < kTreeTerms; ++j) {
+  for (int j = 0; j < T; ++j) {
     if (!((want >> j) & 1u)) continue;  // uniform
     double q = 0.0;
 #pragma unroll
@@ -1870,26 +1870,57 @@ __device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD> &W, in
       near = key <= W.beta[j];
     }
     near = near && i != W.pos[j];
-    if (__ballot(near)) {
-      if (near) {
-        if (LINK == kWard) key = ((2.0 * W.nt[j] * nc) / (W.nt[j] + nc)) * q;
-        const unsigned long long ck = make_key(mt.z, mt.x);
-        if (key <= W.beta[j] && better(key, ck, W.bv[j], W.bk[j])) {
-          W.bv[j] = key;
-          W.bk[j] = ck;
-        }
-      }
-      W.beta[j] = fmin(W.beta[j], wave_min_f64(W.bv[j]));
+    ++W.leaves;
+    if (!__ballot(near)) continue;
+    // the nearest of these lanes; equal values: the lowest key
+    if (LINK == kWard) key = ((2.0 * W.nt[j] * nc) / (W.nt[j] + nc)) * q;
+    if (!near) key = INFINITY;
+    const double m = wave_min_f64(key);
+    if (!(m <= W.beta[j])) continue;  // uniform, as is all that follows
+    const unsigned long long at = __ballot(key == m);
+    const unsigned long long ck = make_key(mt.z, mt.x);
+    const int first = __ffsll(at) - 1;
+    unsigned long long k = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane(mt.z, first) << 32) |
+                           (unsigned)__builtin_amdgcn_readlane(mt.x, first);
+    if (at & (at - 1)) k = wave_min(key == m ? ck : kNoKey);
+    // (a bound no candidate has reached yet carries the key kNoKey)
+    if (m < W.beta[j] || k < W.bk[j]) {
+      W.beta[j] = m;
+      W.bk[j] = k;
     }
-    W.evals += kTreeFan;
   }
 }
 
-// which of the children [c0, c0 + 64) of level `lev` each terminal of `want`
-// has to enter; returns the union
+// largest bound of the terminals, after some have shrunk
+template <int MAXD, int T>
+__device__ __forceinline__ void tree_bmax(TreeTerms<MAXD, T> &W) {
+  W.bmax = W.beta[0];
+#pragma unroll
+  for (int j = 1; j < T; ++j) W.bmax = fmax(W.bmax, W.beta[j]);
+}
+
+// a node's lower bound against one centroid (box lo = hi) or the box of all
 template <int LINK, int MAXD>
-__device__ __forceinline__ unsigned long long tree_test(const State &S, TreeTerms<MAXD> &W, int lev, int c0,
-                                                        unsigned want, unsigned long long *enter) {
+__device__ __forceinline__ bool tree_near(const double *lo, const double *hi, double nm, double vm, const double *tlo,
+                                          const double *thi, double nt, double vt, double beta) {
+  double q = 0.0;
+#pragma unroll
+  for (int k = 0; k < MAXD; ++k) {
+    // (gaps rounded like the key's differences; coordinates past d add zero)
+    const double g = fmax(fmax(lo[k] - thi[k], tlo[k] - hi[k]), 0.0);
+    q += g * g;
+  }
+  if (LINK == kWard) return q * (2.0 * nt * nm) <= beta * (1.0 + 0x1p-46) * (nt + nm);
+  return q + (vt + vm) <= beta;
+}
+
+// The children [c0, c0 + 64) of level `lev` that the terminals have to enter.
+// Above the leaves one test against the box of all terminals decides (they are
+// neighbours, and nodes there are large); leaves are tested for each terminal
+// (enter[j]) that the box test leaves.
+template <int LINK, int MAXD, int T, bool LEAF>
+__device__ __forceinline__ unsigned long long tree_test(const State &S, TreeTerms<MAXD, T> &W, int lev, int c0,
+                                                        unsigned long long *enter) {
   const int lane = threadIdx.x & (kWave - 1);
   const int cnt = S.tree_cnt[lev];
   const bool in = c0 + lane < cnt;
@@ -1902,115 +1933,113 @@ __device__ __forceinline__ unsigned long long tree_test(const State &S, TreeTerm
     hi[k] = k < S.d ? S.tree_hi[k * tn + c] : 0.0;
   }
   const double nm = LINK == kWard ? (double)S.tree_nmin[c] : 0.0, vm = LINK == kAvgSq ? S.tree_vmin[c] : 0.0;
-  unsigned long long any = 0ull;
-#pragma unroll
-  for (int j = 0; j < kTreeTerms; ++j) {
-    enter[j] = 0ull;
-    if (!((want >> j) & 1u)) continue;  // uniform
-    double q = 0.0;
-#pragma unroll
-    for (int k = 0; k < MAXD; ++k) {
-      // (gaps rounded like the key's differences; coordinates past d add zero)
-      const double g = fmax(fmax(lo[k] - W.ct[j][k], W.ct[j][k] - hi[k]), 0.0);
-      q += g * g;
+  ++W.nodes;
+  tree_bmax(W);
+  unsigned long long any =
+      __ballot(in && tree_near<LINK, MAXD>(lo, hi, nm, vm, W.lo, W.hi, W.ntmin, W.vtmin, W.bmax));
+  if constexpr (LEAF) {
+    // leaves of the start are done
+    const int a = W.l0 - c0, e = W.l1 - c0;  // [a, e] within [0, 64)
+    if (e >= 0 && a < kWave) {
+      const int s0 = max(a, 0), s1 = min(e, kWave - 1);
+      any &= ~(((~0ull) >> (63 - (s1 - s0))) << s0);
     }
-    bool near;
-    if (LINK == kWard) near = q * (2.0 * W.nt[j] * nm) <= W.beta[j] * (1.0 + 0x1p-46) * (W.nt[j] + nm);
-    else near = q + (W.vt[j] + vm) <= W.beta[j];
-    enter[j] = __ballot(in && near);
-    any |= enter[j];
-    W.boxes += kTreeFan;
+    if (!any) return 0ull;
+    unsigned long long u = 0ull;
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      enter[j] = any & __ballot(tree_near<LINK, MAXD>(lo, hi, nm, vm, W.ct[j], W.ct[j], W.nt[j], W.vt[j], W.beta[j]));
+      u |= enter[j];
+    }
+    W.nodes += T;
+    return u;
   }
   return any;
 }
 
-template <int LINK, int MAXD, int LEV>
-__device__ __forceinline__ void tree_visit(const State &S, TreeTerms<MAXD> &W, int c0, unsigned long long any,
-                                           const unsigned long long *enter, int nact) {
+template <int LINK, int MAXD, int T, int LEV>
+__device__ __forceinline__ void tree_visit(const State &S, TreeTerms<MAXD, T> &W, int c0, int nact) {
+  unsigned long long enter[T];
+  unsigned long long any = tree_test<LINK, MAXD, T, LEV == 0>(S, W, LEV, c0, enter);
   while (any) {
     const int b = __ffsll((unsigned long long)any) - 1;
     any &= any - 1;
-    unsigned want = 0;
-#pragma unroll
-    for (int j = 0; j < kTreeTerms; ++j) want |= (unsigned)((enter[j] >> b) & 1ull) << j;
     if constexpr (LEV == 0) {
-      const int leaf = c0 + b;
-      if (leaf < W.l0 || leaf > W.l1) tree_leaf<LINK, MAXD>(S, W, leaf, want, nact);
+      unsigned want = 0;
+#pragma unroll
+      for (int j = 0; j < T; ++j) want |= (unsigned)((enter[j] >> b) & 1ull) << j;
+      tree_leaf<LINK, MAXD, T>(S, W, c0 + b, want, nact);
     } else {
-      unsigned long long sub[kTreeTerms];
-      const int n0 = (c0 + b) * kTreeFan;
-      const unsigned long long a = tree_test<LINK, MAXD>(S, W, LEV - 1, n0, want, sub);
-      tree_visit<LINK, MAXD, LEV - 1>(S, W, n0, a, sub, nact);
+      tree_visit<LINK, MAXD, T, LEV - 1>(S, W, (c0 + b) * kTreeFan, nact);
     }
   }
 }
 
 // TOP: the level whose (at most 64) nodes the walk starts with
-template <int LINK, int MAXD, int TOP>
-__global__ __launch_bounds__(kBlock) void k_nn_tree(State S) {
+template <int LINK, int MAXD, int T, int TOP>
+__global__ __launch_bounds__(kBlock, MAXD <= 3 ? 4 : 3) void k_nn_tree(State S) {
   const int nterm = S.cnt->n_term, nact = S.cnt->n_act;
   const int lane = threadIdx.x & (kWave - 1);
   // each XCD (blocks are dealt out to the 8 in turn) takes a contiguous range
   // of the terminals, its wavefronts in turn: their leaves stay in its own L2
-  const int groups = (nterm + kTreeTerms - 1) / kTreeTerms;
+  const int groups = (nterm + T - 1) / T;
   const int per = (groups + 7) / 8, xcd = blockIdx.x & 7;
   const int step = (int)(gridDim.x >> 3) * (kBlock / kWave);
   const int g1 = min(groups, (xcd + 1) * per);
   int g = __builtin_amdgcn_readfirstlane(xcd * per + (int)(blockIdx.x >> 3) * (kBlock / kWave) +
                                          (int)threadIdx.x / kWave);
-  TreeTerms<MAXD> W;
-  W.evals = W.boxes = 0;
+  long long evals = 0, boxes = 0;
   for (; g < g1; g += step) {
-    const long long t0 = (long long)g * kTreeTerms;
-    unsigned all = 0;
+    TreeTerms<MAXD, T> W;
+    W.leaves = W.nodes = 0;
+    const long long t0 = (long long)g * T;
+    // (a group's missing terminals repeat its last one)
 #pragma unroll
-    for (int j = 0; j < kTreeTerms; ++j) {
+    for (int j = 0; j < T; ++j) {
       const int ti = (int)min(t0 + j, (long long)nterm - 1);
-      if (t0 + j < nterm) all |= 1u << j;
       const int t = S.term[ti];
 #pragma unroll
-      for (int k = 0; k < MAXD; ++k) W.ct[j][k] = k < S.d ? S.wcen[(size_t)t * S.d + k] : 0.0;
+      for (int k = 0; k < MAXD; ++k) {
+        const double c = k < S.d ? S.wcen[(size_t)t * S.d + k] : 0.0;
+        W.ct[j][k] = c;
+        W.lo[k] = j == 0 ? c : fmin(W.lo[k], c);
+        W.hi[k] = j == 0 ? c : fmax(W.hi[k], c);
+      }
       W.nt[j] = (double)S.csize[t];
       W.vt[j] = LINK == kAvgSq ? S.cmv[t] : 0.0;
+      W.ntmin = j == 0 ? W.nt[j] : fmin(W.ntmin, W.nt[j]);
+      W.vtmin = j == 0 ? W.vt[j] : fmin(W.vtmin, W.vt[j]);
       W.beta[j] = beta_key<LINK>(S.predd[t]);
       W.pos[j] = S.term_pos[ti];
-      W.bv[j] = INFINITY;
       W.bk[j] = kNoKey;
     }
     W.l0 = W.pos[0] / kTreeFan;
-    W.l1 = W.pos[kTreeTerms - 1] / kTreeFan;
+    W.l1 = W.pos[T - 1] / kTreeFan;
     if (W.l1 > W.l0 + 3) W.l1 = W.l0;  // terminals far apart in the list
-    for (int l = W.l0; l <= W.l1; ++l) tree_leaf<LINK, MAXD>(S, W, l, all, nact);
-    unsigned long long enter[kTreeTerms];
-    const unsigned long long any = tree_test<LINK, MAXD>(S, W, TOP, 0, all, enter);
-    tree_visit<LINK, MAXD, TOP>(S, W, 0, any, enter, nact);
+    for (int l = W.l0; l <= W.l1; ++l) tree_leaf<LINK, MAXD, T>(S, W, l, (1u << T) - 1u, nact);
+    tree_visit<LINK, MAXD, T, TOP>(S, W, 0, nact);
 #pragma unroll
-    for (int j = 0; j < kTreeTerms; ++j) {
-      if (!((all >> j) & 1u)) continue;
-      // the lane with the smallest value; equal values: the lowest key
-      const double v = wave_min_f64(W.bv[j]);
-      const unsigned long long at = __ballot(W.bv[j] == v);
-      unsigned long long k = (unsigned long long)__shfl((long long)W.bk[j], __ffsll(at) - 1, kWave);
-      if (at & (at - 1)) k = wave_min(W.bv[j] == v ? W.bk[j] : kNoKey);  // uniform
-      if (lane == 0) {
-        const int ti = (int)(t0 + j);
-        if (k == kNoKey) {
-          // the predecessor bound held nothing (cannot happen for an exact bound):
-          // the full scan takes the terminal without a bound
-          const int o = atomicAdd(&S.cnt->n_ovf, 1);
-          S.ovf[o] = ti;
-        } else {
-          S.t_best[ti] = v;
-          S.t_key[ti] = k;
-        }
+    for (int j = 0; j < T; ++j) {
+      if (lane != j || t0 + j >= nterm) continue;
+      const int ti = (int)(t0 + j);
+      if (W.bk[j] == kNoKey) {
+        // the predecessor bound held nothing (cannot happen for an exact bound):
+        // the full scan takes the terminal without a bound
+        const int o = atomicAdd(&S.cnt->n_ovf, 1);
+        S.ovf[o] = ti;
+      } else {
+        S.t_best[ti] = W.beta[j];
+        S.t_key[ti] = W.bk[j];
       }
     }
+    evals += (long long)W.leaves * kTreeFan;
+    boxes += (long long)W.nodes * kTreeFan;
   }
   // one addition per block: the counters are single addresses
   __shared__ long long work[2][kBlock / kWave];
   if (lane == 0) {
-    work[0][threadIdx.x / kWave] = W.evals;
-    work[1][threadIdx.x / kWave] = W.evals + W.boxes;
+    work[0][threadIdx.x / kWave] = evals;
+    work[1][threadIdx.x / kWave] = evals + boxes;
   }
   __syncthreads();
   if (threadIdx.x < 2) {
@@ -4230,12 +4259,12 @@ void launch_search(State &S, int nact, hipStream_t s, int *t_ovf) {
 
 // box tree: items and leaf boxes, the other node boxes level by level, the
 // search, then the full scan for any terminal it handed back
-template <int LINK, int MAXD>
+template <int LINK, int MAXD, int T>
 void launch_tree_walk(State &S, int nact, hipStream_t s) {
-  const int grid = (nblk(((long long)nact + kTreeTerms - 1) / kTreeTerms * kWave, 4096) + 7) / 8 * 8;
-  if (S.tree_top <= 1) k_nn_tree<LINK, MAXD, 1><<<grid, kBlock, 0, s>>>(S);
-  else if (S.tree_top == 2) k_nn_tree<LINK, MAXD, 2><<<grid, kBlock, 0, s>>>(S);
-  else k_nn_tree<LINK, MAXD, 3><<<grid, kBlock, 0, s>>>(S);
+  const int grid = (nblk(((long long)nact + T - 1) / T * kWave, 4096) + 7) / 8 * 8;
+  if (S.tree_top <= 1) k_nn_tree<LINK, MAXD, T, 1><<<grid, kBlock, 0, s>>>(S);
+  else if (S.tree_top == 2) k_nn_tree<LINK, MAXD, T, 2><<<grid, kBlock, 0, s>>>(S);
+  else k_nn_tree<LINK, MAXD, T, 3><<<grid, kBlock, 0, s>>>(S);
 }
 template <int LINK>
 void launch_tree_search(State &S, int nact, hipStream_t s) {
@@ -4253,10 +4282,14 @@ void launch_tree_search(State &S, int nact, hipStream_t s) {
   for (int l = 1; l <= S.tree_top; ++l)
     k_tree_level<<<nblk((long long)S.tree_cnt[l] * kWave, 1 << 16), kBlock, 0, s>>>(S, l);
   tmark(S, 0, false, s);
-  if (S.d <= 2) launch_tree_walk<LINK, 2>(S, nact, s);
-  else if (S.d <= 3) launch_tree_walk<LINK, 3>(S, nact, s);
-  else if (S.d <= 5) launch_tree_walk<LINK, 5>(S, nact, s);
-  else launch_tree_walk<LINK, 8>(S, nact, s);
+  // terminals per wavefront: more share loads and box tests, fewer fit the
+  // registers (128, 168 from d = 4 on). 10M points d = 2, ms: Ward 4 38.2, 8
+  // 49.8 (72 spilled); avg-2 8 36.2
+  constexpr bool W = LINK == kWard;
+  if (S.d <= 2) launch_tree_walk<LINK, 2, W ? 4 : 8>(S, nact, s);
+  else if (S.d <= 3) launch_tree_walk<LINK, 3, W ? 4 : 6>(S, nact, s);
+  else if (S.d <= 5) launch_tree_walk<LINK, 5, 4>(S, nact, s);
+  else launch_tree_walk<LINK, 8, 4>(S, nact, s);
   tmark(S, 0, true, s);
   tmark(S, 1, false, s);
   const size_t sm = (size_t)S.d * (sizeof(double) + 2 * sizeof(float));
