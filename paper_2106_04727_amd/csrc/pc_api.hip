@@ -118,12 +118,12 @@ size_t layout(State &S, char *base, int64_t n64, int d, int linkage, bool host_p
   S.gmin = c.take<unsigned long long>(gram ? d : 1);
   S.gmax = c.take<unsigned long long>(gram ? d : 1);
   S.gscale = c.take<double>(1);
-  // box tree: Ward / avg-2 at d <= kTreeMaxDim (the call may still use another
-  // search). Up to d = 2 its arrays lie over the grid's, of which a call uses
-  // one or the other.
-  const bool tree = centroid_link(linkage) && d <= kTreeMaxDim;
+  // box tree: Ward / avg-2 at d <= kTreeMaxDim, complete / average at d <=
+  // kTreePairDim (the call may still use another search). Up to d = 3 its
+  // arrays lie over the grid's, of which a round uses one or the other.
+  const bool tree = d <= (pts ? kTreePairDim : kTreeMaxDim);
   const size_t tnodes = n / 15 + 16;  // (a 64-ary tree over n / 64 leaves needs fewer)
-  if (tree && d <= 2 && n >= 64) {
+  if (tree && d <= 3 && n >= 64) {
     S.term_pos = S.cell_of;
     S.tree_lo = (double *)S.cell_cnt;
     S.tree_hi = (double *)S.cell_start;
@@ -713,7 +713,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   // d = 4 on; 0, the default: none), PC_GRAM_MIN_DIM.
   int tree_max = kTreeMaxDim;
   if (const char *e = getenv("PC_TREE_MAX_DIM")) tree_max = std::min(kTreeMaxDim, atoi(e));
-  const bool tree_ok = prune && centroid_link(linkage) && d <= tree_max && n < (1LL << 30);
+  const bool tree_ok = prune && d <= std::min(tree_max, centroid_link(linkage) ? kTreeMaxDim : kTreePairDim) && n < (1LL << 30);
   int gram_min = centroid_link(linkage) && !tree_ok ? 6 : kGramMinDim;
   if (const char *e = getenv("PC_GRAM_MIN_DIM")) gram_min = std::max(kGramMinDim, atoi(e));
   const bool gram_ok = prune && d >= gram_min && d <= kGramMaxDim;
@@ -897,9 +897,14 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     }
     if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
     if (tree_ok) {
-      const bool use_tree = !gram_used || nact > tree_gram_switch;
+      bool use_tree = !gram_used || nact > tree_gram_switch;
+      // complete linkage in the plane, clusters of up to three points: a thread
+      // per terminal on the grid evaluates their tiny pairs faster (second round
+      // of 1M points 0.9-1.4 ms, tree 2.2; from the fifth on 1.4 / 1.1 on
+      // mixtures, 0.8 / 1.1 on uniform points; below 300K clusters the tree wins)
+      if (linkage == kComplete && d <= 2 && rounds > 0 && nact > 300000 && nact > n / 3) use_tree = false;
       S.tree = use_tree ? 1 : 0;
-      S.gram = use_tree ? 0 : 1;
+      S.gram = use_tree || !gram_used ? 0 : 1;
     }
     bool need_pairs = false;
     S.tb0 = 0;
@@ -1026,6 +1031,21 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     } else if (need_pairs) {
       HIPCHK(hipMemcpyAsync(&h, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
+      if (h.cand_overflow && S.tree) {
+        // the round again on the grid, whose rings can be walked twice
+        S.tree = 0;
+        if (S.timing) S.kt->drop();
+        const long long found = h.n_cand;
+        launch_round(S, (int)rounds, nact, s, need_pairs);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(&h, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        const long long want = std::min<long long>(found + found / 2 + 1024, kMaxRecord);
+        if (!h.cand_overflow && fits(ctx, ctx->cur->cand, (size_t)want * kCandBytes + 1024)) {
+          pc_status st = grow_cand(ctx, S, want);
+          if (st != PC_OK) return st;
+        }
+      }
       if (h.cand_overflow) {
         // this round: emit by re-walking the rings; later rounds: a larger record
         launch_emit_fallback(S, nact, s);

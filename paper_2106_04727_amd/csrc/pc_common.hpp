@@ -24,6 +24,7 @@ constexpr int kSupDirs = 64;       // d == 2, complete: support points in 64 fix
 constexpr int kGramMinDim = 4;     // Gram (MFMA) search from this d on
 constexpr int kGramMaxDim = 128;   // largest d of the Gram search (K = 128 in LDS)
 constexpr int kTreeMaxDim = 8;     // Ward / avg-2: box-tree search over centroids in curve order up to this d
+constexpr int kTreePairDim = 3;    // complete / average: the same up to this d
 constexpr int kCurveAxes = 8;      // at most this many axes in the initial Hilbert order
 // MFMA depth of the Gram tiles: the dimension plus two augmented
 // coordinates (the norm terms of the bound pass), in steps of 16

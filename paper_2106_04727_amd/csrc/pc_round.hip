@@ -1782,11 +1782,23 @@ __global__ __launch_bounds__(kBlock) void k_tree_items(State S) {
     const bool in = i < nact;
     const int s = S.act[in ? i : nact - 1];
     const int sz = S.csize[s];
-    const double v = S.linkage == kAvgSq ? S.cmv[s] : 0.0;
+    // the spread term of the key's lower bound (avg-2: of the key itself)
+    int vb = 0;
+    double v = 0.0;
+    if (S.linkage == kAvgSq) v = S.cmv[s];
+    if (S.linkage == kComplete) {
+      vb = spread_bits(spread_lo(S, s));
+      v = (double)__int_as_float(vb);
+    }
     if (in) {
-      S.item_meta[i] = make_int4(s, sz, S.cid[s], 0);
+      S.item_meta[i] = make_int4(s, sz, S.cid[s], vb);
       if (S.linkage == kAvgSq) S.item_v[i] = v;
     }
+    if (!centroid_link(S.linkage) && in)
+      for (int k = 0; k < d; ++k) {
+        S.item_lo[(size_t)k * S.n + i] = S.lo[(size_t)s * d + k];
+        S.item_hi[(size_t)k * S.n + i] = S.hi[(size_t)s * d + k];
+      }
     for (int k = 0; k < d; ++k) {
       const double c = S.wcen[(size_t)s * d + k];
       if (in) S.item_cen[(size_t)k * S.n + i] = c;
@@ -2048,6 +2060,304 @@ __global__ __launch_bounds__(kBlock, MAXD <= 3 ? 4 : 3) void k_nn_tree(State S) 
     if (v)
       atomicAdd((unsigned long long *)(threadIdx.x == 0 ? &S.cnt->cluster_evals : &S.cnt->visits[0]),
                 (unsigned long long)v);
+  }
+}
+
+// The same walk for complete and average linkage (d <= kTreePairDim): the
+// search bound of every terminal, its best candidate among the small pairs, and
+// the record of the large pairs whose lower bound the walk could not exclude
+// (evaluated later under the final bound). Of the 64 clusters of a leaf the
+// upper bounds lower the terminal's bound first; the few lanes left evaluate
+// pairs of up to kLanePairs point pairs each by itself and larger ones together,
+// a point pair per lane.
+// Terminals per wavefront: one. Two share loads but take 156 registers instead
+// of 84, and the walk waits for the points it gathers (1M planar points: 36.4
+// ms with one, 37.7 with two, 39.7 with four).
+// Bound by the latency of those gathers: about 18K cycles per terminal at 100K
+// clusters, against 38K cycles of a thread's ring walk.
+constexpr int kLanePairs = 8;
+constexpr int kPairTerms = 1;
+
+template <int MAXD, int T>
+struct TreePairs {
+  double ct[T][MAXD], bound[T], bestv[T], sp[T];
+  float lt[T][MAXD], ht[T][MAXD];
+  int slot[T], cid[T], size[T], beg[T], pos[T];
+  unsigned long long bk[T];
+  double lo[MAXD], hi[MAXD], spmin, bmax;
+  int l0, l1;
+  int nodes;
+  unsigned all;  // the terminals there are (the last group may lack some)
+  long long t0;
+};
+
+// the bound a candidate's (squared, for average) lower bound is held against
+template <int LINK>
+__device__ __forceinline__ double pair_limit(double bound) {
+  const double b = bound * kSlack;
+  return LINK == kAverage ? b * b * (1.0 + 1e-12) : b;
+}
+// lower bound of the key (squared for average) at squared centroid distance q
+// and spread terms vs
+template <int LINK>
+__device__ __forceinline__ double pair_floor(double q, double vs) {
+  return LINK == kComplete ? q * (1.0 - 1e-6) + vs : q;
+}
+
+template <int LINK, int MAXD, int T, bool CACHE>
+__device__ __forceinline__ void tree_leaf_pairs(const State &S, TreePairs<MAXD, T> &W, int leaf, unsigned want,
+                                                int nact, long long &evals, long long &ppairs, long long &visits,
+                                                long long &hits) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int d = S.d;
+  const bool in = leaf * kTreeFan + lane < nact;
+  const int i = min(leaf * kTreeFan + lane, nact - 1);
+  double cv[MAXD];
+  float lc[MAXD], hc[MAXD];
+#pragma unroll
+  for (int k = 0; k < MAXD; ++k) {
+    cv[k] = k < d ? S.item_cen[(size_t)k * S.n + i] : 0.0;
+    lc[k] = k < d ? S.item_lo[(size_t)k * S.n + i] : 0.f;
+    hc[k] = k < d ? S.item_hi[(size_t)k * S.n + i] : 0.f;
+  }
+  const int4 mt = S.item_meta[i];
+  const unsigned long long ck = make_key(mt.z, mt.x);
+#pragma unroll
+  for (int j = 0; j < T; ++j) {
+    if (!((want >> j) & 1u)) continue;  // uniform
+    ++visits;
+    double lb, ub;
+    pair_bounds<LINK, MAXD>(W.ct[j], W.lt[j], W.ht[j], cv, lc, hc, d, lb, ub,
+                            W.sp[j] + (double)__int_as_float(mt.w));
+    const bool cand = in && i != W.pos[j];
+    bool near = cand && lb <= fmin(W.bound[j], W.bestv[j]) * kSlack;
+    if (!__ballot(near)) continue;
+    // upper bounds first
+    const long long cost = (long long)W.size[j] * (long long)mt.y;
+    if (LINK == kComplete && near && cost > kInlinePairs) comp_ub_refine(S, W.slot[j], mt.x, W.ct[j], cv, d, ub);
+    W.bound[j] = fmin(W.bound[j], wave_min_f64(near ? ub : INFINITY));
+    near = near && lb <= fmin(W.bound[j], W.bestv[j]) * kSlack;
+    double v = INFINITY;
+    if (near && cost > kInlinePairs) {
+      bool known = false;
+      if (CACHE) {
+        double x;
+        if (cache_find(S, pair_key(S.node[W.slot[j]], S.node[mt.x]), x) == 1) {
+          known = true;
+          v = x;
+          ++hits;
+        }
+      }
+      if (!known) {
+        // remember it: the final bound decides later whether it is evaluated
+        const long long ci = append_slot(&S.cnt->n_cand);
+        if (ci < S.cand_cap) {
+          S.cd_t[ci] = (int)(W.t0 + j);
+          S.cd_c[ci] = mt.x;
+          S.cd_lb[ci] = lb;
+        } else {
+          S.cnt->cand_overflow = 1;
+        }
+      }
+    }
+    if (near && cost <= kLanePairs) {
+      if (cost == 1) {
+        double q = 0.0;
+#pragma unroll
+        for (int k = 0; k < MAXD; ++k) {
+          const double u = W.ct[j][k] - cv[k];
+          q += u * u;
+        }
+        v = LINK == kComplete ? q : sqrt(q);
+      } else {
+        const int bc = S.cbeg[mt.x];
+        v = mt.z < W.cid[j] ? pair_exact_inline<LINK>(S.px, d, bc, mt.y, W.beg[j], W.size[j])
+                            : pair_exact_inline<LINK>(S.px, d, W.beg[j], W.size[j], bc, mt.y);
+      }
+      ++evals;
+      ppairs += cost;
+    }
+    // the larger ones together: rows = the cluster with the lower ID
+    unsigned long long rest = __ballot(near && cost > kLanePairs && cost <= kInlinePairs);
+    while (rest) {
+      const int l = __ffsll(rest) - 1;
+      rest &= rest - 1;
+      const int c = __builtin_amdgcn_readlane(mt.x, l), nc = __builtin_amdgcn_readlane(mt.y, l);
+      const int bc = S.cbeg[c];
+      const bool first = __builtin_amdgcn_readlane(mt.z, l) < W.cid[j];
+      const int n0 = first ? nc : W.size[j], n1 = first ? W.size[j] : nc;
+      const int b0 = first ? bc : W.beg[j], b1 = first ? W.beg[j] : bc;
+      double q = 0.0;
+      if (lane < n0 * n1) {
+        const float *x = S.px + (size_t)(b0 + lane / n1) * d, *y = S.px + (size_t)(b1 + lane % n1) * d;
+        for (int k = 0; k < d; ++k) {
+          const double u = (double)x[k] - (double)y[k];
+          q += u * u;
+        }
+      }
+      double r;
+      if (LINK == kComplete) r = wave_max(q);
+      else r = wave_sum(sqrt(q)) / ((double)n0 * (double)n1);
+      if (lane == l) v = r;
+      if (lane == 0) {
+        ++evals;
+        ppairs += n0 * n1;
+      }
+    }
+    // the best of them; equal values: the lowest key
+    const double m = wave_min_f64(v);
+    if (m <= W.bestv[j] && m < INFINITY) {
+      const unsigned long long k = wave_min(v == m ? ck : kNoKey);
+      if (better(m, k, W.bestv[j], W.bk[j])) {
+        W.bestv[j] = m;
+        W.bk[j] = k;
+      }
+    }
+  }
+}
+
+template <int LINK, int MAXD, int T, bool CACHE, int LEV>
+__device__ __forceinline__ void tree_visit_pairs(const State &S, TreePairs<MAXD, T> &W, int c0, int nact,
+                                                 long long &evals, long long &ppairs, long long &visits,
+                                                 long long &hits) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int cnt = S.tree_cnt[LEV];
+  const bool in = c0 + lane < cnt;
+  const size_t c = (size_t)S.tree_off[LEV] + (in ? c0 + lane : cnt - 1);
+  const size_t tn = tree_stride(S);
+  double lo[MAXD], hi[MAXD];
+#pragma unroll
+  for (int k = 0; k < MAXD; ++k) {
+    lo[k] = k < S.d ? S.tree_lo[k * tn + c] : 0.0;
+    hi[k] = k < S.d ? S.tree_hi[k * tn + c] : 0.0;
+  }
+  const double vm = LINK == kComplete ? S.tree_vmin[c] : 0.0;
+  ++W.nodes;
+  W.bmax = 0.0;
+#pragma unroll
+  for (int j = 0; j < T; ++j) W.bmax = fmax(W.bmax, fmin(W.bound[j], W.bestv[j]));
+  auto gap = [&](const double *a, const double *b) {
+    double q = 0.0;
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k) {
+      const double g = fmax(fmax(lo[k] - b[k], a[k] - hi[k]), 0.0);
+      q += g * g;
+    }
+    return q;
+  };
+  unsigned long long any = __ballot(in && pair_floor<LINK>(gap(W.lo, W.hi), W.spmin + vm) <= pair_limit<LINK>(W.bmax));
+  if constexpr (LEV == 0) {
+    const int a = W.l0 - c0, e = W.l1 - c0;  // leaves of the start are done
+    if (e >= 0 && a < kWave) {
+      const int s0 = max(a, 0), s1 = min(e, kWave - 1);
+      any &= ~(((~0ull) >> (63 - (s1 - s0))) << s0);
+    }
+    if (!any) return;
+    unsigned long long enter[T], u = 0ull;
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      enter[j] = any & __ballot(pair_floor<LINK>(gap(W.ct[j], W.ct[j]), W.sp[j] + vm) <=
+                                pair_limit<LINK>(fmin(W.bound[j], W.bestv[j])));
+      if (!((W.all >> j) & 1u)) enter[j] = 0ull;
+      u |= enter[j];
+    }
+    W.nodes += T;
+    while (u) {
+      const int b = __ffsll(u) - 1;
+      u &= u - 1;
+      unsigned want = 0;
+#pragma unroll
+      for (int j = 0; j < T; ++j) want |= (unsigned)((enter[j] >> b) & 1ull) << j;
+      tree_leaf_pairs<LINK, MAXD, T, CACHE>(S, W, c0 + b, want, nact, evals, ppairs, visits, hits);
+    }
+  } else {
+    while (any) {
+      const int b = __ffsll(any) - 1;
+      any &= any - 1;
+      tree_visit_pairs<LINK, MAXD, T, CACHE, LEV - 1>(S, W, (c0 + b) * kTreeFan, nact, evals, ppairs, visits, hits);
+    }
+  }
+}
+
+template <int LINK, int MAXD, int T, bool CACHE, int TOP>
+__global__ __launch_bounds__(kBlock, 4) void k_nn_tree_pairs(State S, int *t_ovf) {
+  const int nterm = S.cnt->n_term, nact = S.cnt->n_act, d = S.d;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int groups = (nterm + T - 1) / T;
+  const int per = (groups + 7) / 8, xcd = blockIdx.x & 7;  // as in k_nn_tree
+  const int step = (int)(gridDim.x >> 3) * (kBlock / kWave);
+  const int g1 = min(groups, (xcd + 1) * per);
+  int g = __builtin_amdgcn_readfirstlane(xcd * per + (int)(blockIdx.x >> 3) * (kBlock / kWave) +
+                                         (int)threadIdx.x / kWave);
+  long long evals = 0, ppairs = 0, visits = 0, hits = 0;  // visits: uniform, the others per lane
+  for (; g < g1; g += step) {
+    TreePairs<MAXD, T> W;
+    W.t0 = (long long)g * T;
+    W.nodes = 0;
+    const unsigned all = (unsigned)((1ull << min((long long)T, nterm - W.t0)) - 1ull);
+    W.all = all;
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      // (a missing terminal of the last group repeats the last one)
+      const int ti = (int)min(W.t0 + j, (long long)nterm - 1);
+      const int t = S.term[ti];
+#pragma unroll
+      for (int k = 0; k < MAXD; ++k) {
+        const double c = k < d ? S.wcen[(size_t)t * d + k] : 0.0;
+        W.ct[j][k] = c;
+        W.lt[j][k] = k < d ? S.lo[(size_t)t * d + k] : 0.f;
+        W.ht[j][k] = k < d ? S.hi[(size_t)t * d + k] : 0.f;
+        W.lo[k] = j == 0 ? c : fmin(W.lo[k], c);
+        W.hi[k] = j == 0 ? c : fmax(W.hi[k], c);
+      }
+      W.slot[j] = t;
+      W.cid[j] = S.cid[t];
+      W.size[j] = S.csize[t];
+      W.beg[j] = S.cbeg[t];
+      W.pos[j] = S.term_pos[ti];
+      W.sp[j] = LINK == kComplete ? spread_lo(S, t) : 0.0;
+      W.spmin = j == 0 ? W.sp[j] : fmin(W.spmin, W.sp[j]);
+      W.bound[j] = beta_key<LINK>(S.predd[t]);
+      W.bestv[j] = INFINITY;
+      W.bk[j] = kNoKey;
+    }
+    W.l0 = W.pos[0] / kTreeFan;
+    W.l1 = W.pos[T - 1] / kTreeFan;
+    if (W.l1 > W.l0 + 3) W.l1 = W.l0;  // terminals far apart in the list
+    for (int l = W.l0; l <= W.l1; ++l)
+      tree_leaf_pairs<LINK, MAXD, T, CACHE>(S, W, l, all, nact, evals, ppairs, visits, hits);
+    tree_visit_pairs<LINK, MAXD, T, CACHE, TOP>(S, W, 0, nact, evals, ppairs, visits, hits);
+    visits += W.nodes;
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      if (lane != j || !((all >> j) & 1u)) continue;
+      const int ti = (int)(W.t0 + j);
+      t_ovf[ti] = 0;
+      S.t_best[ti] = W.bestv[j];
+      S.t_key[ti] = W.bk[j];
+      S.t_beta[ti] = fmin(W.bound[j], W.bestv[j]);
+      S.t_min[ti] = pos_bits(W.bestv[j]);
+    }
+  }
+  // one addition per block: the counters are single addresses
+  __shared__ long long work[4][kBlock / kWave];
+  evals = wave_sum_ll(evals);
+  ppairs = wave_sum_ll(ppairs);
+  hits = wave_sum_ll(hits);
+  if (lane == 0) {
+    work[0][threadIdx.x / kWave] = evals;
+    work[1][threadIdx.x / kWave] = ppairs;
+    work[2][threadIdx.x / kWave] = visits * kTreeFan;
+    work[3][threadIdx.x / kWave] = hits;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    long long v = 0;
+    for (int w = 0; w < kBlock / kWave; ++w) v += work[threadIdx.x][w];
+    long long *to = threadIdx.x == 0 ? &S.cnt->cluster_evals
+                    : threadIdx.x == 1 ? &S.cnt->point_pairs
+                    : threadIdx.x == 2 ? &S.cnt->visits[0] : &S.cnt->cache_hits;
+    if (v) atomicAdd((unsigned long long *)to, (unsigned long long)v);
   }
 }
 
@@ -4266,8 +4576,7 @@ void launch_tree_walk(State &S, int nact, hipStream_t s) {
   else if (S.tree_top == 2) k_nn_tree<LINK, MAXD, T, 2><<<grid, kBlock, 0, s>>>(S);
   else k_nn_tree<LINK, MAXD, T, 3><<<grid, kBlock, 0, s>>>(S);
 }
-template <int LINK>
-void launch_tree_search(State &S, int nact, hipStream_t s) {
+void launch_tree_build(State &S, int nact, hipStream_t s) {
   int cnt = (nact + kTreeFan - 1) / kTreeFan, off = 0, lev = 0;
   for (;;) {
     S.tree_cnt[lev] = cnt;
@@ -4281,6 +4590,36 @@ void launch_tree_search(State &S, int nact, hipStream_t s) {
   k_tree_items<<<nblk((long long)S.tree_cnt[0] * kWave, 1 << 16), kBlock, 0, s>>>(S);
   for (int l = 1; l <= S.tree_top; ++l)
     k_tree_level<<<nblk((long long)S.tree_cnt[l] * kWave, 1 << 16), kBlock, 0, s>>>(S, l);
+}
+
+template <int LINK, int MAXD, bool CACHE>
+void launch_tree_pairs_walk(State &S, int nact, hipStream_t s, int *t_ovf) {
+  constexpr int T = kPairTerms;
+  const int grid = (nblk(((long long)nact + T - 1) / T * kWave, 4096) + 7) / 8 * 8;
+  if (S.tree_top <= 1) k_nn_tree_pairs<LINK, MAXD, T, CACHE, 1><<<grid, kBlock, 0, s>>>(S, t_ovf);
+  else if (S.tree_top == 2) k_nn_tree_pairs<LINK, MAXD, T, CACHE, 2><<<grid, kBlock, 0, s>>>(S, t_ovf);
+  else k_nn_tree_pairs<LINK, MAXD, T, CACHE, 3><<<grid, kBlock, 0, s>>>(S, t_ovf);
+}
+template <int LINK>
+void launch_tree_pairs(State &S, int nact, hipStream_t s, int *t_ovf) {
+  launch_tree_build(S, nact, s);
+  tmark(S, 0, false, s);
+  if (S.d <= 2) {
+    if (S.cache_mask) launch_tree_pairs_walk<LINK, 2, true>(S, nact, s, t_ovf);
+    else launch_tree_pairs_walk<LINK, 2, false>(S, nact, s, t_ovf);
+  } else {
+    if (S.cache_mask) launch_tree_pairs_walk<LINK, 3, true>(S, nact, s, t_ovf);
+    else launch_tree_pairs_walk<LINK, 3, false>(S, nact, s, t_ovf);
+  }
+  tmark(S, 0, true, s);
+  tmark(S, 3, false, s);
+  k_cand_emit<LINK><<<2048, kBlock, 0, s>>>(S, t_ovf);
+  tmark(S, 3, true, s);
+}
+
+template <int LINK>
+void launch_tree_search(State &S, int nact, hipStream_t s) {
+  launch_tree_build(S, nact, s);
   tmark(S, 0, false, s);
   // terminals per wavefront: more share loads and box tests, fewer fit the
   // registers (128, 168 from d = 4 on). 10M points d = 2, ms: Ward 4 38.2, 8
@@ -4539,8 +4878,13 @@ void launch_round(State &S, int round, int nact, hipStream_t s, bool &need_pairs
   }
   if (S.tree && !full) {
     k_term_pos<<<gb, kBlock, 0, s>>>(S);
-    if (S.linkage == kWard) launch_tree_search<kWard>(S, nact, s);
-    else launch_tree_search<kAvgSq>(S, nact, s);
+    // (the first round of complete linkage is Ward's, see below)
+    S.single = round == 0 && S.linkage == kComplete ? 1 : 0;
+    if (S.linkage == kWard || S.single) launch_tree_search<kWard>(S, nact, s);
+    else if (S.linkage == kAvgSq) launch_tree_search<kAvgSq>(S, nact, s);
+    else if (S.linkage == kComplete) launch_tree_pairs<kComplete>(S, nact, s, t_ovf);
+    else launch_tree_pairs<kAverage>(S, nact, s, t_ovf);
+    need_pairs = !centroid_link(S.linkage) && !S.single;
     return;
   }
   if (full) {
