@@ -2,44 +2,15 @@
 // parallel filter of Alg. 1) and a stable LSD radix sort of (key, value)
 // pairs (initial curve order and the final row order).
 #include "pc_common.hpp"
+#include "pc_scan.hpp"
 
 namespace pc {
 
 namespace {
 
-constexpr int kScanItems = 4;
-constexpr int kScanTile = kBlock * kScanItems;  // 1024
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kBlock * kSortItems;  // 2048
 constexpr int kNW = kBlock / kWave;             // waves per block
-
-template <class T>
-__device__ T block_exclusive_scan(T v, T &total) {
-  __shared__ T sw[kNW + 1];
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  T x = v;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    T y = __shfl_up(x, o, kWave);
-    if (lane >= o) x += y;
-  }
-  if (lane == kWave - 1) sw[wid] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    T acc = 0;
-    for (int w = 0; w < kNW; ++w) {
-      T t = sw[w];
-      sw[w] = acc;
-      acc += t;
-    }
-    sw[kNW] = acc;
-  }
-  __syncthreads();
-  T r = x - v + sw[wid];
-  total = sw[kNW];
-  __syncthreads();
-  return r;
-}
 
 template <class T>
 __device__ __forceinline__ int scan_len(int nmax, const int *dlen) {
@@ -48,29 +19,13 @@ __device__ __forceinline__ int scan_len(int nmax, const int *dlen) {
   return l < nmax ? l : nmax;
 }
 
-// Single-pass exclusive scan by decoupled look-back. A block takes the next
-// ticket (so every block it waits for has started), scans its 1024 items,
-// publishes its total (flag 1), adds the totals of the blocks before it until
-// it meets a published prefix (flag 2), and publishes its own prefix. One
-// wavefront looks back 64 blocks at a time. The status array of the next
-// scan is cleared on the way. A look-back that waits beyond kSpinLimit
-// windows gives up with the part it has (every output position then stays
-// at or below its true value) and raises the error flag.
-constexpr unsigned long long kStValue = (1ull << 62) - 1;
-constexpr int kSpinLimit = 1 << 22;
-
+// Single-pass exclusive scan by decoupled look-back (pc_scan.hpp).
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_scan_lb(const T *in, T *out, int nmax, const int *dlen,
                                                     unsigned long long *st, int *ticket,
                                                     unsigned long long *st_next, int *ticket_next, int cap,
                                                     long long *total64, int *total32, int *err) {
-  __shared__ int sbid;
-  __shared__ T sprefix;
-  if (threadIdx.x == 0) sbid = atomicAdd(ticket, 1);
-  __syncthreads();
-  const int bid = sbid;
-  for (int j = bid * kBlock + threadIdx.x; j < cap; j += gridDim.x * kBlock) st_next[j] = 0ull;
-  if (bid == 0 && threadIdx.x == 0) *ticket_next = 0;
+  const int bid = scan_ticket(ticket, st_next, ticket_next, cap);
   const int len = scan_len<T>(nmax, dlen);
   // blocks past the device length have nothing to scan (the grid is sized
   // for the host's bound); the last live block writes the total
@@ -87,55 +42,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_lb(const T *in, T *out, int nma
   }
   T tot;
   const T ex = block_exclusive_scan<T>(s, tot);
-  if (threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
-    T prefix = 0;
-    if (bid == 0) {
-      if (lane == 0)
-        __hip_atomic_store(&st[0], (2ull << 62) | (unsigned long long)tot, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      if (lane == 0)
-        __hip_atomic_store(&st[bid], (1ull << 62) | (unsigned long long)tot, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-      int top = bid - 1;  // the nearest block not yet added
-      int spins = 0;
-      while (true) {
-        const int idx = top - lane;
-        const unsigned long long w =
-            idx >= 0 ? __hip_atomic_load(&st[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (2ull << 62);
-        const unsigned long long pm = __ballot((w >> 62) == 2ull);
-        const int fp = pm ? __ffsll((long long)pm) - 1 : kWave;  // nearest published prefix
-        const unsigned long long need = fp >= kWave - 1 ? ~0ull : ((2ull << fp) - 1ull);
-        if (__ballot((w >> 62) == 0ull) & need) {
-          // a block in the window has not published yet
-          if (++spins > kSpinLimit) {
-            if (lane == 0) atomicExch(err, 1);
-            break;
-          }
-          continue;
-        }
-        T add = lane <= fp ? (T)(w & kStValue) : (T)0;
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) add += __shfl_xor(add, o, kWave);
-        prefix += add;
-        if (fp < kWave) break;
-        top -= kWave;
-      }
-      if (lane == 0)
-        __hip_atomic_store(&st[bid], (2ull << 62) | (unsigned long long)(prefix + tot), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (lane == 0) {
-      sprefix = prefix;
-      if (bid == live - 1) {
-        if (total64) *total64 = (long long)(prefix + tot);
-        if (total32) *total32 = (int)(prefix + tot);
-      }
-    }
+  const T prefix = scan_look_back<T>(st, bid, tot, err);
+  if (bid == live - 1 && threadIdx.x == 0) {
+    if (total64) *total64 = (long long)(prefix + tot);
+    if (total32) *total32 = (int)(prefix + tot);
   }
-  __syncthreads();
-  T run = ex + sprefix;
+  T run = ex + prefix;
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
     const long long i = base + j;
@@ -217,9 +129,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const unsigned long lo
 inline int blocks_for(long long n, int tile) { return (int)((n + tile - 1) / tile); }
 
 // Short scans (at most kSingleScan elements): one block walks the tiles in
-// order, so a scan costs one launch instead of three (late rounds are short).
-constexpr int kSingleScan = 4 * kScanTile;
-
+// order.
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_scan_single(const T *in, T *out, int nmax, const int *dlen,
                                                         long long *total64, int *total32) {
@@ -263,6 +173,13 @@ void scan_ws_carve(ScanWs &ws, long long *base, long long words, int *err) {
   ws.err = err;
 }
 
+void scan_ws_prepare(ScanWs &ws, hipStream_t s) {
+  if (!ws.fresh) return;
+  // both status arrays and the tickets start at zero
+  k_zero_words<<<64, kBlock, 0, s>>>(ws.st[0], 2LL * ws.cap + 1);
+  ws.fresh = 0;
+}
+
 // Launches one scan: a single block for short ones, else the look-back scan.
 template <class T>
 static void scan_exclusive(const T *in, T *out, int nmax, const int *dlen, long long *dtotal64, int *dtotal32,
@@ -271,11 +188,7 @@ static void scan_exclusive(const T *in, T *out, int nmax, const int *dlen, long 
     k_scan_single<T><<<1, kBlock, 0, s>>>(in, out, nmax, dlen, dtotal64, dtotal32);
     return;
   }
-  if (ws.fresh) {
-    // both status arrays and the tickets start at zero
-    k_zero_words<<<64, kBlock, 0, s>>>(ws.st[0], 2LL * ws.cap + 1);
-    ws.fresh = 0;
-  }
+  scan_ws_prepare(ws, s);
   const int nb = blocks_for(nmax, kScanTile);
   if (nb > ws.cap) {
     // (the workspace is sized for the longest scan; one block is slow but safe)

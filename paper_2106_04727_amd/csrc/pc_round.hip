@@ -26,6 +26,7 @@
 #include <math.h>
 
 #include "pc_common.hpp"
+#include "pc_scan.hpp"
 
 namespace pc {
 
@@ -287,19 +288,38 @@ __global__ void k_init_slots(State S, const float *x, const unsigned *perm) {
 __global__ void k_set_nact(Counters *c, int n) { c->n_act = n; }
 
 // -------------------------------------------------------------- act pass --
-__global__ void k_act_pass(State S, int round) {
+// Terminals (Alg. 1 last line): active clusters without a successor, or whose
+// successor is no longer the cluster it was.
+struct TermFilter {
+  State S;
+  int round;
+  int positions;  // also the terminals' places in the active list
+  __device__ int len() const { return S.cnt->n_act; }
+  __device__ unsigned long long value(int i) const {
+    const int s = S.act[i];
+    const int sc = S.succ[s];
+    const bool term = sc < 0 || S.node[sc] != S.succ_node[s];  // dead slots carry node -1
+    if (term) S.term_round[s] = round;
+    S.mdst[s] = s;
+    S.moff[s] = 0;
+    return term ? 1ull : 0ull;
+  }
+  __device__ void emit(int i, unsigned long long at, unsigned long long v) const {
+    if (!v) return;
+    S.term[at] = S.act[i];
+    if (positions) S.term_pos[at] = i;
+  }
+  __device__ void total(unsigned long long n) const { S.cnt->n_term = (int)n; }
+};
+
+// grid rounds: smallest cluster and the centroids' range
+__global__ void k_act_bounds(State S) {
   const int nact = S.cnt->n_act;
   const int axes = S.d >= 2 ? 2 : 1;
   int mn = 0x7fffffff;
   unsigned long long lo[2] = {~0ull, ~0ull}, hi[2] = {0ull, 0ull};
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x) {
     const int s = S.act[i];
-    const int sc = S.succ[s];
-    const bool term = sc < 0 || S.node[sc] != S.succ_node[s];  // dead slots carry node -1
-    S.flags[i] = term ? 1 : 0;
-    if (term) S.term_round[s] = round;
-    S.mdst[s] = s;
-    S.moff[s] = 0;
     const int sz = S.csize[s];
     mn = sz < mn ? sz : mn;
     for (int a = 0; a < axes; ++a) {
@@ -320,12 +340,6 @@ __global__ void k_act_pass(State S, int round) {
       atomicMax(&S.cnt->bb_hi[a], hi[a]);
     }
   }
-}
-
-__global__ void k_scatter_flagged(const int *src, const int *flags, const int *pos, const int *dlen, int *dst) {
-  const int len = *dlen;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x)
-    if (flags[i]) dst[pos[i]] = src[i];
 }
 
 // ------------------------------------------------------------------ grid --
@@ -3056,12 +3070,6 @@ __global__ void k_gram_prep(State S) {
   }
 }
 
-__global__ void k_term_pos(State S) {
-  const int nact = S.cnt->n_act;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x)
-    if (S.flags[i]) S.term_pos[S.scan[i]] = i;
-}
-
 template <int LINK>
 __global__ void k_gram_init(State S, int *t_ovf) {
   const int nterm = min(S.tb1, S.cnt->n_term);
@@ -4230,34 +4238,31 @@ __global__ void k_chain(State S) {
 
 // Reciprocal pairs: t with succ[succ[t]] == t, kept once (from the lower ID
 // when both ends are terminals of this round).
-__global__ void k_rnn_flags(State S, int round) {
-  const int nterm = S.cnt->n_term;
-  for (int ti = blockIdx.x * blockDim.x + threadIdx.x; ti < nterm; ti += gridDim.x * blockDim.x) {
+struct PairFilter {
+  State S;
+  int round;
+  __device__ int len() const { return S.cnt->n_term; }
+  __device__ unsigned long long value(int ti) const {
     const int t = S.term[ti];
     const int u = S.succ[t];
-    int f = 0;
     if (u >= 0 && S.succ[u] == t && S.succ_node[u] == S.node[t])
-      f = (S.term_round[u] != round || S.cid[t] < S.cid[u]) ? 1 : 0;
-    S.flags[ti] = f;
+      return (S.term_round[u] != round || S.cid[t] < S.cid[u]) ? 1ull : 0ull;
+    return 0ull;
   }
-}
-
-__global__ void k_rnn_scatter(State S) {
-  const int nterm = S.cnt->n_term;
-  for (int ti = blockIdx.x * blockDim.x + threadIdx.x; ti < nterm; ti += gridDim.x * blockDim.x) {
-    if (!S.flags[ti]) continue;
-    const int m = S.scan[ti];
-    if (m < 0 || m > S.n / 2) {
+  __device__ void emit(int ti, unsigned long long at, unsigned long long v) const {
+    if (!v) return;
+    if (at > (unsigned long long)(S.n / 2)) {
       S.cnt->nonfinite = 3;
-      continue;
+      return;
     }
     const int t = S.term[ti], u = S.succ[t];
     const bool tl = S.cid[t] < S.cid[u];
-    S.m_a[m] = tl ? t : u;
-    S.m_b[m] = tl ? u : t;
-    S.m_h[m] = S.nn_h[t];
+    S.m_a[at] = tl ? t : u;
+    S.m_b[at] = tl ? u : t;
+    S.m_h[at] = S.nn_h[t];
   }
-}
+  __device__ void total(unsigned long long n) const { S.cnt->n_merge = (int)n; }
+};
 
 // Merge every reciprocal pair (Alg. 1 merge): the new cluster lives in the
 // slot of the child with the lower ID; Ward/centroid sums in FP64.
@@ -4365,23 +4370,26 @@ __global__ void k_merge_sup(State S) {
   }
 }
 
-__global__ void k_alive_flags(State S) {
-  const int nact = S.cnt->n_act;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x)
-    S.flags[i] = S.alive[S.act[i]];
-}
-
-__global__ void k_sizes_of_act(State S) {
-  const int nact = S.cnt->n_act;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x)
-    S.flags[i] = S.csize[S.act[i]];
-}
-
-__global__ void k_set_nbeg(State S) {
-  const int nact = S.cnt->n_act;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nact; i += gridDim.x * blockDim.x)
-    S.nbeg[S.act[i]] = S.scan[i];
-}
+// Survivors: the next round's active list and, where points are kept, the
+// start of each cluster's points. One prefix sum carries both: the number of
+// survivors above bit 31, their points (at most n < 2^31) below.
+struct AliveFilter {
+  State S;
+  int pts;
+  __device__ int len() const { return S.cnt->n_act; }
+  __device__ unsigned long long value(int i) const {
+    const int s = S.act[i];
+    if (!S.alive[s]) return 0ull;
+    return (1ull << 31) | (pts ? (unsigned long long)S.csize[s] : 0ull);
+  }
+  __device__ void emit(int i, unsigned long long at, unsigned long long v) const {
+    if (!v) return;
+    const int s = S.act[i];
+    S.act2[at >> 31] = s;
+    if (pts) S.nbeg[s] = (int)(at & 0x7fffffffull);
+  }
+  __device__ void total(unsigned long long n) const { S.cnt->n_act = (int)(n >> 31); }
+};
 
 // Every point moves to its cluster's new contiguous range: merged clusters
 // are the lower-ID child's points followed by the other child's.
@@ -4407,8 +4415,6 @@ __global__ void k_copy_beg(State S) {
     S.cbeg[s] = S.nbeg[s];
   }
 }
-
-__global__ void k_swap_count(Counters *c, int *total_slot) { c->n_act = *total_slot; }
 
 // --------------------------------------------------------------- finalize --
 // (size, lowest point index): both below 2^lob, packed into 2 lob bits
@@ -4849,9 +4855,7 @@ void launch_round(State &S, int round, int nact, hipStream_t s, bool &need_pairs
   const int gb = nblk(nact, 2048);
   S.single = 0;
   k_reset_round<<<1, 1, 0, s>>>(S.cnt);
-  k_act_pass<<<gb, kBlock, 0, s>>>(S, round);
-  scan_exclusive_i32(S.flags, S.scan, nact, &S.cnt->n_act, &S.cnt->n_term, S.sws, s);
-  k_scatter_flagged<<<gb, kBlock, 0, s>>>(S.act, S.flags, S.scan, &S.cnt->n_act, S.term);
+  launch_filter(TermFilter{S, round, S.gram || S.tree ? 1 : 0}, nact, S.sws, s);
   // Few active clusters: a block per terminal scans all of them (every
   // candidate's bounds and values are those of the ring search, so the rows
   // are the same), which beats a thread walking grid rings in latency; the
@@ -4859,6 +4863,7 @@ void launch_round(State &S, int round, int nact, hipStream_t s, bool &need_pairs
   const bool full = S.full_scan_max > 0 && nact <= S.full_scan_max && round > 0 && S.d <= kGridMaxDim &&
                     S.prune && !S.gram;
   if (S.d <= kGridMaxDim && S.prune && !S.gram && !S.tree && !full) {
+    k_act_bounds<<<gb, kBlock, 0, s>>>(S);
     k_grid_params<<<1, 1, 0, s>>>(S, S.cell_cap);
     k_zero_cells<<<nblk(nact + 1, 2048), kBlock, 0, s>>>(S);
     k_cell_count<<<gb, kBlock, 0, s>>>(S);
@@ -4871,13 +4876,11 @@ void launch_round(State &S, int round, int nact, hipStream_t s, bool &need_pairs
   need_pairs = false;
   if (S.gram) {
     // the host then runs the terminals in batches (launch_gram_batch)
-    k_term_pos<<<gb, kBlock, 0, s>>>(S);
     launch_gram_setup(S, nact, s);
     need_pairs = !centroid_link(S.linkage);
     return;
   }
   if (S.tree && !full) {
-    k_term_pos<<<gb, kBlock, 0, s>>>(S);
     // (the first round of complete linkage is Ward's, see below)
     S.single = round == 0 && S.linkage == kComplete ? 1 : 0;
     if (S.linkage == kWard || S.single) launch_tree_search<kWard>(S, nact, s);
@@ -4992,23 +4995,15 @@ void launch_pairs(State &S, int round, int npairs, long long work, hipStream_t s
 void launch_round_tail(State &S, int round, int nact, int merges_before, hipStream_t s) {
   const int gb = nblk(nact, 2048);
   k_chain<<<gb, kBlock, 0, s>>>(S);
-  k_rnn_flags<<<gb, kBlock, 0, s>>>(S, round);
-  scan_exclusive_i32(S.flags, S.scan, nact, &S.cnt->n_term, &S.cnt->n_merge, S.sws, s);
-  k_rnn_scatter<<<gb, kBlock, 0, s>>>(S);
+  launch_filter(PairFilter{S, round}, nact, S.sws, s);
   k_merge<<<nblk(nact / 2 + 1, 2048), kBlock, 0, s>>>(S, merges_before);
   if (S.linkage == kComplete && S.d == 2)
     k_merge_sup<<<nblk((long long)(nact / 2 + 1) * kSupDirs, 8192), kBlock, 0, s>>>(S);
   if (S.phases) (void)hipEventRecord(S.rev[2], s);
-  k_alive_flags<<<gb, kBlock, 0, s>>>(S);
-  int *total = S.scan + S.n;  // one spare int past the scan array
-  scan_exclusive_i32(S.flags, S.scan, nact, &S.cnt->n_act, total, S.sws, s);
-  k_scatter_flagged<<<gb, kBlock, 0, s>>>(S.act, S.flags, S.scan, &S.cnt->n_act, S.act2);
-  k_swap_count<<<1, 1, 0, s>>>(S.cnt, total);
+  const int pts = centroid_link(S.linkage) ? 0 : 1;
+  launch_filter(AliveFilter{S, pts}, nact, S.sws, s);
   std::swap(S.act, S.act2);
-  if (!centroid_link(S.linkage)) {
-    k_sizes_of_act<<<gb, kBlock, 0, s>>>(S);
-    scan_exclusive_i32(S.flags, S.scan, nact, &S.cnt->n_act, nullptr, S.sws, s);
-    k_set_nbeg<<<gb, kBlock, 0, s>>>(S);
+  if (pts) {
     k_move_points<<<nblk(S.n, 4096), kBlock, 0, s>>>(S);
     k_copy_beg<<<gb, kBlock, 0, s>>>(S);
     std::swap(S.px, S.px2);
