@@ -553,8 +553,9 @@ static int scan_max(int d) {
 // Gram searches are dearer the higher d and the more points. Measured (whole
 // calls, complete / average, ms):
 //   24K points d = 2: 8192 clusters 4.0 / 4.0, 16384 4.8 / 4.7, all points 10.9 / 11.1
-//   24K points d = 10: 8192 11.3 / 11.3, 12288 9.8 / 10.1, all points 13.8 / 15.0
-//   200K points d = 5 complete: 8192 201, 16384 151, 32768 127
+//   32K points d = 10, complete uniform / average blobs: 8192 15.3 / 16.8, 12288 13.7 / 14.4,
+//     16384 13.3 / 14.4 (all points, both on blobs: 23.8 / 26.1)
+//   200K points d = 5 complete: 8192 174, 16384 119, 32768 83; 250K d = 10 average: 16384 136, 24576 133, 32768 137
 //   24K points d = 64: 12288 19.9 / 27.8, 16384 18.2 / 22.6, all points 20.3 / 23.9
 //   50K points d = 128: 16384 72.8 / 139, 32768 63.5 / 71.1, 49152 70.9 / 73.1
 // Two matrices of 32768 clusters are 17 GB.
@@ -562,7 +563,7 @@ static int matrix_max(int linkage, int d, int64_t n) {
   if (centroid_link(linkage)) return scan_max(d);
   int64_t m;
   if (d <= 3) m = linkage == kAverage ? 12288 : 8192;
-  else if (d <= 16) m = std::max<int64_t>(12288, n / 6);
+  else if (d <= 16) m = std::max<int64_t>(16384, n / 6);
   else m = std::max<int64_t>(16384, n * 3 / 4);
   // complete linkage in the plane and in space searches rings faster than it
   // builds a matrix of many points (65K points d = 2: 15.2 ms without, 8.7 with;

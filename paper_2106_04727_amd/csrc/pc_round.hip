@@ -4,9 +4,11 @@
 //   act pass        terminals (Alg. 1 last line), n_min (Sec. 4.1), grid bbox
 //   grid            counting sort of active clusters by centroid cell; the
 //                   flat stand-in for the per-round centroid k-d tree
-//   nn search       per terminal: ring search outward from its own cell with
-//                   the linkage's centroid bound (Table 1 radius, Sec. 4.1-4.3)
-//                   as the stop rule; argmin on (distance, cluster ID)
+//   nn search       per terminal, with the linkage's centroid bound (Table 1
+//                   radius, Sec. 4.1-4.3) as the stop rule and argmin on
+//                   (distance, cluster ID): a walk of the box tree (Ward and
+//                   avg-2 up to d = 8, complete and average up to d = 3), a ring
+//                   search outward from its own grid cell, or MFMA Gram tiles
 //   full scan       terminals whose ring search gets too wide (and every
 //                   terminal when pruning is off or d is large): one block
 //                   scans all active clusters
@@ -2906,6 +2908,12 @@ __global__ void k_pending_key(State S) {
 //     outward margins) does not exceed that bound: Ward w D^2, complete
 //     D^2 + spreads (mean squared point distance <= largest), average D
 //     (centroid distance <= mean distance, Sec. 4.2).
+// Up to d = kGramBoxDim active clusters lie in Hilbert order, so 64 of them have
+// a small box, and a column tile whose box lies beyond every row's bound is left
+// out of either pass. Both passes are bound by the FP32 epilogue of a pair
+// (K = 16: two MFMAs per 32 x 32 pairs), so a tile left out is its whole cost.
+// 250K points of 100 mixtures, d = 10 average: both passes 100 ms a call without
+// boxes, 35 with; the call 201 / 136 ms. Higher up the boxes rule out too little.
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
@@ -3142,6 +3150,27 @@ __device__ __forceinline__ void gram_stage(const State &S, typename El<E>::T (*d
   }
 }
 
+// FP64 boxes of the centroids of 64 consecutive active clusters, d <= kGramBoxDim
+// (coordinate-major, S.n / kGT + 1 per coordinate, over the grid's items, which
+// the Gram search does not use): a wavefront per box.
+constexpr int kGramBoxDim = kGridMaxDim;
+__device__ __forceinline__ size_t gram_boxes(const State &S) { return (size_t)S.n / kGT + 1; }
+__global__ __launch_bounds__(kBlock) void k_gram_boxes(State S) {
+  const int nact = S.cnt->n_act, d = S.d, lane = threadIdx.x & (kWave - 1);
+  const size_t nb = gram_boxes(S);
+  for (int b = (blockIdx.x * kBlock + threadIdx.x) / kWave; b * kGT < nact; b += gridDim.x * kBlock / kWave) {
+    const int s = S.act[min(b * kGT + lane, nact - 1)];
+    for (int k = 0; k < d; ++k) {
+      const double c = S.wcen[(size_t)s * d + k];
+      const double lo = wave_min_f64(c), hi = -wave_min_f64(-c);
+      if (lane == 0) {
+        S.item_cen[k * nb + b] = lo;
+        S.item_cen[(d + k) * nb + b] = hi;
+      }
+    }
+  }
+}
+
 template <int LINK, int KP, int PASS, int E>
 __global__ __launch_bounds__(kBlock) void k_gram(State S) {
   typedef typename El<E>::T T;
@@ -3217,8 +3246,102 @@ __global__ __launch_bounds__(kBlock) void k_gram(State S) {
     best[i] = INFINITY;
     barg[i] = -1;
   }
+  // Up to kGramBoxDim a column tile is skipped if its box is farther from the
+  // box of the rows than any of them can use: pass 1 by the rows' largest bound
+  // (a lower bound of the key as in the box tree), pass 0 by their largest
+  // estimate once the tiles of the rows' own places are done (any pick is a
+  // valid one; the skipped tiles hold no smaller estimate).
+  constexpr bool BOX = KP <= 32;
+  const bool box = BOX && d <= kGramBoxDim;
+  __shared__ double rlo[BOX ? kGramBoxDim : 1], rhi[BOX ? kGramBoxDim : 1];
+  __shared__ unsigned long long need[kBlock / kWave];
+  __shared__ double lim;
+  if (box) {
+    for (int k = w; k < d; k += kBlock / kWave) {
+      const double c = S.wcen[(size_t)qs[min(lane, nq - 1)] * d + k];
+      const double lo = wave_min_f64(c), hi = -wave_min_f64(-c);
+      if (lane == 0) {
+        rlo[k] = lo;
+        rhi[k] = hi;
+      }
+    }
+    if (PASS == 1 && w == 0) {
+      const int r = min(lane, nq - 1);
+      const double u = S.t_beta[qt[r]] * kSlack * kSlack;
+      const double m = -wave_min_f64(-u);
+      const double nt = wave_min_f64((double)S.csize[qs[r]]);
+      if (lane == 0) {
+        // in squared centroid distances
+        if (LINK == kAverage) lim = m * m * (1.0 + 1e-12);
+        else if (LINK == kWard) lim = m * (nt + 1.0) / (2.0 * nt) * (1.0 + 1e-12);  // the other size is at least 1
+        else lim = m * (1.0 + 2e-6);
+      }
+    }
+    __syncthreads();
+  }
+  const int own0 = pmin / kGT, own1 = pmax / kGT, ntile = (nact + kGT - 1) / kGT;
+  bool own = PASS == 0 && box && own1 - own0 < 8;
+  const bool first = own;
+  int tl = own ? own0 - 1 : 0;             // current tile
+  int base = -kBlock, wv = kBlock / kWave;  // tested tiles [base, base + kBlock), place in their masks
+  unsigned long long mask = 0ull;
   long long pairs = 0;
-  for (int c0 = blockIdx.y * kGT; c0 < nact; c0 += gridDim.y * kGT) {
+  const size_t nbox = gram_boxes(S);
+  for (;;) {
+    // the next tile (uniform in the block)
+    if (own) {
+      if (++tl > own1) {
+        own = false;
+        // the largest of the rows' smallest estimates so far
+        float worst = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          float v = best[i];
+          for (int o = 16; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
+          if ((lane & 31) == 0) rbest[w][(i >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] = v;
+        }
+        __syncthreads();
+        if (w == 0) {
+          const int q = (lane >> 5) * 2;
+          if (lane < nq) worst = fminf(rbest[q][lane & 31], rbest[q + 1][lane & 31]);
+          double x = -wave_min_f64(-(double)worst);
+          if (LINK == kWard) {
+            // estimates are divided by 1/|A| + 1/|B|, at most 1/|A| + 1
+            const double nt = wave_min_f64((double)S.csize[qs[min(lane, nq - 1)]]);
+            x *= 1.0 / nt + 1.0;
+          }
+          if (lane == 0) lim = x > 0.0 ? x / (scale * scale) * 1.001 : 0.0;
+        }
+        __syncthreads();
+        continue;
+      }
+    } else {
+      while (!mask && wv < kBlock / kWave - 1) mask = need[++wv];
+      if (!mask) {
+        base += kBlock;
+        if ((long long)base * gridDim.y + blockIdx.y >= ntile) break;
+        const long long c = (long long)(base + (int)threadIdx.x) * gridDim.y + blockIdx.y;
+        bool in = c < ntile && !(first && c >= own0 && c <= own1);
+        if (in && box && (PASS == 1 || first)) {
+          double q = 0.0;
+          for (int k = 0; k < d; ++k) {
+            const double g = fmax(fmax(S.item_cen[k * nbox + c] - rhi[k], rlo[k] - S.item_cen[(d + k) * nbox + c]), 0.0);
+            q += g * g;
+          }
+          in = q <= lim;
+        }
+        const unsigned long long m = __ballot(in);
+        __syncthreads();
+        if (lane == 0) need[w] = m;
+        __syncthreads();
+        wv = -1;
+        continue;
+      }
+      const int b = __ffsll(mask) - 1;
+      mask &= mask - 1;
+      tl = (int)((long long)(base + wv * kWave + b) * gridDim.y + blockIdx.y);
+    }
+    const int c0 = tl * kGT;
     const int nc = min(kGT, nact - c0);
     __syncthreads();
     if (threadIdx.x < kGT) {
@@ -4737,6 +4860,7 @@ void launch_gram_setup(State &S, int nact, hipStream_t s) {
   k_gram_range<<<nblk((long long)nact * kWave, 1024), kBlock, 0, s>>>(S);
   k_gram_setup<<<1, kGramMaxDim, 0, s>>>(S);
   const int gp = nblk((long long)nact * kWave, 4096), pp = nblk((long long)S.n * kWave, 4096);
+  if (S.d <= kGramBoxDim) k_gram_boxes<<<nblk((long long)nact, 4096), kBlock, 0, s>>>(S);
   switch (S.elem) {
   case kElBF16:
     k_gram_prep<kElBF16><<<gp, kBlock, 0, s>>>(S);
@@ -4822,8 +4946,9 @@ void launch_check_finite(const float *x, long long count, Counters *cnt, hipStre
 
 void launch_init(State &S, const float *x, hipStream_t s) {
   const int n = S.n;
-  // the box tree orders points over all (up to 8) axes, the grid over two
-  const int axes = S.tree ? std::min(S.d, kCurveAxes) : (S.d >= 2 ? 2 : 1);
+  // the box tree and the Gram search (whose tiles have boxes) order points over
+  // all (up to 8) axes, the grid over two
+  const int axes = S.tree || S.gram ? std::min(S.d, kCurveAxes) : (S.d >= 2 ? 2 : 1);
   const int key_bits = axes <= 2 ? 16 * axes : axes * (64 / axes);
   k_reset_round<<<1, 1, 0, s>>>(S.cnt);
   k_point_bbox<<<nblk(n, 1024), kBlock, 0, s>>>(x, n, S.d, axes, S.cnt);
