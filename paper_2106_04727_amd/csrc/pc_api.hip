@@ -82,7 +82,6 @@ size_t layout(State &S, char *base, int64_t n64, int d, int linkage, bool host_p
   S.act = c.take<int>(n);
   S.act2 = c.take<int>(n);
   S.term = c.take<int>(n);
-  S.flags = c.take<int>(n);
   S.scan = c.take<int>(n + 1);
   S.ovf = c.take<int>(n);
   const bool grid = d <= kGridMaxDim;

@@ -257,7 +257,7 @@ struct State {
                    // support point in direction (cos, sin)(2 pi k / kSupDirs)
   const float *xin;  // the caller's points (original order)
   // lists
-  int *act, *act2, *term, *flags, *scan, *ovf;
+  int *act, *act2, *term, *scan, *ovf;
   // grid over active centroids
   int *cell_cnt, *cell_start, *cell_of, *cell_rank;
   int *cell_nmin;  // smallest cluster size in each cell

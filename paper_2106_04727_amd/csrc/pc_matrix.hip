@@ -37,12 +37,6 @@ constexpr int kBookItems = 4;
 // so that the same column of successive rows falls on different channels
 __host__ __device__ __forceinline__ long long mx_ld(int n) { return (((long long)n + 31) / 32 | 1) * 32; }
 
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-
 // Average: every squared distance starts from kTiny, which keeps the
 // reciprocal root finite at distance zero. Float distances are zero or at least
 // 2^-149, so kTiny changes no other value, and a sum below kZero is one of
@@ -134,7 +128,9 @@ __global__ __launch_bounds__(kBlock) void k_mx_zero(Mx X, int m) {
 // cluster that reaches into another window are added (maximised) in memory.
 // Bound by the FP64 vector units: d subtractions and fused multiply-adds, the
 // root (7 and the hardware's reciprocal root) and the sum per point pair. All
-// loads are amortised over 64 rows.
+// loads are amortised over 64 rows. 500K points d = 2 average: 70 ms, 1.8e12
+// pairs/s (the tiles of the search rounds 6.4e11); 250,007 points d = 10 average:
+// 41 ms, 7.6e11 pairs/s.
 constexpr int kHold = 8;
 template <int LINK, int MAXD>
 __global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, int n, int d, int m, int group) {
@@ -256,13 +252,23 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, i
 
 // The same for d > 16: 64 x 64 tiles, each thread a 4 x 4 block, coordinates
 // staged 16 at a time; the tile's values go through LDS, where the rows and
-// columns of each cluster are combined.
+// columns of each cluster are combined. Bound by the FP64 units (3 operations
+// per pair and coordinate, complete; 2, average) and, next, by the LDS reads.
+// The next stage is in flight while one is used, one barrier a stage, and the
+// values take the stages' LDS (four blocks a CU). 50K points d = 128 complete
+// (1.25e9 pairs): 24.6 ms with one stage and two barriers, 20.7 so; at the units'
+// nominal rate 12.3. Stages of doubles, which save the conversions, 20.7 too.
 constexpr int kKc = 16;
+constexpr int kStageIt = kWin * kKc / kBlock;
 template <int LINK>
 __global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, int n, int d, int m, int group) {
-  __shared__ __attribute__((aligned(16))) float As[kKc][kWin + 4];
-  __shared__ __attribute__((aligned(16))) float Bs[kKc][kWin + 4];
-  __shared__ double tile[kWin][kWin + 1];
+  // two stages of coordinates; the values of the tile take their place
+  struct Stage {
+    float a[kKc][kWin + 4], b[kKc][kWin + 4];
+  };
+  static_assert(2 * sizeof(Stage) <= sizeof(double) * kWin * (kWin + 1), "both stages lie under the tile");
+  __shared__ __attribute__((aligned(16))) double tile[kWin][kWin + 1];
+  Stage *st = (Stage *)&tile[0][0];
   __shared__ int rown[kWin + 2], cown[kWin + 2];  // with the neighbours outside the window
   const int nwin = (n + kWin - 1) / kWin;
   const int I = blockIdx.x;
@@ -284,24 +290,32 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, i
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int b = 0; b < 4; ++b) q[a][b] = LINK == kAverage ? kTiny : 0.0;
-    for (int k0 = 0; k0 < d; k0 += kKc) {
-      const int kc = min(kKc, d - k0);
-      __syncthreads();
-      for (int t = threadIdx.x; t < kWin * kKc; t += kBlock) {
-        const int i = t / kKc, k = t % kKc;
-        float a = 0.0f, b = 0.0f;
-        if (k < kc) {
-          if (i < nrow) a = px[(size_t)(r0 + i) * d + k0 + k];
-          if (i < ncol) b = px[(size_t)(c0 + i) * d + k0 + k];
-        }
-        As[k][i] = a;
-        Bs[k][i] = b;
+    // the next coordinates are loaded while these are used
+    float pa[kStageIt], pb[kStageIt];
+    auto load = [&](int k0) {
+#pragma unroll
+      for (int it = 0; it < kStageIt; ++it) {
+        const int t = threadIdx.x + it * kBlock, i = t / kKc, k = k0 + t % kKc;
+        pa[it] = k < d && i < nrow ? px[(size_t)(r0 + i) * d + k] : 0.0f;
+        pb[it] = k < d && i < ncol ? px[(size_t)(c0 + i) * d + k] : 0.0f;
       }
+    };
+    load(0);
+    for (int k0 = 0, cur = 0; k0 < d; k0 += kKc, cur ^= 1) {
+      Stage &g = st[cur];
+#pragma unroll
+      for (int it = 0; it < kStageIt; ++it) {
+        const int t = threadIdx.x + it * kBlock;
+        g.a[t % kKc][t / kKc] = pa[it];
+        g.b[t % kKc][t / kKc] = pb[it];
+      }
+      // one barrier: the stage written next was last read before it
       __syncthreads();
+      if (k0 + kKc < d) load(k0 + kKc);
 #pragma unroll 4
       for (int k = 0; k < kKc; ++k) {
-        const float4 av = *(const float4 *)&As[k][ty * 4];
-        const float4 bv = *(const float4 *)&Bs[k][tx * 4];
+        const float4 av = *(const float4 *)&g.a[k][ty * 4];
+        const float4 bv = *(const float4 *)&g.b[k][tx * 4];
         const double ar[4] = {(double)av.x, (double)av.y, (double)av.z, (double)av.w};
         const double br[4] = {(double)bv.x, (double)bv.y, (double)bv.z, (double)bv.w};
 #pragma unroll
@@ -314,6 +328,7 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, i
           }
       }
     }
+    __syncthreads();
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -399,7 +414,8 @@ __device__ __forceinline__ void nearer(Near &b, double v, int cid, int q) {
 // linkage compares sums times 1/size first (the row's own size is common to
 // all) and divides only for a value that may win: the product and the quotient
 // differ by less than 2^-50.
-// Bound by memory: about (n_old^2 + n_new^2) * 8 bytes a round.
+// Bound by memory: about (n_old^2 + n_new^2) * 8 bytes a round. 7151 clusters
+// average: 66 us, 3.5 TB/s (73 with the division for every entry).
 template <int LINK, bool FIRST, bool NEAR>
 __device__ __forceinline__ void pass_row(const double *__restrict__ A, const double *__restrict__ B, bool two,
                                          double *__restrict__ out, const int2 *__restrict__ src,
