@@ -846,6 +846,8 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   int nact = (int)n;
   int merges = 0;
   long long rounds = 0, terms = 0, ovfq = 0, gram_terms = 0;
+  long long evals0 = 0;    // evaluations up to the last round
+  bool even_grid = false;  // the last round searched the grid with few evaluations per terminal
   double ms_nn = 0.0, ms_merge = 0.0, ms_update = 0.0;
   Counters &h = *ctx->hcnt;
   while (nact > 1) {
@@ -898,11 +900,18 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
     if (tree_ok) {
       bool use_tree = !gram_used || nact > tree_gram_switch;
-      // complete linkage in the plane, clusters of up to three points: a thread
-      // per terminal on the grid evaluates their tiny pairs faster (second round
-      // of 1M points 0.9-1.4 ms, tree 2.2; from the fifth on 1.4 / 1.1 on
-      // mixtures, 0.8 / 1.1 on uniform points; below 300K clusters the tree wins)
-      if (linkage == kComplete && d <= 2 && rounds > 0 && nact > 300000 && nact > n / 3) use_tree = false;
+      // Complete linkage in the plane: ring searches evaluate the tiny pairs of
+      // clusters of up to three points faster (second round of 1M points 0.9-1.4
+      // ms, tree 2.2), and on evenly spread points stay ahead until a wavefront
+      // serves a terminal in either (10M uniform points: 730K clusters 13.3 /
+      // 17.5 ms, 102K 3.0 / 3.6, 53K 2.5 / 2.5). On uneven points, whose cells
+      // hold many clusters in the dense parts, the tree is ahead from a third of
+      // the points on (3M points of five Gaussians: 552K clusters 3.6 / 2.4). The
+      // last round's evaluations per terminal tell them apart: 2.3 to 2.8 on
+      // uniform points, 3.8 to 4.1 on mixtures.
+      if (linkage == kComplete && d <= 2 && rounds > 0 && nact > 60000 &&
+          (rounds == 1 || even_grid || (nact > 300000 && nact > n / 3)))
+        use_tree = false;
       S.tree = use_tree ? 1 : 0;
       S.gram = use_tree || !gram_used ? 0 : 1;
     }
@@ -1121,6 +1130,8 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
       last = now;
     }
     if (h.n_merge <= 0) return fail(PC_ERR_DEVICE, "round merged nothing");
+    even_grid = !S.tree && !S.gram && h.cluster_evals - evals0 < 3.2 * h.n_term;
+    evals0 = h.cluster_evals;
     terms += h.n_term;
     ovfq += h.n_ovf;
     merges += h.n_merge;

@@ -89,3 +89,19 @@ def test_tree_pair_ties_and_overflow(pc, link, monkeypatch):
     for cap in ("16", "400"):  # a record too small for the walk: the round runs again on the grid
         monkeypatch.setenv("PC_TEST_CAND_CAP", cap)
         assert _trees.same_tree(pc.hac(x, link), Zo, 3000, rtol=RTOL[link])
+
+
+@pytest.mark.parametrize("kind", ["u", "b"])
+def test_complete_plane_grid_or_tree(kind):
+    """Rounds above and below 60,000 active clusters, on evenly spread points
+    (ring searches down to there) and on mixtures (box tree from the third round):
+    the same rows, exactly, as the accelerated oracle's."""
+    import paper_2106_04727_amd as pc
+
+    n = 100_000
+    x = synth.uniform(n, 2, 71) if kind == "u" else synth.blobs(n, 2, 50, 0.01, 72)
+    Z = pc.hac(x, "complete")
+    Zo, cert = oracle.nnchain(x, "complete", threads=8, accel=True)
+    assert cert["min_gap"] >= 1e-10, "fixed input no longer certified tie-free"
+    _trees.assert_valid(Z, n)
+    assert _trees.same_tree(Z, Zo, n, rtol=0.0)
