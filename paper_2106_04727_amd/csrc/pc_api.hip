@@ -810,8 +810,8 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   if (points_on_device) {
     launch_check_finite(xdev, (long long)n * d, S.cnt, s);
     HIPCHK(hipGetLastError());
-    // (a direct call reads the flag with its first rounds: their kernels end on
-    // any input)
+    // (a direct call reads the flag with its first rounds, whose kernels merge
+    // nothing once it is set)
     if (!direct) {
       HIPCHK(hipMemcpyAsync(ctx->hcnt, S.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));

@@ -468,7 +468,7 @@ __device__ __forceinline__ void pass_row(const double *__restrict__ A, const dou
 #pragma unroll
       for (int j = 0; j < U; ++j) {
         const double key = LINK == kAverage ? v[j] * rs[j] : v[j];
-        if (key <= lim) {
+        if (key <= lim && q[j] != p) {
           const int4 o = id[q[j]];
           nearer(b, LINK == kAverage ? v[j] / (sz * (double)o.y) : v[j], o.x, q[j]);
           lim = LINK == kAverage ? b.v * sz * (1.0 + 0x1p-49) : b.v;
@@ -600,12 +600,15 @@ __device__ __forceinline__ unsigned long long book_scan(unsigned long long v, un
 // then every cluster looks again, and the pair of the smallest value whose
 // lower ID is lowest is reciprocal.
 // Rounds of at most `stop` clusters are left to the tail kernels.
+// Nothing is merged on non-finite input (a direct call's check is read by the
+// host only after these kernels ran), and no row past the n - 1 there are is
+// written, whatever the values.
 template <int LINK>
 __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int stop) {
   constexpr bool CEN = centroid_link(LINK);
   Counters *cnt = S.cnt;
   const int n = cnt->n_act;
-  if (n <= 1 || n <= stop || cnt->mx_err) {  // uniform
+  if (n <= 1 || n <= stop || cnt->mx_err || cnt->nonfinite) {  // uniform
     if (threadIdx.x == 0) cnt->mx_ran = 0;
     return;
   }
@@ -659,8 +662,8 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int sto
         mate[j] = -2;  // no cluster here
         continue;
       }
-      if (mate[j] < 0) bad = 1;  // no neighbour: NaN values cannot occur on finite input
-      if (part[j] != i) mate[j] = -1;
+      if (mate[j] < 0 || mate[j] == i) bad = 1;  // no neighbour: cannot occur on finite input
+      if (part[j] != i || mate[j] == i) mate[j] = -1;
       else if (idm[j].x < id[j].x) mate[j] = -2;  // merges into the other one
       if (mate[j] != -1) X.place[i] = -1;
       if (mate[j] != -2) cntv += mate[j] >= 0 ? (1ull << 32) + 1ull : 1ull;
@@ -679,6 +682,10 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int sto
       if (b >= 0) {
         const int mr = base + ml;
         const double h = key_to_height(LINK, nnv[i]);
+        if (mr >= S.n - 1) {  // (never on sound records)
+          bad = 1;
+          break;
+        }
         S.row_na[mr] = node;
         S.row_nb[mr] = idm[j].z;
         S.row_h[mr] = h;
@@ -706,7 +713,7 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int sto
   if (CEN) {
     // merged clusters' centroids, then the clusters that search again: merged,
     // or their neighbour did (see k_mx_pass)
-    if (S.d <= kScanMaxDim)
+    if (S.d <= kScanMaxDim && !bad)
       for (int m = threadIdx.x; m < merged; m += kBookThreads) merge_centroid<LINK>(S, X.mpair[m]);
     nterm = 0;
     for (int b0 = 0; b0 < kept && !bad; b0 += kTileN) {
@@ -1041,11 +1048,11 @@ __device__ __forceinline__ int tail_book(State &S, TailRec &R, TailShared &T, in
   bool drop = false;
   if (a >= 0) {
     const int j = R.nni[a];
-    if (j >= 0 && R.nni[j] == a) {
+    if (j >= 0 && j != a && R.nni[j] == a) {
       if (R.cid[j] < R.cid[a]) drop = true;
       else b = j;
     }
-    if (j < 0) T.err = 1;
+    if (j < 0 || j == a) T.err = 1;
   }
   int merged, kept;
   const int m = tail_rank(b >= 0, T.ws, merged);
@@ -1053,7 +1060,8 @@ __device__ __forceinline__ int tail_book(State &S, TailRec &R, TailShared &T, in
   if (a >= 0) {
     R.st[a] = drop ? -2 : (b >= 0 ? m : -1);
     if (!drop) R.act[k] = a;  // (every thread has read its own entry)
-    if (b >= 0) {
+    if (b >= 0 && base + m >= S.n - 1) T.err = 1;  // (never on sound records)
+    if (b >= 0 && base + m < S.n - 1) {
       const int mr = base + m;
       const double h = key_to_height(LINK, R.nnv[a]);
       const int sz = R.size[a] + R.size[b];
@@ -1136,7 +1144,7 @@ template <int LINK>
 __global__ __launch_bounds__(kTailThreads) void k_mx_tail(State S, Mx X, int stop) {
   Counters *cnt = S.cnt;
   int nact = cnt->n_act;
-  if (nact <= 1 || nact > stop || cnt->mx_err) return;
+  if (nact <= 1 || nact > stop || cnt->mx_err || cnt->nonfinite) return;
   extern __shared__ __attribute__((aligned(16))) char sm[];
   __shared__ TailShared T;
   const int n = nact, src = cnt->mx_rounds & 1;
@@ -1226,7 +1234,7 @@ template <int LINK>
 __global__ __launch_bounds__(kTailThreads) void k_sc_tail(State S, Mx X, int stop) {
   Counters *cnt = S.cnt;
   int nact = cnt->n_act;
-  if (nact <= 1 || nact > stop || cnt->mx_err) return;
+  if (nact <= 1 || nact > stop || cnt->mx_err || cnt->nonfinite) return;
   extern __shared__ __attribute__((aligned(16))) char sm[];
   __shared__ TailShared T;
   const int n = nact, src = cnt->mx_rounds & 1, d = S.d;
