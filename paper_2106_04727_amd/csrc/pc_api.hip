@@ -587,7 +587,7 @@ static bool search_pinned() {
 // scratch window or the device (the call then goes on without it).
 static bool matrix_room(pc_context *ctx, Mx &X, int m, int n, int linkage) {
   const bool scan = centroid_link(linkage);
-  const size_t need = scan ? sc_layout(X, nullptr, m) : mx_layout(X, nullptr, m, n);
+  const size_t need = scan ? sc_layout(X, nullptr, m) : mx_layout(X, nullptr, m, n, linkage);
   Buf &b = ctx->cur->mat;
   if (b.bytes < need) {
     if (ctx->cur->fixed) return false;
@@ -601,7 +601,7 @@ static bool matrix_room(pc_context *ctx, Mx &X, int m, int n, int linkage) {
     }
   }
   if (scan) sc_layout(X, (char *)b.p, m);
-  else mx_layout(X, (char *)b.p, m, n);
+  else mx_layout(X, (char *)b.p, m, n, linkage);
   return true;
 }
 
@@ -617,7 +617,7 @@ size_t matrix_extra_bytes(int64_t n, int32_t d, int32_t linkage, const pc_option
   const int m = (int)std::min<int64_t>(n, matrix_max(linkage, d, n));
   if (m < 2) return 0;
   Mx X;
-  const size_t need = centroid_link(linkage) ? sc_layout(X, nullptr, m) : mx_layout(X, nullptr, m, (int)n);
+  const size_t need = centroid_link(linkage) ? sc_layout(X, nullptr, m) : mx_layout(X, nullptr, m, (int)n, linkage);
   if (m < n) return need;
   // a call that starts with the matrix grows no candidate, pair or cache buffers
   State S;
@@ -854,7 +854,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     if (rounds > n) return fail(PC_ERR_DEVICE, "round loop did not converge");
     if (!direct && nact <= mx_max) {
       if (matrix_room(ctx, X, nact, (int)n, linkage)) ctx->mat_used = true;
-      else mx_max = nact * 3 / 4;  // less room than that: try again later
+      else mx_max = nact - 1;  // less room than that: try again with fewer clusters
     }
     if (ctx->mat_used) {
       // the remaining rounds; launches are queued several rounds at a time

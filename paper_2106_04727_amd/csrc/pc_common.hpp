@@ -212,11 +212,14 @@ struct Mx {
   int cap;          // clusters at entry
   double *k[2];     // pair values (both halves, infinity on the diagonal); round r of the
                     // matrix reads buffer r & 1 and writes the other one
+  double *kp;       // average, entered with clusters: sums of pairs of pieces, in k[1]'s place
+  int unit;         // positions between the cuts of the clusters into pieces (0: no pieces)
+  int pieces;       // rows of kp
   MxClusters c[2];
   int2 *src;        // a new cluster's sources in the old records (y: -1 if unmerged)
   int *place;       // an old cluster's place in the new records if it was not merged, else -1
   int *beg;         // first point position of a cluster at entry
-  int *own;         // cluster of every point position at entry
+  int *own;         // cluster (average: piece) of every point position at entry
   double *nnv[2];   // nearest neighbour: key and place
   int *nni[2];
   // scan rounds (Ward, avg-2): no matrix; clusters whose neighbour is searched
@@ -474,7 +477,7 @@ void launch_finalize(State &S, void *out_rows, hipStream_t s);
 
 // pair-matrix rounds (pc_matrix.hip)
 // carves the arrays for m clusters of n points out of `base` (or counts bytes)
-size_t mx_layout(Mx &X, char *base, int m, int n);
+size_t mx_layout(Mx &X, char *base, int m, int n, int linkage);
 // records, matrix and nearest neighbours of the m active clusters (direct:
 // of the n input points themselves)
 void launch_mx_enter(State &S, Mx &X, int m, int merges, bool direct, hipStream_t s);

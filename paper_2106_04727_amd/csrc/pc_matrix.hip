@@ -4,7 +4,7 @@
 //
 //   build    exact values of all active pairs from the points: every point
 //            pair once (complete: the largest squared distance; average: the
-//            sum of the distances)
+//            sum of the distances, always added in the same order)
 //   pass     one sweep per round: the merged clusters' rows and columns are
 //            combined by the Lance-Williams rules of Table 2 (complete: the
 //            maximum, average: the sum), the matrix is compacted into the
@@ -57,12 +57,19 @@ __device__ __forceinline__ double root_sum(double x) {
   return __builtin_fma(e, h, g);
 }
 
-// a cluster whose points do not lie in one window: several tiles add to its entries
+// a cluster whose points do not lie in one window: several tiles meet in its entries
 __device__ __forceinline__ bool straddles(int beg, int size) { return beg / kWin != (beg + size - 1) / kWin; }
 
+// Complete: tiles of different wavefronts meet in the entries of a cluster that
+// reaches into another window; those start at zero and keep the maximum.
+// Average: a sum depends on the order of its terms, so the clusters are cut into
+// pieces at the multiples of X.unit positions, and the tiles of one pair of
+// pieces belong to one wavefront (block, d > 16), which takes them in a fixed
+// order: the first stores, the others add (a wavefront's operations on an
+// address stay in order). The pieces' sums are then added up per cluster.
 template <int LINK>
-__device__ __forceinline__ void put(double *p, double v, bool shared) {
-  if (!shared) *p = v;
+__device__ __forceinline__ void put(double *p, double v, bool meet) {
+  if (!meet) *p = v;
   else if (LINK == kComplete) atomicMax((unsigned long long *)p, pos_bits(v));
   else unsafeAtomicAdd(p, v);
 }
@@ -102,13 +109,16 @@ __global__ void k_mx_enter(State S, Mx X, int merges, int direct) {
     S.mdst[s] = i;  // slot -> place in the active list
   }
 }
-// cluster of every point position (points lie in active-list order)
+// cluster of every point position (points lie in active-list order). Average:
+// its piece, numbered by the cluster's place plus the unit: along the positions
+// one or the other grows from piece to piece, so the numbers are distinct (a
+// cluster that ends with a unit leaves one unused).
 __global__ void k_mx_own(State S, Mx X) {
   for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < S.n; p += gridDim.x * blockDim.x)
-    X.own[p] = S.mdst[S.powner[p]];
+    X.own[p] = S.mdst[S.powner[p]] + (X.unit ? p / X.unit : 0);
 }
 
-// entries that several tiles add to start at zero
+// complete: entries in which several tiles meet start at zero
 __global__ __launch_bounds__(kBlock) void k_mx_zero(Mx X, int m) {
   const long long ld = mx_ld(m);
   for (int i = blockIdx.x; i < m; i += gridDim.x) {
@@ -119,13 +129,14 @@ __global__ __launch_bounds__(kBlock) void k_mx_zero(Mx X, int m) {
 }
 
 // ------------------------------------------------------------------ build --
-// Values of all cluster pairs, upper half, d <= 16. A block stages 64 row
-// points in LDS as FP64; each wavefront takes two windows of 64 column points
-// at a time, a column point of each per lane, and walks the rows. At the last
-// row of a cluster the lanes' sums (maxima) go to LDS; after kHold of them the
-// wavefront adds up the columns of every column cluster, a (row cluster,
-// column cluster) pair per lane, and stores one value per pair. Pairs with a
-// cluster that reaches into another window are added (maximised) in memory.
+// Values of all cluster (average: piece) pairs, upper half, d <= 16. A block
+// stages 64 row points in LDS as FP64; each wavefront takes two windows of 64
+// column points at a time, two column points per lane, and walks the rows. At the
+// last row of a cluster the lanes' sums (maxima) go to LDS; after kHold of them
+// the wavefront adds up the columns of every column cluster, a (row cluster,
+// column cluster) pair per lane, and stores one value per pair.
+// A block takes `rw` row windows in turn, a wavefront `cp` pairs of column
+// windows: one window and one pair, or (average, clusters) a unit of either.
 // Bound by the FP64 vector units: d subtractions and fused multiply-adds, the
 // root (7 and the hardware's reciprocal root) and the sum per point pair. All
 // loads are amortised over 64 rows. 500K points d = 2 average: 70 ms, 1.8e12
@@ -133,7 +144,8 @@ __global__ __launch_bounds__(kBlock) void k_mx_zero(Mx X, int m) {
 // 41 ms, 7.6e11 pairs/s.
 constexpr int kHold = 8;
 template <int LINK, int MAXD>
-__global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, int n, int d, int m, int group) {
+__global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, double *K, long long ld, int n, int d,
+                                                        int rw, int cp, int group) {
   __shared__ __attribute__((aligned(16))) double rows[kWin][MAXD];
   __shared__ int rown[kWin];
   __shared__ double held[kBlock / kWave][kHold][2 * kWin];
@@ -141,112 +153,116 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, i
   __shared__ int sown[kBlock / kWave][2 * kWin];             // column clusters: owner,
   __shared__ unsigned char sbeg[kBlock / kWave][2 * kWin];   // first column,
   __shared__ unsigned char send[kBlock / kWave][2 * kWin];   // last column, top bit
-                                                             // set if shared
-  const int nwin = (n + kWin - 1) / kWin;
-  const int I = blockIdx.x;
+                                                             // set if tiles meet there
+  const int nwin = (n + kWin - 1) / kWin, npair = (nwin + 1) / 2;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int r0 = I * kWin, nrow = min(kWin, n - r0);
-  const int pbeg = I / 2 + blockIdx.y * group;  // pairs of column windows
-  const int pend = min((nwin + 1) / 2, pbeg + group);
-  if (pbeg >= pend) return;  // uniform per block
-  for (int t = threadIdx.x; t < kWin * MAXD; t += kBlock) {
-    const int i = t / MAXD, k = t % MAXD;
-    rows[i][k] = i < nrow && k < d ? (double)px[(size_t)(r0 + i) * d + k] : 0.0;
-  }
-  if (threadIdx.x < kWin) rown[threadIdx.x] = threadIdx.x < nrow ? X.own[r0 + threadIdx.x] : -1;
-  __syncthreads();
-  // rows that end a cluster within this window
-  const int ro = rown[lane];
-  const int rnext = lane + 1 < nrow ? rown[lane + 1] : -1;
-  const unsigned long long ends = __ballot(lane < nrow && ro != rnext);
-  const bool row_in = r0 > 0 && X.own[r0 - 1] == rown[0];                    // first row's cluster began earlier
-  const bool row_out = r0 + nrow < n && X.own[r0 + nrow] == rown[nrow - 1];  // last row's cluster goes on
-  const int rfirst = rown[0], rlast = rown[nrow - 1];
-  const long long ld = mx_ld(m);
-  double *K = X.k[0];
+  // units of column pairs, from the row windows' own on
+  const int ubeg = blockIdx.x * rw / (2 * cp) + blockIdx.y * group;
+  const int uend = min((npair + cp - 1) / cp, ubeg + group);
+  if (ubeg >= uend) return;  // uniform per block
   const double q0 = LINK == kAverage ? kTiny : 0.0;
-  for (int P = pbeg + w; P < pend; P += kBlock / kWave) {
-    double cv[2][MAXD];
-    int oc[2];
-    bool cshared[2];  // this lane's column cluster reaches into another window
-    int nseg = 0, ncol = 0;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int J = 2 * P + c;
-      const int pos = J * kWin + lane;
-      const bool in = J >= I && pos < n;
-      oc[c] = in ? X.own[pos] : -1;
-#pragma unroll
-      for (int k = 0; k < MAXD; ++k) cv[c][k] = in && k < d ? (double)px[(size_t)pos * d + k] : 0.0;
-      const int prev = in && pos > 0 ? X.own[pos - 1] : -2;
-      const int next = in && pos + 1 < n ? X.own[pos + 1] : -2;
-      const bool head = in && (lane == 0 || prev != oc[c]);
-      const bool tail = in && (lane == kWave - 1 || next != oc[c]);
-      const unsigned long long heads = __ballot(head);
-      const int w0 = J * kWin;
-      cshared[c] = in && ((w0 > 0 && X.own[w0 - 1] == oc[c]) || (w0 + kWin < n && X.own[w0 + kWin] == oc[c]));
-      const int k = nseg + __popcll(heads & lanemask_lt()) - (head ? 0 : 1);
-      if (head) {
-        sown[w][k] = oc[c];
-        sbeg[w][k] = (unsigned char)(c * kWin + lane);
-      }
-      if (tail) send[w][k] = (unsigned char)((c * kWin + lane) | (cshared[c] ? 0x80 : 0));
-      nseg += __popcll(heads);
-      ncol += __popcll(__ballot(in));
+  for (int I = blockIdx.x * rw; I < min(nwin, ((int)blockIdx.x + 1) * rw); ++I) {
+    const int r0 = I * kWin, nrow = min(kWin, n - r0);
+    __syncthreads();
+    for (int t = threadIdx.x; t < kWin * MAXD; t += kBlock) {
+      const int i = t / MAXD, k = t % MAXD;
+      rows[i][k] = i < nrow && k < d ? (double)px[(size_t)(r0 + i) * d + k] : 0.0;
     }
-    if (nseg == 0) continue;
-    const bool points = nseg == ncol;  // every column cluster here is one point
-    double acc[2] = {0.0, 0.0};
-    int hold = 0;
-    for (int r = 0; r < nrow; ++r) {
-      double q[2] = {q0, q0};
-#pragma unroll
-      for (int k = 0; k < MAXD; ++k) {
-        const double a = rows[r][k];
+    if (threadIdx.x < kWin) rown[threadIdx.x] = threadIdx.x < nrow ? X.own[r0 + threadIdx.x] : -1;
+    __syncthreads();
+    // rows that end a cluster within this window
+    const int ro = rown[lane];
+    const int rnext = lane + 1 < nrow ? rown[lane + 1] : -1;
+    const unsigned long long ends = __ballot(lane < nrow && ro != rnext);
+    const bool row_in = r0 > 0 && X.own[r0 - 1] == rown[0];  // first row's cluster began earlier
+    // last row's cluster goes on (complete; a later tile adds to what average stores)
+    const bool row_out = LINK == kComplete && r0 + nrow < n && X.own[r0 + nrow] == rown[nrow - 1];
+    const int rfirst = rown[0], rlast = rown[nrow - 1];
+    for (int u = ubeg + w; u < uend; u += kBlock / kWave)
+      for (int P = max(u * cp, I / 2); P < min(npair, (u + 1) * cp); ++P) {
+        double cv[2][MAXD];
+        int oc[2];
+        int nseg = 0, ncol = 0;
+        // the columns: both windows, or the second one if the first lies before the rows
+        const int p0 = max(2 * P, I) * kWin, p1 = min(n, (2 * P + 2) * kWin) - 1;
+        const bool col_in = p0 > 0 && X.own[p0 - 1] == X.own[p0];
+        const bool col_out = LINK == kComplete && p1 + 1 < n && X.own[p1 + 1] == X.own[p1];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          const double u = a - cv[c][k];
-          if (LINK == kComplete) q[c] += u * u;  // as the oracle sums: bit-identical maxima
-          else q[c] = __builtin_fma(u, u, q[c]);
-        }
-      }
+          const int pos = (2 * P + c) * kWin + lane;
+          const bool in = pos >= p0 && pos <= p1;
+          oc[c] = in ? X.own[pos] : -1;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        if (LINK == kComplete) acc[c] = q[c] > acc[c] ? q[c] : acc[c];
-        else acc[c] += root_sum(q[c]);
-      }
-      if (!((ends >> r) & 1ull)) continue;  // uniform
-      if (points) {
-        const int ri = __builtin_amdgcn_readfirstlane(rown[r]);
-        const bool rs = (row_in && ri == rfirst) || (row_out && ri == rlast);
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-          if (ri < oc[c])
-            put<LINK>(K + (size_t)ri * ld + oc[c], LINK == kAverage && acc[c] < kZero ? 0.0 : acc[c], rs || cshared[c]);
-      } else {
-        held[w][hold][lane] = acc[0];
-        held[w][hold][kWin + lane] = acc[1];
-        if (lane == 0) heldr[w][hold] = rown[r];
-        if (++hold == kHold || (ends >> r) == 1ull) {
-          // (a wavefront's LDS operations complete in order)
-          for (int t = lane; t < hold * nseg; t += kWave) {
-            const int h = t / nseg, k = t - h * nseg;
-            const int e = send[w][k] & 0x7f;
-            double x = held[w][h][sbeg[w][k]];
-            for (int c = sbeg[w][k] + 1; c <= e; ++c) {
-              const double y = held[w][h][c];
-              x = LINK == kComplete ? (y > x ? y : x) : x + y;
-            }
-            const int ri = heldr[w][h], ci = sown[w][k];
-            if (ri < ci)
-              put<LINK>(K + (size_t)ri * ld + ci, LINK == kAverage && x < kZero ? 0.0 : x,
-                        (row_in && ri == rfirst) || (row_out && ri == rlast) || (send[w][k] & 0x80));
+          for (int k = 0; k < MAXD; ++k) cv[c][k] = in && k < d ? (double)px[(size_t)pos * d + k] : 0.0;
+          const bool head = in && (pos == p0 || X.own[pos - 1] != oc[c]);
+          const bool tail = in && (pos == p1 || X.own[pos + 1] != oc[c]);
+          const unsigned long long heads = __ballot(head);
+          const int k = nseg + __popcll(heads & lanemask_lt()) - (head ? 0 : 1);
+          if (head) {
+            sown[w][k] = oc[c];
+            sbeg[w][k] = (unsigned char)(c * kWin + lane);
           }
-          hold = 0;
+          if (tail) send[w][k] = (unsigned char)((c * kWin + lane) | ((k == 0 && col_in) || (pos == p1 && col_out) ? 0x80 : 0));
+          nseg += __popcll(heads);
+          ncol += __popcll(__ballot(in));
+        }
+        const bool points = nseg == ncol;  // every column cluster here is one point
+        double acc[2] = {0.0, 0.0};
+        int hold = 0;
+        for (int r = 0; r < nrow; ++r) {
+          double q[2] = {q0, q0};
+#pragma unroll
+          for (int k = 0; k < MAXD; ++k) {
+            const double a = rows[r][k];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              const double u2 = a - cv[c][k];
+              if (LINK == kComplete) q[c] += u2 * u2;  // as the oracle sums: bit-identical maxima
+              else q[c] = __builtin_fma(u2, u2, q[c]);
+            }
+          }
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            if (LINK == kComplete) acc[c] = q[c] > acc[c] ? q[c] : acc[c];
+            else acc[c] += root_sum(q[c]);
+          }
+          if (!((ends >> r) & 1ull)) continue;  // uniform
+          if (points) {
+            const int ri = __builtin_amdgcn_readfirstlane(rown[r]);
+            const bool rs = (row_in && ri == rfirst) || (row_out && ri == rlast);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              const int pos = (2 * P + c) * kWin + lane;
+              if (ri < oc[c])
+                put<LINK>(K + (size_t)ri * ld + oc[c], LINK == kAverage && acc[c] < kZero ? 0.0 : acc[c],
+                          rs || (pos == p0 && col_in) || (pos == p1 && col_out));
+            }
+          } else {
+            held[w][hold][lane] = acc[0];
+            held[w][hold][kWin + lane] = acc[1];
+            if (lane == 0) heldr[w][hold] = rown[r];
+            if (++hold == kHold || (ends >> r) == 1ull) {
+              // (a wavefront's LDS operations complete in order)
+              for (int t = lane; t < hold * nseg; t += kWave) {
+                const int h = t / nseg, k = t - h * nseg;
+                const int e = send[w][k] & 0x7f;
+                auto both = [](double x, double y) { return LINK == kComplete ? (y > x ? y : x) : x + y; };
+                const double *v = held[w][h];
+                int c = sbeg[w][k];
+                double x = v[c++];
+                for (; c + 3 <= e; c += 4) x = both(x, both(both(v[c], v[c + 1]), both(v[c + 2], v[c + 3])));
+                for (; c <= e; ++c) x = both(x, v[c]);
+                const int ri = heldr[w][h], ci = sown[w][k];
+                if (ri < ci)
+                  put<LINK>(K + (size_t)ri * ld + ci, LINK == kAverage && x < kZero ? 0.0 : x,
+                            (row_in && ri == rfirst) || (row_out && ri == rlast) || (send[w][k] & 0x80));
+              }
+              hold = 0;
+            }
+          }
+          acc[0] = acc[1] = 0.0;
         }
       }
-      acc[0] = acc[1] = 0.0;
-    }
   }
 }
 
@@ -261,7 +277,8 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, i
 constexpr int kKc = 16;
 constexpr int kStageIt = kWin * kKc / kBlock;
 template <int LINK>
-__global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, int n, int d, int m, int group) {
+__global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, double *K, long long ld, int n, int d,
+                                                        int rw, int group) {
   // two stages of coordinates; the values of the tile take their place
   struct Stage {
     float a[kKc][kWin + 4], b[kKc][kWin + 4];
@@ -271,13 +288,13 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, i
   Stage *st = (Stage *)&tile[0][0];
   __shared__ int rown[kWin + 2], cown[kWin + 2];  // with the neighbours outside the window
   const int nwin = (n + kWin - 1) / kWin;
-  const int I = blockIdx.x;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int r0 = I * kWin, nrow = min(kWin, n - r0);
-  const int jbeg = I + blockIdx.y * group, jend = min(nwin, jbeg + group);
-  const long long ld = mx_ld(m);
-  double *K = X.k[0];
-  for (int J = jbeg; J < jend; ++J) {
+  // a block takes `rw` row windows in turn: one, or (average, clusters) a unit,
+  // as many as divide `group`
+  const int jbeg = blockIdx.x * rw + blockIdx.y * group, jend = min(nwin, jbeg + group);
+  for (int I = blockIdx.x * rw; I < min(nwin, ((int)blockIdx.x + 1) * rw); ++I)
+  for (int J = max(jbeg, I); J < jend; ++J) {
+    const int r0 = I * kWin, nrow = min(kWin, n - r0);
     const int c0 = J * kWin, ncol = min(kWin, n - c0);
     __syncthreads();
     for (int t = threadIdx.x; t < kWin + 2; t += kBlock) {
@@ -363,11 +380,69 @@ __global__ __launch_bounds__(kBlock) void k_mx_build_hi(const float *px, Mx X, i
         const double u = tile[rr][c];
         v = LINK == kComplete ? (u > v ? u : v) : v + u;
       }
-      // shared with a tile of another window: the cluster lies across an edge
-      const bool sh = (rown[0] == ri) || (r == nrow - 1 && rown[r + 2] == ri) || (cown[0] == o) ||
-                      (c == ncol - 1 && cown[c + 2] == o);
+      // another window's tile meets this one: the cluster lies across an edge
+      // (average: an earlier tile's, of this block)
+      bool sh = rown[0] == ri || cown[0] == o;
+      if (LINK == kComplete) sh = sh || (r == nrow - 1 && rown[r + 2] == ri) || (c == ncol - 1 && cown[c + 2] == o);
       put<LINK>(K + (size_t)ri * ld + o, LINK == kAverage && v < kZero ? 0.0 : v, sh);
     }
+  }
+}
+
+// Average, clusters: the sums of a cluster's pieces, rows first. A block takes 64
+// clusters and 256 columns; the sums replace the first piece's row. Pieces are
+// few (a unit holds two clusters or more on average), so both sweeps are short
+// of the build.
+__device__ __forceinline__ int2 mx_pieces(const Mx &X, int i) {  // first piece, number
+  const int b = X.beg[i], e = b + X.c[0].id[i].y - 1;
+  return make_int2(i + b / X.unit, e / X.unit - b / X.unit + 1);
+}
+__global__ __launch_bounds__(kBlock) void k_mx_fold_rows(Mx X, int m) {
+  __shared__ int2 pc[kWin];
+  const long long ld = mx_ld(X.pieces);
+  const int i0 = blockIdx.x * kWin, nc = min(kWin, m - i0);
+  if (threadIdx.x < nc) pc[threadIdx.x] = mx_pieces(X, i0 + threadIdx.x);
+  __syncthreads();
+  const int b = blockIdx.y * kBlock + threadIdx.x;
+  if (b >= X.pieces) return;
+  for (int r = 0; r < nc; ++r) {
+    const int f = pc[r].x, k = pc[r].y;
+    if (k == 1 || b < f + k) continue;
+    double *p = X.kp + (size_t)f * ld + b;
+    double v = *p;
+    for (int j = 1; j < k; ++j) v += p[j * ld];
+    *p = v;
+  }
+}
+// then columns, into both halves of the matrix: 64 x 64 tiles through LDS;
+// infinity on the diagonal
+__global__ __launch_bounds__(kBlock) void k_mx_fold(Mx X, int m) {
+  __shared__ double t[kWin][kWin + 1];
+  __shared__ int2 pr[kWin], pc[kWin];
+  const int I = blockIdx.x, J = blockIdx.y;
+  if (J < I) return;
+  const long long lp = mx_ld(X.pieces), ld = mx_ld(m);
+  double *K = X.k[0];
+  const int r0 = I * kWin, c0 = J * kWin;
+  if (threadIdx.x < kWin) {
+    if (r0 + (int)threadIdx.x < m) pr[threadIdx.x] = mx_pieces(X, r0 + threadIdx.x);
+    if (c0 + (int)threadIdx.x < m) pc[threadIdx.x] = mx_pieces(X, c0 + threadIdx.x);
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < kWin * kWin; j += kBlock) {
+    const int r = j / kWin, c = j % kWin;
+    if (r0 + r >= m || c0 + c >= m || c0 + c <= r0 + r) continue;
+    const double *p = X.kp + (size_t)pr[r].x * lp + pc[c].x;
+    double v = p[0];
+    for (int q = 1; q < pc[c].y; ++q) v += p[q];
+    t[r][c] = v;
+    K[(size_t)(r0 + r) * ld + c0 + c] = v;
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < kWin * kWin; j += kBlock) {
+    const int r = j / kWin, c = j % kWin;  // of the transposed tile
+    if (c0 + r < m && r0 + c < m && c0 + r >= r0 + c)
+      K[(size_t)(c0 + r) * ld + r0 + c] = c0 + r > r0 + c ? t[c][r] : INFINITY;
   }
 }
 
@@ -1333,6 +1408,8 @@ __global__ __launch_bounds__(kTailThreads) void k_sc_tail(State S, Mx X, int sto
   if (threadIdx.x == 0) tail_end(cnt, T.err ? 1 : (nact > 1 ? 2 : 0), nact, base, rounds, terms, evals);
 }
 
+constexpr int kMaxGridY = 65535;
+
 inline int nblk(long long n, int cap = 4096) {
   const long long b = (n + kBlock - 1) / kBlock;
   return (int)(b < 1 ? 1 : (b < cap ? b : cap));
@@ -1350,23 +1427,36 @@ template <int LINK>
 void launch_build(State &S, Mx &X, const float *px, int m, hipStream_t s) {
   const int n = S.n, d = S.d;
   const int nwin = (n + kWin - 1) / kWin;
-  if (m < n) k_mx_zero<<<std::min(m, 1 << 16), kBlock, 0, s>>>(X, m);
+  const bool pieces = X.unit > 0;
+  double *K = pieces ? X.kp : X.k[0];
+  const long long ld = mx_ld(pieces ? X.pieces : m);
+  const int rw = pieces ? X.unit / kWin : 1;  // row windows per block
+  if (LINK == kComplete && m < n) k_mx_zero<<<std::min(m, 1 << 16), kBlock, 0, s>>>(X, m);
+  const int gx = (nwin + rw - 1) / rw;
   if (d <= 16) {
-    const int pairs = (nwin + 1) / 2;
-    // column windows per block: enough blocks for small inputs, few stagings for large ones
-    const int group = pairs <= 256 ? 4 : 32;
-    const dim3 g(nwin, (pairs + group - 1) / group);
-    if (d <= 2) k_mx_build_lo<LINK, 2><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
-    else if (d <= 3) k_mx_build_lo<LINK, 3><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
-    else if (d <= 5) k_mx_build_lo<LINK, 5><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
-    else if (d <= 10) k_mx_build_lo<LINK, 10><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
-    else k_mx_build_lo<LINK, 16><<<g, kBlock, 0, s>>>(px, X, n, d, m, group);
+    const int cp = pieces ? rw / 2 : 1;  // pairs of column windows per wavefront
+    const int units = ((nwin + 1) / 2 + cp - 1) / cp;
+    // units per block: enough blocks for small inputs, few stagings for large ones
+    int group = units <= 256 ? 4 : std::max(4, 32 / cp);
+    while ((units + group - 1) / group > kMaxGridY) group *= 2;
+    const dim3 g(gx, (units + group - 1) / group);
+    if (d <= 2) k_mx_build_lo<LINK, 2><<<g, kBlock, 0, s>>>(px, X, K, ld, n, d, rw, cp, group);
+    else if (d <= 3) k_mx_build_lo<LINK, 3><<<g, kBlock, 0, s>>>(px, X, K, ld, n, d, rw, cp, group);
+    else if (d <= 5) k_mx_build_lo<LINK, 5><<<g, kBlock, 0, s>>>(px, X, K, ld, n, d, rw, cp, group);
+    else if (d <= 10) k_mx_build_lo<LINK, 10><<<g, kBlock, 0, s>>>(px, X, K, ld, n, d, rw, cp, group);
+    else k_mx_build_lo<LINK, 16><<<g, kBlock, 0, s>>>(px, X, K, ld, n, d, rw, cp, group);
   } else {
-    const int group = nwin <= 64 ? 1 : 8;
-    k_mx_build_hi<LINK><<<dim3(nwin, (nwin + group - 1) / group), kBlock, 0, s>>>(px, X, n, d, m, group);
+    int group = std::max(nwin <= 64 ? 1 : 8, rw);
+    while ((nwin + group - 1) / group > kMaxGridY) group *= 2;
+    k_mx_build_hi<LINK><<<dim3(gx, (nwin + group - 1) / group), kBlock, 0, s>>>(px, X, K, ld, n, d, rw, group);
   }
   const int t = (m + kWin - 1) / kWin;
-  k_mx_mirror<<<dim3(t, t), kBlock, 0, s>>>(X, m);
+  if (pieces) {
+    k_mx_fold_rows<<<dim3(t, (X.pieces + kBlock - 1) / kBlock), kBlock, 0, s>>>(X, m);
+    k_mx_fold<<<dim3(t, t), kBlock, 0, s>>>(X, m);
+  } else {
+    k_mx_mirror<<<dim3(t, t), kBlock, 0, s>>>(X, m);
+  }
 }
 
 // Column parts of a scan: enough blocks to fill the chip while a wavefront
@@ -1434,8 +1524,17 @@ int mx_tail_max(int linkage, int d) {
   return std::max(1, std::min(kCenTail, kCenTailNd / d));
 }
 
-size_t mx_layout(Mx &X, char *base, int m, int n) {
+size_t mx_layout(Mx &X, char *base, int m, int n, int linkage) {
   size_t off = 0;
+  // average, clusters: two windows a unit, or as many more as keep the pieces
+  // below 1.4 times the clusters (they are few then, and the units still many)
+  X.unit = X.pieces = 0;
+  if (linkage == kAverage && m < n) {
+    long long unit = 2 * kWin;
+    while ((n - 1) / unit > m * 2LL / 5 + kWin) unit *= 2;
+    X.unit = (int)unit;
+    X.pieces = m + (int)((n - 1) / unit);
+  }
   auto take = [&](size_t bytes) {
     off = (off + 255) & ~(size_t)255;
     char *p = base ? base + off : nullptr;
@@ -1444,8 +1543,10 @@ size_t mx_layout(Mx &X, char *base, int m, int n) {
   };
   X.cap = m;
   const size_t mat = (size_t)m * (size_t)mx_ld(m) * sizeof(double);
+  const size_t pmat = (size_t)X.pieces * (size_t)mx_ld(X.pieces) * sizeof(double);
+  X.k[0] = (double *)take(mat);
+  X.k[1] = X.kp = (double *)take(std::max(mat, pmat));  // (the pieces are dead once the first round writes)
   for (int i = 0; i < 2; ++i) {
-    X.k[i] = (double *)take(mat);
     X.c[i].id = (int4 *)take((size_t)m * sizeof(int4));
     X.c[i].eff = (double *)take((size_t)m * sizeof(double));
     X.c[i].rsize = (double *)take((size_t)m * sizeof(double));

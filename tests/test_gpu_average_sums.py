@@ -1,0 +1,44 @@
+"""Sums of the pair matrix under average linkage when it is entered with
+clusters: the same bits in every run, and the values of the other searches.
+Clusters across windows of 64 positions and across units (two windows, or more
+where few clusters hold many points), giant clusters beside single points, both
+kernels (d <= 16 and above). Heights within 1e-12 of the search without a matrix
+(a mean of N FP64 terms in another order)."""
+import numpy as np
+import pytest
+
+import synth
+from tests import _trees
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(kind, n, d):
+    if kind == "blobs":
+        return synth.blobs(n, d, max(1, n // 600), 0.02, 5 + n + d)
+    rng = np.random.default_rng(n + d)  # "giants": two dense groups and far single points
+    x = rng.normal(0.0, 1.0, (n, d))
+    x[: n // 3] += 40.0
+    x[-n // 20 :] *= 300.0
+    return x[rng.permutation(n)].astype(np.float32)
+
+
+@pytest.mark.parametrize("kind,n,d,cap", [
+    ("blobs", 129, 2, 40), ("blobs", 1025, 3, 300), ("blobs", 60_000, 2, None), ("blobs", 20_000, 2, 60),
+    ("blobs", 9_001, 10, 1_000), ("blobs", 9_000, 20, 3_000), ("blobs", 20_000, 20, 60), ("giants", 20_011, 2, 2_000),
+    ("giants", 12_000, 3, 100), ("giants", 9_000, 17, 500)])
+def test_average_sums(kind, n, d, cap, monkeypatch):
+    import paper_2106_04727_amd as pc
+
+    x = _points(kind, n, d)
+    monkeypatch.setenv("PC_MATRIX_MAX", "0")
+    Z0 = pc.hac(x, "average")
+    if cap is None:
+        monkeypatch.delenv("PC_MATRIX_MAX")
+    else:
+        monkeypatch.setenv("PC_MATRIX_MAX", str(cap))
+    Z = pc.hac(x, "average")
+    _trees.assert_valid(Z, n)
+    assert _trees.same_tree(Z, Z0, n, rtol=1e-12)
+    for _ in range(3):
+        assert np.array_equal(Z, pc.hac(x, "average"))
