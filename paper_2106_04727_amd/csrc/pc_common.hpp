@@ -212,6 +212,7 @@ struct Mx {
   int cap;          // clusters at entry
   double *k[2];     // pair values (both halves, infinity on the diagonal); round r of the
                     // matrix reads buffer r & 1 and writes the other one
+  signed char *kl[2];  // average: what the sums' rounding left over (null otherwise)
   double *kp;       // average, entered with clusters: sums of pairs of pieces, in k[1]'s place
   int unit;         // positions between the cuts of the clusters into pieces (0: no pieces)
   int pieces;       // rows of kp

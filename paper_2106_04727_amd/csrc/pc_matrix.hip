@@ -9,7 +9,9 @@
 //            combined by the Lance-Williams rules of Table 2 (complete: the
 //            maximum, average: the sum), the matrix is compacted into the
 //            other buffer, and every row's nearest neighbour is found on the
-//            way
+//            way. A sum along a chain of merges takes a rounding per merge, so
+//            every entry of average linkage carries what its rounding left
+//            over, in a byte (Low)
 //   book     one block: reciprocal pairs, rows of the dendrogram, the next
 //            round's cluster records
 //
@@ -55,6 +57,48 @@ __device__ __forceinline__ double root_sum(double x) {
   h = __builtin_fma(h, r, h);
   const double e = __builtin_fma(-g, g, x);
   return __builtin_fma(e, h, g);
+}
+
+// What the rounding of a sum left over, in units of 2^-8 of its last place: a
+// sum and its byte hold 61 bits. Heights of 7151 points d = 64 over 4096 to 65536
+// point pairs, against long double, in units of 2^-53 (rms, largest): 2.2 and 4.6
+// without it, 0.7 and 1.6 with it (the search rounds, which add the points
+// themselves, 1.0 and 1.7).
+typedef signed char Low;
+struct Sum {
+  double v, r;  // rounded, and the rest
+};
+// the unit at v >= 0 (2^-60 below v's power of two), and its inverse; from their
+// exponent bits, the same unit for all v below 2^-960 (sums of distances are zero
+// or at least 2^-149)
+__device__ __forceinline__ int low_exp(double v) { return max(__double2hiint(v) >> 20, 64); }
+__device__ __forceinline__ double low_value(double v, Low l) {
+  return (double)(int)l * __hiloint2double((low_exp(v) - 60) << 20, 0);
+}
+__device__ __forceinline__ Low low_byte(const Sum &s) {
+  // (the addition rounds to a whole number, which the low word then holds)
+  const double q = s.r * __hiloint2double((2106 - low_exp(s.v)) << 20, 0) + 0x1.8p52;
+  return (Low)max(min(__double2loint(q), 127), -127);
+}
+// a + b: its rounding, and what that left over, exactly (Knuth's two-sum)
+__device__ __forceinline__ Sum two_sum(double a, double b) {
+  const double s = a + b, t = s - a;
+  return Sum{s, (a - (s - t)) + (b - t)};
+}
+// s + rest, rounded again (the rest is far below s)
+__device__ __forceinline__ Sum settled(double s, double rest) {
+  const double v = s + rest;
+  return Sum{v, rest - (v - s)};
+}
+// Both are the same bits with the operands (pairs) exchanged.
+__device__ __forceinline__ Sum add2(double a, Low la, double b, Low lb) {
+  const Sum s = two_sum(a, b);
+  return settled(s.v, s.r + (low_value(a, la) + low_value(b, lb)));
+}
+__device__ __forceinline__ Sum add4(double a, Low la, double b, Low lb, double c, Low lc, double d, Low ld) {
+  const Sum s = two_sum(a, b), t = two_sum(c, d), u = two_sum(s.v, t.v);
+  return settled(u.v, u.r + ((s.r + (low_value(a, la) + low_value(b, lb))) +
+                             (t.r + (low_value(c, lc) + low_value(d, ld)))));
 }
 
 // a cluster whose points do not lie in one window: several tiles meet in its entries
@@ -409,15 +453,20 @@ __global__ __launch_bounds__(kBlock) void k_mx_fold_rows(Mx X, int m) {
     const int f = pc[r].x, k = pc[r].y;
     if (k == 1 || b < f + k) continue;
     double *p = X.kp + (size_t)f * ld + b;
-    double v = *p;
-    for (int j = 1; j < k; ++j) v += p[j * ld];
-    *p = v;
+    Sum s{*p, 0.0};
+    for (int j = 1; j < k; ++j) {
+      const Sum u = two_sum(s.v, p[j * ld]);
+      s.v = u.v;
+      s.r += u.r;
+    }
+    *p = s.v + s.r;
   }
 }
 // then columns, into both halves of the matrix: 64 x 64 tiles through LDS;
 // infinity on the diagonal
 __global__ __launch_bounds__(kBlock) void k_mx_fold(Mx X, int m) {
   __shared__ double t[kWin][kWin + 1];
+  __shared__ Low tl[kWin][kWin + 4];
   __shared__ int2 pr[kWin], pc[kWin];
   const int I = blockIdx.x, J = blockIdx.y;
   if (J < I) return;
@@ -433,17 +482,33 @@ __global__ __launch_bounds__(kBlock) void k_mx_fold(Mx X, int m) {
     const int r = j / kWin, c = j % kWin;
     if (r0 + r >= m || c0 + c >= m || c0 + c <= r0 + r) continue;
     const double *p = X.kp + (size_t)pr[r].x * lp + pc[c].x;
-    double v = p[0];
-    for (int q = 1; q < pc[c].y; ++q) v += p[q];
-    t[r][c] = v;
-    K[(size_t)(r0 + r) * ld + c0 + c] = v;
+    Sum s{p[0], 0.0};
+    for (int q = 1; q < pc[c].y; ++q) {
+      const Sum u = two_sum(s.v, p[q]);
+      s.v = u.v;
+      s.r += u.r;
+    }
+    s = settled(s.v, s.r);
+    const Low l = low_byte(s);
+    t[r][c] = s.v;
+    tl[r][c] = l;
+    K[(size_t)(r0 + r) * ld + c0 + c] = s.v;
+    X.kl[0][(size_t)(r0 + r) * ld + c0 + c] = l;
   }
   __syncthreads();
   for (int j = threadIdx.x; j < kWin * kWin; j += kBlock) {
     const int r = j / kWin, c = j % kWin;  // of the transposed tile
-    if (c0 + r < m && r0 + c < m && c0 + r >= r0 + c)
+    if (c0 + r < m && r0 + c < m && c0 + r >= r0 + c) {
       K[(size_t)(c0 + r) * ld + r0 + c] = c0 + r > r0 + c ? t[c][r] : INFINITY;
+      X.kl[0][(size_t)(c0 + r) * ld + r0 + c] = c0 + r > r0 + c ? tl[c][r] : (Low)0;
+    }
   }
+}
+
+// average, single points: nothing is left over yet (`words` of 16 bytes)
+__global__ __launch_bounds__(kBlock) void k_mx_zero_low(uint4 *l, long long words) {
+  const long long step = (long long)gridDim.x * kBlock;
+  for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < words; i += step) l[i] = make_uint4(0, 0, 0, 0);
 }
 
 // lower half = upper half transposed, 64 x 64 tiles through LDS; infinity on
@@ -489,17 +554,23 @@ __device__ __forceinline__ void nearer(Near &b, double v, int cid, int q) {
 // linkage compares sums times 1/size first (the row's own size is common to
 // all) and divides only for a value that may win: the product and the quotient
 // differ by less than 2^-50.
-// Bound by memory: about (n_old^2 + n_new^2) * 8 bytes a round. 7151 clusters
-// average: 66 us, 3.5 TB/s (73 with the division for every entry).
-template <int LINK, bool FIRST, bool NEAR>
-__device__ __forceinline__ void pass_row(const double *__restrict__ A, const double *__restrict__ B, bool two,
-                                         double *__restrict__ out, const int2 *__restrict__ src,
+// Bound by memory: about (n_old^2 + n_new^2) * 8 bytes a round (9, average).
+// 24 rounds from 7151 clusters on, average linkage: 53 us a round without the low
+// bytes, 66 with them.
+// A merged cluster's row (TWO sources) takes up to four values per column, so two
+// columns at a time.
+template <int LINK, bool FIRST, bool NEAR, bool TWO>
+__device__ __forceinline__ void pass_row(const double *__restrict__ A, const Low *__restrict__ Al,
+                                         const double *__restrict__ B, const Low *__restrict__ Bl,
+                                         double *__restrict__ out, Low *__restrict__ outl, const int2 *__restrict__ src,
                                          const double *__restrict__ rsize, const int4 *__restrict__ id, int p,
                                          double sz, int nn, int t, int tpr, Near &b) {
-  constexpr int U = 4;
+  constexpr int U = TWO && LINK == kAverage ? 2 : 4;
+  constexpr bool LOW = LINK == kAverage && !FIRST;
   double lim = INFINITY;  // b.v, for average in units of the sums over size
   for (int q0 = t; q0 < nn; q0 += U * tpr) {
     double v[U], rs[U];
+    Low l[U];
     int2 c[U];
     int q[U];
 #pragma unroll
@@ -509,23 +580,35 @@ __device__ __forceinline__ void pass_row(const double *__restrict__ A, const dou
       if (NEAR && LINK == kAverage) rs[j] = rsize[q[j]];
     }
 #pragma unroll
-    for (int j = 0; j < U; ++j) v[j] = A[FIRST ? q[j] : c[j].x];
+    for (int j = 0; j < U; ++j) {
+      v[j] = A[FIRST ? q[j] : c[j].x];
+      if (LOW) l[j] = Al[c[j].x];
+    }
     if (!FIRST) {
-      if (two) {  // uniform in the row: a merged cluster's
+      if constexpr (TWO) {
 #pragma unroll
         for (int j = 0; j < U; ++j) {
           const double x = B[c[j].x];
-          if (c[j].y < 0) {
-            v[j] = LINK == kComplete ? (x > v[j] ? x : v[j]) : v[j] + x;
-          } else {
-            const double y = A[c[j].y], z = B[c[j].y];
-            if (LINK == kComplete) {
-              const double m1 = x > v[j] ? x : v[j], m2 = z > y ? z : y;
-              v[j] = m1 > m2 ? m1 : m2;
-            } else {
-              // the same grouping on both sides of the diagonal
-              v[j] = p < q[j] ? (v[j] + x) + (y + z) : (v[j] + y) + (x + z);
+          if (LINK == kComplete) {
+            v[j] = x > v[j] ? x : v[j];
+            if (c[j].y >= 0) {
+              const double y = A[c[j].y], z = B[c[j].y];
+              const double m2 = z > y ? z : y;
+              v[j] = v[j] > m2 ? v[j] : m2;
             }
+          } else {
+            const Low lx = Bl[c[j].x];
+            Sum s;
+            if (c[j].y < 0) {
+              s = add2(v[j], l[j], x, lx);
+            } else {
+              const double y = A[c[j].y], z = B[c[j].y];
+              const Low ly = Al[c[j].y], lz = Bl[c[j].y];
+              // the same grouping on both sides of the diagonal
+              s = p < q[j] ? add4(v[j], l[j], x, lx, y, ly, z, lz) : add4(v[j], l[j], y, ly, x, lx, z, lz);
+            }
+            v[j] = s.v;
+            l[j] = low_byte(s);
           }
         }
       } else {
@@ -533,11 +616,20 @@ __device__ __forceinline__ void pass_row(const double *__restrict__ A, const dou
         for (int j = 0; j < U; ++j)
           if (c[j].y >= 0) {
             const double y = A[c[j].y];
-            v[j] = LINK == kComplete ? (y > v[j] ? y : v[j]) : v[j] + y;
+            if (LINK == kComplete) {
+              v[j] = y > v[j] ? y : v[j];
+            } else {
+              const Sum s = add2(v[j], l[j], y, Al[c[j].y]);
+              v[j] = s.v;
+              l[j] = low_byte(s);
+            }
           }
       }
 #pragma unroll
-      for (int j = 0; j < U; ++j) out[q[j]] = v[j];
+      for (int j = 0; j < U; ++j) {
+        out[q[j]] = v[j];
+        if (LOW) outl[q[j]] = l[j];
+      }
     }
     if (NEAR) {
 #pragma unroll
@@ -576,19 +668,25 @@ __global__ __launch_bounds__(kBlock) void k_mx_pass(Mx X, const Counters *cnt) {
       rb = c.y;
       if (rb < 0 && !fresh) old = X.place[X.nni[src][ra]];
     }
-    const double *A = X.k[src] + (size_t)ra * lo;
-    const double *B = X.k[src] + (size_t)(rb < 0 ? ra : rb) * lo;
-    double *out = X.k[dst] + (size_t)p * ln;
+    const size_t oa = (size_t)ra * lo, ob = (size_t)(rb < 0 ? ra : rb) * lo, oo = (size_t)p * ln;
+    const double *A = X.k[src] + oa, *B = X.k[src] + ob;
+    double *out = X.k[dst] + oo;
+    const Low *Al = LINK == kAverage ? X.kl[src] + oa : nullptr, *Bl = LINK == kAverage ? X.kl[src] + ob : nullptr;
+    Low *outl = LINK == kAverage ? X.kl[dst] + oo : nullptr;
     Near b{INFINITY, 0x7fffffff, -1};
     if (old >= 0) {
-      pass_row<LINK, FIRST, false>(A, B, false, out, X.src, C.rsize, C.id, p, 0.0, nn, t, TPR, b);
+      pass_row<LINK, FIRST, false, false>(A, Al, B, Bl, out, outl, X.src, C.rsize, C.id, p, 0.0, nn, t, TPR, b);
       if (t == 0) {
         X.nnv[dst][p] = X.nnv[src][ra];
         X.nni[dst][p] = old;
       }
       continue;
     }
-    pass_row<LINK, FIRST, true>(A, B, rb >= 0, out, X.src, C.rsize, C.id, p, (double)C.id[p].y, nn, t, TPR, b);
+    const double sz = (double)C.id[p].y;
+    if (!FIRST && rb >= 0)  // uniform in the row
+      pass_row<LINK, FIRST, true, !FIRST>(A, Al, B, Bl, out, outl, X.src, C.rsize, C.id, p, sz, nn, t, TPR, b);
+    else
+      pass_row<LINK, FIRST, true, false>(A, Al, B, Bl, out, outl, X.src, C.rsize, C.id, p, sz, nn, t, TPR, b);
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
       const double ov = __shfl_xor(b.v, o, kWave);
@@ -755,12 +853,9 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int sto
       int sz = id[j].y, node = id[j].z;
       double e = eff[j];
       if (b >= 0) {
-        const int mr = base + ml;
+        if (base + ml > S.n - 2) bad = 1;  // (never on sound records)
+        const int mr = min(base + ml, S.n - 2);
         const double h = key_to_height(LINK, nnv[i]);
-        if (mr >= S.n - 1) {  // (never on sound records)
-          bad = 1;
-          break;
-        }
         S.row_na[mr] = node;
         S.row_nb[mr] = idm[j].z;
         S.row_h[mr] = h;
@@ -1058,7 +1153,7 @@ __global__ __launch_bounds__(kBlock) void k_sc_merge(State S, Mx X) {
 // from memory (25 us); here it is bound by its barriers (about 3 us). Clusters
 // keep their places; `act` lists the ones alive.
 constexpr int kTailThreads = 1024;
-constexpr int kMatTail = 176;    // lower triangle of 176 clusters: 123 KB
+constexpr int kMatTail = 176;    // lower triangle of 176 clusters: 123 KB, and 15 KB of low bytes
 constexpr int kCenTail = 512;    // scan rounds: one cluster per thread at most,
 constexpr int kCenTailNd = 4096; // and two FP64 values per coordinate: 64 KB
 
@@ -1226,12 +1321,15 @@ __global__ __launch_bounds__(kTailThreads) void k_mx_tail(State S, Mx X, int sto
   const long long ld = mx_ld(n);
   TailRec R;
   double *K = (double *)tail_carve(R, sm, stop);
+  Low *L = (Low *)(K + stop * (stop - 1) / 2);
   auto at = [](int i, int j) { return i > j ? i * (i - 1) / 2 + j : j * (j - 1) / 2 + i; };
   tail_begin(X, R, src, n);
   if (threadIdx.x == 0) T.err = 0;
   for (int e = threadIdx.x; e < n * n; e += kTailThreads) {
     const int i = e / n, j = e - i * n;
-    if (j < i) K[at(i, j)] = X.k[src][i * ld + j];
+    if (j >= i) continue;
+    K[at(i, j)] = X.k[src][i * ld + j];
+    if (LINK == kAverage) L[at(i, j)] = X.kl[src][i * ld + j];
   }
   int base = cnt->mx_merges, rounds = 0, before = cnt->mx_merged;
   long long terms = 0;
@@ -1246,6 +1344,7 @@ __global__ __launch_bounds__(kTailThreads) void k_mx_tail(State S, Mx X, int sto
     before = merged;
     // new rows from the old values, held in registers until all are read
     double v[kHeld];
+    Low l[kHeld];
 #pragma unroll
     for (int u = 0; u < kHeld; ++u) {
       const int e = u * kTailThreads + threadIdx.x;
@@ -1255,18 +1354,30 @@ __global__ __launch_bounds__(kTailThreads) void k_mx_tail(State S, Mx X, int sto
       const int a = R.ma[m], b = R.mb[m];
       if (c == a) continue;
       const int cm = R.st[c];
-      const double x = K[at(a, c)], y = K[at(b, c)];
-      if (cm < 0) {
-        v[u] = LINK == kComplete ? (y > x ? y : x) : x + y;
-      } else {
-        const int cb = R.mb[cm];
-        const double z = K[at(a, cb)], w = K[at(b, cb)];
-        if (LINK == kComplete) {
-          const double p = y > x ? y : x, q = w > z ? w : z;
-          v[u] = q > p ? q : p;
-        } else {
-          v[u] = a < c ? (x + y) + (z + w) : (x + z) + (y + w);  // the same on both sides
+      const int ac = at(a, c), bc = at(b, c);
+      const double x = K[ac], y = K[bc];
+      int cb = 0, az = 0, bz = 0;
+      double z = 0.0, w = 0.0;
+      if (cm >= 0) {
+        cb = R.mb[cm];
+        az = at(a, cb);
+        bz = at(b, cb);
+        z = K[az];
+        w = K[bz];
+      }
+      if (LINK == kComplete) {
+        v[u] = y > x ? y : x;
+        if (cm >= 0) {
+          const double q = w > z ? w : z;
+          v[u] = q > v[u] ? q : v[u];
         }
+      } else {
+        Sum s;
+        if (cm < 0) s = add2(x, L[ac], y, L[bc]);
+        else  // the same on both sides
+          s = a < c ? add4(x, L[ac], y, L[bc], z, L[az], w, L[bz]) : add4(x, L[ac], z, L[az], y, L[bc], w, L[bz]);
+        v[u] = s.v;
+        l[u] = low_byte(s);
       }
     }
     __syncthreads();
@@ -1275,7 +1386,9 @@ __global__ __launch_bounds__(kTailThreads) void k_mx_tail(State S, Mx X, int sto
       const int e = u * kTailThreads + threadIdx.x;
       if (e >= merged * nact || v[u] < 0.0) continue;
       const int m = e / nact;
-      K[at(R.ma[m], R.act[e - m * nact])] = v[u];
+      const int to = at(R.ma[m], R.act[e - m * nact]);
+      K[to] = v[u];
+      if (LINK == kAverage) L[to] = l[u];
     }
     for (int m = threadIdx.x; m < merged; m += kTailThreads) tail_merge_rec<LINK>(S, R, m, was);
     __syncthreads();
@@ -1456,6 +1569,8 @@ void launch_build(State &S, Mx &X, const float *px, int m, hipStream_t s) {
     k_mx_fold<<<dim3(t, t), kBlock, 0, s>>>(X, m);
   } else {
     k_mx_mirror<<<dim3(t, t), kBlock, 0, s>>>(X, m);
+    const long long words = m * mx_ld(m) / 16;  // (rows are multiples of 32 bytes)
+    if (LINK == kAverage) k_mx_zero_low<<<nblk(words), kBlock, 0, s>>>((uint4 *)X.kl[0], words);
   }
 }
 
@@ -1514,7 +1629,9 @@ __global__ void k_sc_enter(State S, Mx X, int merges, int direct) {
   }
 }
 
-inline size_t mat_tail_bytes(int stop) { return tail_rec_bytes(stop) + (size_t)stop * (stop - 1) / 2 * sizeof(double); }
+inline size_t mat_tail_bytes(int stop, bool low) {
+  return tail_rec_bytes(stop) + (size_t)stop * (stop - 1) / 2 * (sizeof(double) + (low ? sizeof(Low) : 0));
+}
 inline size_t cen_tail_bytes(int stop, int d) { return tail_rec_bytes(stop) + (size_t)stop * (2 * d + 2) * sizeof(double); }
 
 }  // namespace
@@ -1542,10 +1659,15 @@ size_t mx_layout(Mx &X, char *base, int m, int n, int linkage) {
     return p;
   };
   X.cap = m;
-  const size_t mat = (size_t)m * (size_t)mx_ld(m) * sizeof(double);
+  const size_t ents = (size_t)m * (size_t)mx_ld(m), low = linkage == kAverage ? ents * sizeof(Low) : 0;
+  const size_t mat = (ents * sizeof(double) + 255) & ~(size_t)255;
   const size_t pmat = (size_t)X.pieces * (size_t)mx_ld(X.pieces) * sizeof(double);
-  X.k[0] = (double *)take(mat);
-  X.k[1] = X.kp = (double *)take(std::max(mat, pmat));  // (the pieces are dead once the first round writes)
+  for (int i = 0; i < 2; ++i) {
+    char *p = take(i == 0 ? mat + low : std::max(mat + low, pmat));
+    X.k[i] = (double *)p;
+    X.kl[i] = low && base ? (Low *)(p + mat) : nullptr;
+  }
+  X.kp = X.k[1];  // (dead once the first round writes there)
   for (int i = 0; i < 2; ++i) {
     X.c[i].id = (int4 *)take((size_t)m * sizeof(int4));
     X.c[i].eff = (double *)take((size_t)m * sizeof(double));
@@ -1634,8 +1756,8 @@ void launch_mx_tail(State &S, Mx &X, hipStream_t s) {
   const int stop = mx_tail_max(S.linkage, S.d);
   tmark(S, 1, false, s);
   switch (S.linkage) {
-  case kComplete: k_mx_tail<kComplete><<<1, kTailThreads, mat_tail_bytes(stop), s>>>(S, X, stop); break;
-  case kAverage: k_mx_tail<kAverage><<<1, kTailThreads, mat_tail_bytes(stop), s>>>(S, X, stop); break;
+  case kComplete: k_mx_tail<kComplete><<<1, kTailThreads, mat_tail_bytes(stop, false), s>>>(S, X, stop); break;
+  case kAverage: k_mx_tail<kAverage><<<1, kTailThreads, mat_tail_bytes(stop, true), s>>>(S, X, stop); break;
   case kWard: k_sc_tail<kWard><<<1, kTailThreads, cen_tail_bytes(stop, S.d), s>>>(S, X, stop); break;
   default: k_sc_tail<kAvgSq><<<1, kTailThreads, cen_tail_bytes(stop, S.d), s>>>(S, X, stop); break;
   }
