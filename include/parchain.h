@@ -165,7 +165,17 @@ typedef struct pc_context pc_context;
 pc_status pc_context_create(int device, size_t hbm_budget_bytes, pc_context **out);
 void pc_context_destroy(pc_context *ctx);
 
-/* Device bytes pc_hac needs for (n, d, linkage); 0 on bad arguments. */
+/*
+ * Device bytes pc_hac needs for (n, d, linkage); 0 on bad arguments.
+ *
+ * With default options (prune, cache_slots = -1) the late rounds may take more:
+ * records of up to 12,288 clusters (Ward, avg-2: a few MB) or the values of all
+ * pairs of up to 32,768 clusters (complete: 16 bytes a pair of places, average
+ * 18, 17 to 25 GB at most). A call takes this room only if it lies within the
+ * context's budget and is at most half of the device's free memory, and goes on
+ * without it otherwise. The context keeps it for its next calls, and gives it
+ * back as soon as one of its other buffers finds no memory.
+ */
 size_t pc_hac_workspace_bytes(int64_t n, int32_t d, int32_t linkage, const pc_options *opt);
 
 /*
@@ -221,8 +231,9 @@ pc_status pc_hac_noalloc(pc_context *ctx, const float *points, int64_t n, int32_
  * bytes are accounted per slot, an idle slot counting what its context kept
  * from earlier requests and a busy one its request's reservation (at least
  * that). A request's reservation starts at pc_hac_workspace_bytes(n, d,
- * linkage, opt); it starts when a slot is free and the bytes it adds fit in
- * the budget. While it runs, its context may not hold more than the
+ * linkage, opt), plus the room its late rounds may take (see there) if the sum
+ * is at most a slot's share of the budget; the request starts when a slot is
+ * free and the bytes it adds fit in the budget. While it runs, its context may not hold more than the
  * reservation; a request that needs more (its candidate records grow with
  * the data) goes back to the head of the queue with twice the reservation
  * (counted in pc_server_stats.requeued) and fails with PC_ERR_OUT_OF_MEMORY

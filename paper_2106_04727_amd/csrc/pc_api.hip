@@ -249,17 +249,24 @@ hipError_t grow(pc_context *c, Buf &b, size_t bytes) {
     c->over_budget = true;  // b is left as it was
     return hipErrorOutOfMemory;
   }
+  // a matrix kept from an earlier call gives way, to the budget or to the device
   Buf &m = c->own.mat;
-  if (c->budget && &b != &m && !c->mat_used && held_bytes(c) - b.bytes + bytes > c->budget) {
-    if (m.p) hipFree(m.p);
-    m.p = nullptr;
-    m.bytes = 0;
-  }
-  if (b.p) hipFree(b.p);
-  b.p = nullptr;
-  b.bytes = 0;
+  const bool idle = &b != &m && !c->mat_used && m.p;
+  auto drop = [](Buf &x) {
+    if (x.p) hipFree(x.p);
+    x.p = nullptr;
+    x.bytes = 0;
+  };
+  if (idle && c->budget && held_bytes(c) - b.bytes + bytes > c->budget) drop(m);
+  drop(b);
   hipError_t e = hipMalloc(&b.p, bytes);
+  if (e == hipErrorOutOfMemory && idle && m.p) {
+    (void)hipGetLastError();
+    drop(m);
+    e = hipMalloc(&b.p, bytes);
+  }
   if (e == hipSuccess) b.bytes = bytes;
+  else b.p = nullptr;
   return e;
 }
 
