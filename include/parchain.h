@@ -140,10 +140,11 @@ typedef struct {
                                  (Lance-Williams rules, Table 2 / Sec. 5) */
     int64_t refined;          /* candidates the screening tiles could not rule
                                  out, then given their exact FP64 value (the
-                                 pair matrix gives it to every pair) */
-    int64_t fp64_fallbacks;   /* of those, the ones beyond one per screened
-                                 chain tail: FP64 work owed to the tiles'
-                                 error bounds */
+                                 rounds that keep a pair matrix or scan all
+                                 clusters give it to every pair) */
+    int64_t fp64_fallbacks;   /* of the screened ones, those beyond one per
+                                 screened chain tail: FP64 work owed to the
+                                 tiles' error bounds */
     /* with PC_TIME_PHASES: device time of the rounds by phase */
     double ms_nn;             /* terminals, spatial index, nearest-neighbour
                                  search and candidate evaluation */

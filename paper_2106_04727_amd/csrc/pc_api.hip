@@ -1189,7 +1189,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     stats->cache_fail = h.cache_fail;
     stats->cache_derived = h.cache_derived;
     stats->refined = h.refined;
-    stats->fp64_fallbacks = h.refined > gram_terms ? h.refined - gram_terms : 0;
+    stats->fp64_fallbacks = std::max<long long>(0, h.refined - h.mx_exact - gram_terms);
     stats->ms_nn = ms_nn;
     stats->ms_merge = ms_merge;
     stats->ms_update = ms_update;

@@ -153,6 +153,7 @@ struct Counters {
   int mx_ran;      // the last round's launches had a round to run
   int mx_pad;
   long long mx_terms;  // clusters whose neighbour was searched, summed over the rounds
+  long long mx_exact;  // pairs counted in `refined` that no tile screened
 };
 
 // Workspace of the single-pass prefix scans (decoupled look-back): two status

@@ -129,6 +129,7 @@ __global__ void k_mx_enter(State S, Mx X, int merges, int direct) {
     // every pair's exact value is computed from all its point pairs
     S.cnt->cluster_evals += m * (m - 1) / 2;
     S.cnt->refined += m * (m - 1) / 2;
+    S.cnt->mx_exact += m * (m - 1) / 2;
     S.cnt->point_pairs += (long long)n * (n - 1) / 2;
     S.cnt->visits[1] += m * (m - 1);
   }
@@ -928,6 +929,7 @@ __global__ __launch_bounds__(kBookThreads) void k_mx_book(State S, Mx X, int sto
       cnt->mx_nterm = nterm;
       cnt->cluster_evals += (long long)nterm * (kept - 1);
       cnt->refined += (long long)nterm * (kept - 1);
+      cnt->mx_exact += (long long)nterm * (kept - 1);
       cnt->visits[1] += (long long)nterm * (kept - 1);
     }
     cnt->mx_terms += CEN ? nterm : kept;
@@ -1305,6 +1307,7 @@ __device__ __forceinline__ void tail_end(Counters *cnt, int err, int nact, int b
   if (evals) {
     cnt->cluster_evals += evals;
     cnt->refined += evals;
+    cnt->mx_exact += evals;
     cnt->visits[1] += evals;
   }
 }
@@ -1625,6 +1628,7 @@ __global__ void k_sc_enter(State S, Mx X, int merges, int direct) {
     const long long pairs = (long long)n * (n - 1);
     c->cluster_evals += pairs;
     c->refined += pairs;
+    c->mx_exact += pairs;
     c->visits[1] += pairs;
   }
 }
