@@ -132,7 +132,9 @@ typedef struct {
                                  matrix's build; [3] ring search (pair emission pass) or
                                  Gram pass 1 with exact candidate values */
     int64_t kernel_launches[4];
-    int64_t candidate_visits[4]; /* candidate clusters examined, per kernel above */
+    int64_t candidate_visits[4]; /* candidate clusters examined, per kernel above
+                                 (box tree: clusters and boxes loaded, once for
+                                 all terminals of a wavefront) */
     int64_t cache_hits;       /* pair distances reused from the cache */
     int64_t cache_inserts;    /* cache slots taken (claims and stores) */
     int64_t cache_fail;       /* stores dropped because the probe window was full */

@@ -1866,7 +1866,8 @@ struct TreeTerms {
   unsigned long long bk[T];
   double lo[MAXD], hi[MAXD], ntmin, vtmin, bmax;
   int l0, l1;  // leaves evaluated at the start
-  int leaves, nodes;
+  int evals;   // keys evaluated
+  int loads;   // clusters and boxes loaded, for all terminals together
 };
 
 // the 64 clusters of a leaf, for the terminals of `want`
@@ -1879,6 +1880,8 @@ __device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD, T> &W,
   for (int k = 0; k < MAXD; ++k) cv[k] = k < S.d ? S.item_cen[(size_t)k * S.n + i] : 0.0;
   const int4 mt = S.item_meta[i];
   const double nc = (double)mt.y, vc = LINK == kAvgSq ? S.item_v[i] : 0.0;
+  const int cols = min(kTreeFan, nact - leaf * kTreeFan);
+  W.loads += cols;
 #pragma unroll
   for (int j = 0; j < T; ++j) {
     if (!((want >> j) & 1u)) continue;  // uniform
@@ -1898,7 +1901,7 @@ __device__ __forceinline__ void tree_leaf(const State &S, TreeTerms<MAXD, T> &W,
       near = key <= W.beta[j];
     }
     near = near && i != W.pos[j];
-    ++W.leaves;
+    W.evals += cols;
     if (!__ballot(near)) continue;
     // the nearest of these lanes; equal values: the lowest key
     if (LINK == kWard) key = ((2.0 * W.nt[j] * nc) / (W.nt[j] + nc)) * q;
@@ -1961,7 +1964,7 @@ __device__ __forceinline__ unsigned long long tree_test(const State &S, TreeTerm
     hi[k] = k < S.d ? S.tree_hi[k * tn + c] : 0.0;
   }
   const double nm = LINK == kWard ? (double)S.tree_nmin[c] : 0.0, vm = LINK == kAvgSq ? S.tree_vmin[c] : 0.0;
-  ++W.nodes;
+  W.loads += min(kTreeFan, cnt - c0);
   tree_bmax(W);
   unsigned long long any =
       __ballot(in && tree_near<LINK, MAXD>(lo, hi, nm, vm, W.lo, W.hi, W.ntmin, W.vtmin, W.bmax));
@@ -1979,7 +1982,6 @@ __device__ __forceinline__ unsigned long long tree_test(const State &S, TreeTerm
       enter[j] = any & __ballot(tree_near<LINK, MAXD>(lo, hi, nm, vm, W.ct[j], W.ct[j], W.nt[j], W.vt[j], W.beta[j]));
       u |= enter[j];
     }
-    W.nodes += T;
     return u;
   }
   return any;
@@ -2016,10 +2018,10 @@ __global__ __launch_bounds__(kBlock, MAXD <= 3 ? 4 : 3) void k_nn_tree(State S) 
   const int g1 = min(groups, (xcd + 1) * per);
   int g = __builtin_amdgcn_readfirstlane(xcd * per + (int)(blockIdx.x >> 3) * (kBlock / kWave) +
                                          (int)threadIdx.x / kWave);
-  long long evals = 0, boxes = 0;
+  long long evals = 0, loads = 0;
   for (; g < g1; g += step) {
     TreeTerms<MAXD, T> W;
-    W.leaves = W.nodes = 0;
+    W.evals = W.loads = 0;
     const long long t0 = (long long)g * T;
     // (a group's missing terminals repeat its last one)
 #pragma unroll
@@ -2060,14 +2062,14 @@ __global__ __launch_bounds__(kBlock, MAXD <= 3 ? 4 : 3) void k_nn_tree(State S) 
         S.t_key[ti] = W.bk[j];
       }
     }
-    evals += (long long)W.leaves * kTreeFan;
-    boxes += (long long)W.nodes * kTreeFan;
+    evals += W.evals;
+    loads += W.loads;
   }
   // one addition per block: the counters are single addresses
   __shared__ long long work[2][kBlock / kWave];
   if (lane == 0) {
     work[0][threadIdx.x / kWave] = evals;
-    work[1][threadIdx.x / kWave] = evals + boxes;
+    work[1][threadIdx.x / kWave] = loads;
   }
   __syncthreads();
   if (threadIdx.x < 2) {
@@ -2102,7 +2104,7 @@ struct TreePairs {
   unsigned long long bk[T];
   double lo[MAXD], hi[MAXD], spmin, bmax;
   int l0, l1;
-  int nodes;
+  int loads;  // clusters and boxes loaded
   unsigned all;  // the terminals there are (the last group may lack some)
   long long t0;
 };
@@ -2122,8 +2124,7 @@ __device__ __forceinline__ double pair_floor(double q, double vs) {
 
 template <int LINK, int MAXD, int T, bool CACHE>
 __device__ __forceinline__ void tree_leaf_pairs(const State &S, TreePairs<MAXD, T> &W, int leaf, unsigned want,
-                                                int nact, long long &evals, long long &ppairs, long long &visits,
-                                                long long &hits) {
+                                                int nact, long long &evals, long long &ppairs, long long &hits) {
   const int lane = threadIdx.x & (kWave - 1);
   const int d = S.d;
   const bool in = leaf * kTreeFan + lane < nact;
@@ -2138,10 +2139,10 @@ __device__ __forceinline__ void tree_leaf_pairs(const State &S, TreePairs<MAXD, 
   }
   const int4 mt = S.item_meta[i];
   const unsigned long long ck = make_key(mt.z, mt.x);
+  W.loads += min(kTreeFan, nact - leaf * kTreeFan);
 #pragma unroll
   for (int j = 0; j < T; ++j) {
     if (!((want >> j) & 1u)) continue;  // uniform
-    ++visits;
     double lb, ub;
     pair_bounds<LINK, MAXD>(W.ct[j], W.lt[j], W.ht[j], cv, lc, hc, d, lb, ub,
                             W.sp[j] + (double)__int_as_float(mt.w));
@@ -2234,8 +2235,7 @@ __device__ __forceinline__ void tree_leaf_pairs(const State &S, TreePairs<MAXD, 
 
 template <int LINK, int MAXD, int T, bool CACHE, int LEV>
 __device__ __forceinline__ void tree_visit_pairs(const State &S, TreePairs<MAXD, T> &W, int c0, int nact,
-                                                 long long &evals, long long &ppairs, long long &visits,
-                                                 long long &hits) {
+                                                 long long &evals, long long &ppairs, long long &hits) {
   const int lane = threadIdx.x & (kWave - 1);
   const int cnt = S.tree_cnt[LEV];
   const bool in = c0 + lane < cnt;
@@ -2248,7 +2248,7 @@ __device__ __forceinline__ void tree_visit_pairs(const State &S, TreePairs<MAXD,
     hi[k] = k < S.d ? S.tree_hi[k * tn + c] : 0.0;
   }
   const double vm = LINK == kComplete ? S.tree_vmin[c] : 0.0;
-  ++W.nodes;
+  W.loads += min(kTreeFan, cnt - c0);
   W.bmax = 0.0;
 #pragma unroll
   for (int j = 0; j < T; ++j) W.bmax = fmax(W.bmax, fmin(W.bound[j], W.bestv[j]));
@@ -2277,20 +2277,19 @@ __device__ __forceinline__ void tree_visit_pairs(const State &S, TreePairs<MAXD,
       if (!((W.all >> j) & 1u)) enter[j] = 0ull;
       u |= enter[j];
     }
-    W.nodes += T;
     while (u) {
       const int b = __ffsll(u) - 1;
       u &= u - 1;
       unsigned want = 0;
 #pragma unroll
       for (int j = 0; j < T; ++j) want |= (unsigned)((enter[j] >> b) & 1ull) << j;
-      tree_leaf_pairs<LINK, MAXD, T, CACHE>(S, W, c0 + b, want, nact, evals, ppairs, visits, hits);
+      tree_leaf_pairs<LINK, MAXD, T, CACHE>(S, W, c0 + b, want, nact, evals, ppairs, hits);
     }
   } else {
     while (any) {
       const int b = __ffsll(any) - 1;
       any &= any - 1;
-      tree_visit_pairs<LINK, MAXD, T, CACHE, LEV - 1>(S, W, (c0 + b) * kTreeFan, nact, evals, ppairs, visits, hits);
+      tree_visit_pairs<LINK, MAXD, T, CACHE, LEV - 1>(S, W, (c0 + b) * kTreeFan, nact, evals, ppairs, hits);
     }
   }
 }
@@ -2309,7 +2308,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_nn_tree_pairs(State S, int *t_ovf
   for (; g < g1; g += step) {
     TreePairs<MAXD, T> W;
     W.t0 = (long long)g * T;
-    W.nodes = 0;
+    W.loads = 0;
     const unsigned all = (unsigned)((1ull << min((long long)T, nterm - W.t0)) - 1ull);
     W.all = all;
 #pragma unroll
@@ -2341,9 +2340,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_nn_tree_pairs(State S, int *t_ovf
     W.l1 = W.pos[T - 1] / kTreeFan;
     if (W.l1 > W.l0 + 3) W.l1 = W.l0;  // terminals far apart in the list
     for (int l = W.l0; l <= W.l1; ++l)
-      tree_leaf_pairs<LINK, MAXD, T, CACHE>(S, W, l, all, nact, evals, ppairs, visits, hits);
-    tree_visit_pairs<LINK, MAXD, T, CACHE, TOP>(S, W, 0, nact, evals, ppairs, visits, hits);
-    visits += W.nodes;
+      tree_leaf_pairs<LINK, MAXD, T, CACHE>(S, W, l, all, nact, evals, ppairs, hits);
+    tree_visit_pairs<LINK, MAXD, T, CACHE, TOP>(S, W, 0, nact, evals, ppairs, hits);
+    visits += W.loads;
 #pragma unroll
     for (int j = 0; j < T; ++j) {
       if (lane != j || !((all >> j) & 1u)) continue;
@@ -2363,7 +2362,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_nn_tree_pairs(State S, int *t_ovf
   if (lane == 0) {
     work[0][threadIdx.x / kWave] = evals;
     work[1][threadIdx.x / kWave] = ppairs;
-    work[2][threadIdx.x / kWave] = visits * kTreeFan;
+    work[2][threadIdx.x / kWave] = visits;
     work[3][threadIdx.x / kWave] = hits;
   }
   __syncthreads();
