@@ -48,7 +48,8 @@ constexpr double kTiny = 1e-300, kZero = 1e-120;
 // Square root of a positive double for the sums of average linkage:
 // hardware reciprocal root, then Goldschmidt's coupled iteration and one
 // residual correction (Markstein). No scaling: x is at least kTiny and below
-// 2^260.
+// 2^270 (2^258 a coordinate, 2048 of them), its reciprocal root between 2^-135 and
+// 2^499, and no product or residual of the steps leaves the normal range.
 __device__ __forceinline__ double root_sum(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;

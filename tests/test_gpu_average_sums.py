@@ -7,6 +7,7 @@ kernels (d <= 16 and above). Heights within 1e-12 of the search without a matrix
 import numpy as np
 import pytest
 
+import oracle
 import synth
 from tests import _trees
 
@@ -71,3 +72,20 @@ def test_average_height_error():
         err.append(float((np.longdouble(h) - exact) / exact) * 2.0 ** 53)
     assert len(err) > 50
     assert np.sqrt(np.mean(np.square(err))) <= 0.85
+
+
+@pytest.mark.parametrize("n,d", [(130, 3), (130, 20), (700, 200)])
+@pytest.mark.parametrize("scale", [3.4e38, 1e-36, 1e-43])
+def test_average_at_the_ends_of_the_range(n, d, scale):
+    """Coordinates next to the largest floats, and so small that they lose bits:
+    squared distances from 2^-290 to 2^266."""
+    import paper_2106_04727_amd as pc
+
+    x = (synth.uniform(n, d, 17).astype(np.float64) * 2.0 - 1.0) * scale
+    x = x.astype(np.float32)
+    assert np.isfinite(x).all()
+    Z = pc.hac(x, "average")
+    _trees.assert_valid(Z, n)
+    Zo, cert = oracle.nnchain(x, "average", threads=8)
+    assert cert["min_gap"] >= 1e-10, "fixed input no longer certified tie-free"
+    assert _trees.same_tree(Z, Zo, n, rtol=1e-12)
