@@ -47,7 +47,36 @@ struct Carver {
   }
 };
 
-size_t layout(State &S, char *base, int64_t n64, int d, int linkage, bool host_points, int elem,
+// The searches of a call.
+// Ward and avg-2 up to d = 8 search a box tree over centroids in Hilbert
+// order (whole calls, 1M points, ms: d = 2 Ward grid 10.8, tree 7.0; d = 1
+// 124 / 5.2; 200K points: d = 3 14.4 / 6.5, d = 5 Gram search 84.9, tree 6.8,
+// d = 8 96 / 10.6 on mixtures, 87 / 32 on uniform points), the Gram search
+// above. Without the tree (2^30 points and more, PC_TREE_MAX_DIM): the centroid
+// grid up to d = 5, the Gram search above. Complete and average linkage: tree and
+// grid up to d = 3 (see the round loop), the Gram search above.
+// Tuning knobs: PC_TREE_MAX_DIM (0 = no tree, at most 8), PC_TREE_GRAM_SWITCH
+// (rounds with at most that many active clusters take the Gram search from
+// d = 4 on; 0, the default: none), PC_GRAM_MIN_DIM.
+struct Route {
+  bool tree;  // box tree
+  bool gram;  // Gram search in some round (none if the tree serves them all)
+  long long tree_gram_switch;
+};
+Route route_of(int64_t n, int d, int linkage, bool prune) {
+  Route r;
+  int tree_max = kTreeMaxDim;
+  if (const char *e = getenv("PC_TREE_MAX_DIM")) tree_max = std::min(kTreeMaxDim, atoi(e));
+  r.tree = prune && d <= std::min(tree_max, centroid_link(linkage) ? kTreeMaxDim : kTreePairDim) && n < (1LL << 30);
+  int gram_min = centroid_link(linkage) && !r.tree ? 6 : kGramMinDim;
+  if (const char *e = getenv("PC_GRAM_MIN_DIM")) gram_min = std::max(kGramMinDim, atoi(e));
+  r.tree_gram_switch = 0;
+  if (const char *e = getenv("PC_TREE_GRAM_SWITCH")) r.tree_gram_switch = atoll(e);
+  r.gram = prune && d >= gram_min && d <= kGramMaxDim && (!r.tree || r.tree_gram_switch > 0);
+  return r;
+}
+
+size_t layout(State &S, char *base, int64_t n64, int d, int linkage, bool gram, bool host_points, int elem,
               float **xin = nullptr, pc_merge **rows_out = nullptr) {
   Carver c{base};
   const size_t n = (size_t)n64;
@@ -98,7 +127,6 @@ size_t layout(State &S, char *base, int64_t n64, int d, int linkage, bool host_p
   S.item_v = c.take<double>(grid && avgsq ? n : 1);
   S.item_lo = c.take<float>(grid && pts ? n * d : 1);
   S.item_hi = c.take<float>(grid && pts ? n * d : 1);
-  const bool gram = d >= kGramMinDim && d <= kGramMaxDim;
   const int kp = gram_kp(d);
   S.gkp = kp;
   S.pkp = point_kp(d);
@@ -361,8 +389,8 @@ size_t pc_hac_workspace_bytes(int64_t n, int32_t d, int32_t linkage, const pc_op
   if (n < 1 || d < 1 || d > kMaxDim || n > 2147483646LL || linkage < 0 || linkage > 3) return 0;
   if (opt && (opt->precision < 0 || opt->precision > 2)) return 0;
   State S;
-  size_t bytes = layout(S, nullptr, n, d, linkage, true, opt ? opt->precision : 0);
-  const bool gram = d >= kGramMinDim && d <= kGramMaxDim;
+  const bool gram = route_of(n, d, linkage, !opt || opt->prune).gram;
+  size_t bytes = layout(S, nullptr, n, d, linkage, gram, true, opt ? opt->precision : 0);
   // initial candidate record (grown on demand), pair list, tiles and filter
   const size_t cand = (size_t)std::max<int64_t>(1 << 22, 4 * n);
   const size_t per_cand = 3 * sizeof(double) + sizeof(long long) + sizeof(int4) + 4 * sizeof(int);
@@ -471,7 +499,7 @@ static pc_status grow_cand(pc_context *ctx, State &S, long long cap) {
 // (`ws` bytes), the scan partials, then the candidate record, pair list, tile
 // partials or filter indices and the two cache tables in fixed shares of what
 // is left. cache_cap: entries per cache table (a power of two, 0: no cache).
-static pc_status carve_scratch(char *base, size_t ws, int64_t n, int d, int linkage, int cache_slots, Bufs &B,
+static pc_status carve_scratch(char *base, size_t ws, int64_t n, int linkage, bool gram, int cache_slots, Bufs &B,
                                unsigned long long &cache_cap) {
   const size_t total = PC_NOALLOC_SCRATCH_BYTES;
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -492,7 +520,6 @@ static pc_status carve_scratch(char *base, size_t ws, int64_t n, int d, int link
   if (off + (1u << 20) > total)
     return fail(PC_ERR_OUT_OF_MEMORY, "input too large for the allocation-free scratch buffer");
   const size_t rest = total - off - 8 * 256;  // alignment slack of the windows below
-  const bool gram = d >= kGramMinDim && d <= kGramMaxDim;
   B.mat.p = base + off;  // the records below are dead once the pair matrix is built
   B.mat.bytes = total - off;
   double fc = 0.0, fp = 0.0, ft = 0.0, ff = 0.0, fk = 0.0;  // shares of the rest
@@ -628,7 +655,8 @@ size_t matrix_extra_bytes(int64_t n, int32_t d, int32_t linkage, const pc_option
   if (m < n) return need;
   // a call that starts with the matrix grows no candidate, pair or cache buffers
   State S;
-  const size_t ws = layout(S, nullptr, n, d, linkage, true, opt ? opt->precision : 0);
+  const bool gram = route_of(n, d, linkage, true).gram;
+  const size_t ws = layout(S, nullptr, n, d, linkage, gram, true, opt ? opt->precision : 0);
   const size_t part = (2 * ((size_t)(2 * n + 64) / 1024 + 1024) + 1) * sizeof(long long);
   const size_t model = pc_hac_workspace_bytes(n, d, linkage, opt);
   return ws + part + need > model ? ws + part + need - model : 0;
@@ -683,7 +711,9 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   ctx->mat_used = false;
   State S;
   memset(&S, 0, sizeof(S));
-  const size_t need = layout(S, nullptr, n, d, linkage, !points_on_device, elem);
+  const Route route = route_of(n, d, linkage, prune);
+  const bool tree_ok = route.tree, gram_used = route.gram;
+  const size_t need = layout(S, nullptr, n, d, linkage, gram_used, !points_on_device, elem);
   // allocation-free call: every buffer is a window of the scratch array
   Bufs fixed;
   struct Restore {
@@ -695,7 +725,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     if (!ctx->scratch)
       return fail(PC_ERR_DEVICE, std::string("no scratch address for this device: ") +
                                      hipGetErrorString(ctx->scratch_error));
-    pc_status st = carve_scratch((char *)ctx->scratch, need, n, d, linkage, cache_slots, fixed, fixed_cache);
+    pc_status st = carve_scratch((char *)ctx->scratch, need, n, linkage, gram_used, cache_slots, fixed, fixed_cache);
     if (st != PC_OK) return st;
     if (!fixed_cache) cache_slots = 0;  // no room for the cache: values are recomputed (same rows)
     ctx->cur = &fixed;
@@ -703,34 +733,16 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   HIPCHK(grow(ctx, ctx->cur->ws, need));
   float *xstage = nullptr;
   pc_merge *rstage = nullptr;
-  layout(S, (char *)ctx->cur->ws.p, n, d, linkage, !points_on_device, elem, &xstage, &rstage);
+  layout(S, (char *)ctx->cur->ws.p, n, d, linkage, gram_used, !points_on_device, elem, &xstage, &rstage);
   S.n = (int)n;
   S.d = d;
   S.linkage = linkage;
   S.prune = prune;
   S.timing = (opt && (opt->timing & PC_TIME_KERNELS)) ? 1 : 0;
   S.phases = (opt && (opt->timing & PC_TIME_PHASES)) ? 1 : 0;
-  // Ward and avg-2 up to d = 8 search a box tree over centroids in Hilbert
-  // order (whole calls, 1M points, ms: d = 2 Ward grid 10.8, tree 7.0; d = 1
-  // 124 / 5.2; 200K points: d = 3 14.4 / 6.5, d = 5 Gram search 84.9, tree 6.8,
-  // d = 8 96 / 10.6 on mixtures, 87 / 32 on uniform points), the Gram search
-  // above. Without the tree: the centroid grid up to d = 5, the Gram search above.
-  // Tuning knobs: PC_TREE_MAX_DIM (0 = no tree, at most 8), PC_TREE_GRAM_SWITCH
-  // (rounds with at most that many active clusters take the Gram search from
-  // d = 4 on; 0, the default: none), PC_GRAM_MIN_DIM.
-  int tree_max = kTreeMaxDim;
-  if (const char *e = getenv("PC_TREE_MAX_DIM")) tree_max = std::min(kTreeMaxDim, atoi(e));
-  const bool tree_ok = prune && d <= std::min(tree_max, centroid_link(linkage) ? kTreeMaxDim : kTreePairDim) && n < (1LL << 30);
-  int gram_min = centroid_link(linkage) && !tree_ok ? 6 : kGramMinDim;
-  if (const char *e = getenv("PC_GRAM_MIN_DIM")) gram_min = std::max(kGramMinDim, atoi(e));
-  const bool gram_ok = prune && d >= gram_min && d <= kGramMaxDim;
-  long long tree_gram_switch = 0;
-  if (const char *e = getenv("PC_TREE_GRAM_SWITCH")) tree_gram_switch = atoll(e);
-  // no Gram search in any round of a call that searches the tree in all of them
-  const bool gram_used = gram_ok && (!tree_ok || tree_gram_switch > 0);
   // the first round's search (tree_ok also fixes the axes of the initial order)
   S.tree = tree_ok ? 1 : 0;
-  S.gram = (!tree_ok && gram_ok) ? 1 : 0;
+  S.gram = (!tree_ok && gram_used) ? 1 : 0;
   S.kt = &ctx->ktimer;
   S.kt->begin_call();
   S.rev = ctx->rev;
@@ -906,7 +918,7 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     }
     if (S.phases) HIPCHK(hipEventRecord(ctx->rev[0], s));
     if (tree_ok) {
-      bool use_tree = !gram_used || nact > tree_gram_switch;
+      bool use_tree = !gram_used || nact > route.tree_gram_switch;
       // Complete linkage in the plane: ring searches evaluate the tiny pairs of
       // clusters of up to three points faster (second round of 1M points 0.9-1.4
       // ms, tree 2.2), and on evenly spread points stay ahead until a wavefront
