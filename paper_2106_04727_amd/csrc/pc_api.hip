@@ -847,7 +847,8 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
   S.cell_budget = centroid_link(linkage) ? 24 : 160;  // measured on the 1M 2-D workload
   if (const char *e = getenv("PC_CELL_BUDGET")) S.cell_budget = std::max(1, atoi(e));
   // tuning knob: active clusters at or below which the ring search's first
-  // pass runs a wavefront per terminal (0: never)
+  // pass runs a wavefront per terminal (0: never). By default only rounds that
+  // run again after a record overflow search rings with that few clusters.
   // (avg-2: off; its per-item work is too light to pay for combining lanes)
   S.wave_terms = linkage == kAvgSq ? 0 : (linkage == kWard ? 30000 : 60000);  // swept on the 1M 2-D workload
   if (const char *e = getenv("PC_WAVE_TERMS")) S.wave_terms = std::max(0, atoi(e));

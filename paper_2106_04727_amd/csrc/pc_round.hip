@@ -827,6 +827,10 @@ __device__ __forceinline__ double beta_key(unsigned predbits) {
 }
 
 // ------------------------------------------------------ ring search kernel --
+// The grid's searches serve complete linkage in the plane while many clusters are
+// active (see the round loop), rounds of complete and average linkage whose tree
+// walk overflows its record, which only the rings can walk twice, and, with the
+// tree switched off, every linkage: the tests compare the tree with them.
 // One thread per terminal. PASS 0: Ward (final result) or, for complete and
 // average, the search bound plus the best inline-evaluated candidate. PASS 1
 // (complete/average): re-walk the rings under the final bound and emit the
@@ -2089,8 +2093,8 @@ __global__ __launch_bounds__(kBlock, MAXD <= 3 ? 4 : 3) void k_nn_tree(State S) 
 // pairs of up to kLanePairs point pairs each by itself and larger ones together,
 // a point pair per lane.
 // Terminals per wavefront: one. Two share loads but take 156 registers instead
-// of 84, and the walk waits for the points it gathers (1M planar points: 36.4
-// ms with one, 37.7 with two, 39.7 with four).
+// of 84, and the walk waits for the points it gathers (1M planar points: 34.7
+// ms with one, 35.4 with two, 37.5 with four).
 // Bound by the latency of those gathers: about 18K cycles per terminal at 100K
 // clusters, against 38K cycles of a thread's ring walk.
 constexpr int kLanePairs = 8;
