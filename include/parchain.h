@@ -173,11 +173,11 @@ void pc_context_destroy(pc_context *ctx);
  *
  * With default options (prune, cache_slots = -1) the late rounds may take more:
  * records of up to 12,288 clusters (Ward, avg-2: a few MB) or the values of all
- * pairs of up to 32,768 clusters (complete: 16 bytes a pair of places, average
- * 18, 17 to 25 GB at most). A call takes this room only if it lies within the
- * context's budget and is at most half of the device's free memory, and goes on
- * without it otherwise. The context keeps it for its next calls, and gives it
- * back as soon as one of its other buffers finds no memory.
+ * pairs of up to 32,768 clusters (complete linkage up to 17 GB, average up to
+ * 27). A call takes this room only if it lies within the context's budget and is
+ * at most half of the device's free memory, and goes on without it otherwise. The
+ * context keeps it for its next calls, and gives it back as soon as one of its
+ * other buffers finds no memory.
  */
 size_t pc_hac_workspace_bytes(int64_t n, int32_t d, int32_t linkage, const pc_options *opt);
 

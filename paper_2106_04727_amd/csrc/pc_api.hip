@@ -591,7 +591,8 @@ static int scan_max(int d) {
 //   200K points d = 5 complete: 8192 174, 16384 119, 32768 83; 250K d = 10 average: 16384 136, 24576 133, 32768 137
 //   24K points d = 64: 12288 19.9 / 27.8, 16384 18.2 / 22.6, all points 20.3 / 23.9
 //   50K points d = 128: 16384 72.8 / 139, 32768 63.5 / 71.1, 49152 70.9 / 73.1
-// Two matrices of 32768 clusters are 17 GB.
+// Two matrices of 32768 clusters are 17 GB (average linkage 19, and up to 27 while
+// its pieces lie in the second one's place).
 static int matrix_max(int linkage, int d, int64_t n) {
   if (centroid_link(linkage)) return scan_max(d);
   int64_t m;

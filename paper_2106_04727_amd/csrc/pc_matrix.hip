@@ -185,9 +185,9 @@ __global__ __launch_bounds__(kBlock) void k_mx_zero(Mx X, int m) {
 // windows: one window and one pair, or (average, clusters) a unit of either.
 // Bound by the FP64 vector units: d subtractions and fused multiply-adds, the
 // root (7 and the hardware's reciprocal root) and the sum per point pair. All
-// loads are amortised over 64 rows. 500K points d = 2 average: 70 ms, 1.8e12
+// loads are amortised over 64 rows. 500K points d = 2 average: 68 ms, 1.8e12
 // pairs/s (the tiles of the search rounds 6.4e11); 250,007 points d = 10 average:
-// 41 ms, 7.6e11 pairs/s.
+// 38 ms, 8.3e11 pairs/s.
 constexpr int kHold = 8;
 template <int LINK, int MAXD>
 __global__ __launch_bounds__(kBlock) void k_mx_build_lo(const float *px, Mx X, double *K, long long ld, int n, int d,
