@@ -95,12 +95,13 @@ def roofline(kname, link, d, ms, nl, sts):
         achieved = work / (avg_ms / 1000.0) / 1e12
         r = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP64_VEC_TFLOPS, "unit": "TFLOP/s",
              "note": "exact FP64 point-pair tiles; work = point pairs x FP64 flops per pair"}
-    elif link in ("ward", "avgsq") and 3 <= d <= 5 and kname == "ring_search":
-        # the slot holds the box-tree walk (gathers) of the rounds with many
-        # active clusters and Gram pass 0 (MFMA pairs) of the later ones, and
-        # its visit count adds both: no single unit prices it
+    elif link in ("ward", "avgsq") and ((3 <= d <= 8 and kname == "ring_search") or
+                                        (d >= 4 and kname == "block_search")):
+        # the box-tree walk loads clusters and boxes of different sizes (2d
+        # words a box) and is bound by its FP64 tests at these d; the scan
+        # rounds evaluate FP64 keys: no unit here prices either
         r = {"bound": None, "achieved": None, "peak": None, "unit": None,
-             "note": "box-tree walk and Gram pass 0 share this timing slot; not priced"}
+             "note": "box-tree walk or scan rounds, bound by FP64 tests and keys; not priced"}
         r.update({"frac": None, "traffic": None, "kernel": kname, "linkage": link, "avg_launch_ms": avg_ms,
                   "launches": nl, "work_per_launch": None})
         return r
