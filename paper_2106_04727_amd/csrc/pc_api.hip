@@ -385,41 +385,21 @@ void pc_context_destroy(pc_context *c) {
   delete c;
 }
 
-size_t pc_hac_workspace_bytes(int64_t n, int32_t d, int32_t linkage, const pc_options *opt) {
-  if (n < 1 || d < 1 || d > kMaxDim || n > 2147483646LL || linkage < 0 || linkage > 3) return 0;
-  if (opt && (opt->precision < 0 || opt->precision > 2)) return 0;
-  State S;
-  const bool gram = route_of(n, d, linkage, !opt || opt->prune).gram;
-  size_t bytes = layout(S, nullptr, n, d, linkage, gram, true, opt ? opt->precision : 0);
-  // initial candidate record (grown on demand), pair list, tiles and filter
-  const size_t cand = (size_t)std::max<int64_t>(1 << 22, 4 * n);
-  const size_t per_cand = 3 * sizeof(double) + sizeof(long long) + sizeof(int4) + 4 * sizeof(int);
-  if (!centroid_link(linkage) || gram) bytes += cand * per_cand + 1024;
-  bytes += ((size_t)(2 * n + 64) / 1024 + 1024) * sizeof(long long);
-  if (!centroid_link(linkage)) {
-    const size_t pc = (size_t)std::max<int64_t>(1 << 20, 2 * n);
-    bytes += pc * (4 * sizeof(long long) + 6 * sizeof(int)) + 1024;
-    if (linkage == kAverage) bytes += ((size_t)1 << 22) * sizeof(double);
-    if (linkage == kComplete) bytes += cand * sizeof(int);
-    int cs = opt ? opt->cache_slots : -1;
-    if (cs < 0) cs = linkage == kAverage ? 64 : 0;
-    if (cs > 0) {
-      size_t cap = (size_t)1 << 16;
-      while (cap < (size_t)n * (size_t)cs && cap < ((size_t)1 << 31)) cap <<= 1;
-      bytes += 2 * cap * 2 * sizeof(unsigned long long);
-    }
-  }
-  return bytes;
-}
-
 // Largest candidate record / pair list a round may use (entries). Beyond it a
 // call fails with PC_ERR_OUT_OF_MEMORY instead of growing without bound.
 constexpr long long kMaxRecord = 1LL << 30;
 
+// Entries of the candidate record (and of complete linkage's filter indices), the
+// pair list and average linkage's tile partials at a call's start.
+static long long start_cands(long long n) { return std::max<long long>(1 << 22, 4 * n); }
+static long long start_pairs(long long n) { return std::max<long long>(1 << 20, 2 * n); }
+constexpr long long kStartTiles = 1 << 22;
+
 // Scan workspace: two status words per 1024 elements of the longest scan of
 // the call (two arrays taken in turn), plus the tickets.
+static long long part_words(long long longest_scan) { return 2 * (longest_scan / 1024 + 1024) + 1; }
 static pc_status grow_part(pc_context *ctx, State &S, long long longest_scan) {
-  const long long need = 2 * (longest_scan / 1024 + 1024) + 1;
+  const long long need = part_words(longest_scan);
   const void *old = ctx->cur->part.p;
   const size_t old_bytes = ctx->cur->part.bytes;
   HIPCHK(grow(ctx, ctx->cur->part, (size_t)need * sizeof(long long)));
@@ -495,6 +475,32 @@ static pc_status grow_cand(pc_context *ctx, State &S, long long cap) {
   return grow_part(ctx, S, std::max<long long>(cc, 2LL * S.n + 64));
 }
 
+// What the call's buffers hold at its start, as hac_impl grows them (the records
+// grow further on demand).
+size_t pc_hac_workspace_bytes(int64_t n, int32_t d, int32_t linkage, const pc_options *opt) {
+  if (n < 1 || d < 1 || d > kMaxDim || n > 2147483646LL || linkage < 0 || linkage > 3) return 0;
+  if (opt && (opt->precision < 0 || opt->precision > 2)) return 0;
+  State S;
+  const bool gram = route_of(n, d, linkage, !opt || opt->prune).gram, pts = !centroid_link(linkage);
+  size_t bytes = layout(S, nullptr, n, d, linkage, gram, true, opt ? opt->precision : 0);
+  const long long cand = pts || gram ? start_cands(n) : 0, pairs = pts ? start_pairs(n) : 0;
+  if (cand) bytes += (size_t)cand * kCandBytes + 1024;
+  bytes += (size_t)part_words(std::max<long long>({cand, pairs, 2 * n + 64})) * sizeof(long long);
+  if (pts) {
+    bytes += (size_t)pairs * kPairBytes + 1024;
+    bytes += (linkage == kAverage ? (size_t)kStartTiles : 1) * sizeof(double);
+    bytes += (linkage == kComplete ? (size_t)cand : 1) * sizeof(int);
+    int cs = opt ? opt->cache_slots : -1;
+    if (cs < 0) cs = linkage == kAverage ? 64 : 0;
+    if (cs > 0) {
+      size_t cap = (size_t)1 << 16;
+      while (cap < (size_t)n * (size_t)cs && cap < ((size_t)1 << 31)) cap <<= 1;
+      bytes += 2 * cap * 2 * sizeof(unsigned long long);
+    }
+  }
+  return bytes;
+}
+
 // Windows of the scratch array for one allocation-free call: the layout
 // (`ws` bytes), the scan partials, then the candidate record, pair list, tile
 // partials or filter indices and the two cache tables in fixed shares of what
@@ -516,7 +522,7 @@ static pc_status carve_scratch(char *base, size_t ws, int64_t n, int linkage, bo
   // scan partials for the longest scan a record of this scratch can need
   const size_t left = total - off;
   const long long longest = std::max<long long>(2 * n + 64, (long long)(left / kPairBytes) + 1);
-  take(B.part, (size_t)(2 * (longest / 1024 + 1024) + 1) * sizeof(long long));
+  take(B.part, (size_t)part_words(longest) * sizeof(long long));
   if (off + (1u << 20) > total)
     return fail(PC_ERR_OUT_OF_MEMORY, "input too large for the allocation-free scratch buffer");
   const size_t rest = total - off - 8 * 256;  // alignment slack of the windows below
@@ -658,7 +664,7 @@ size_t matrix_extra_bytes(int64_t n, int32_t d, int32_t linkage, const pc_option
   State S;
   const bool gram = route_of(n, d, linkage, true).gram;
   const size_t ws = layout(S, nullptr, n, d, linkage, gram, true, opt ? opt->precision : 0);
-  const size_t part = (2 * ((size_t)(2 * n + 64) / 1024 + 1024) + 1) * sizeof(long long);
+  const size_t part = (size_t)part_words(2 * n + 64) * sizeof(long long);
   const size_t model = pc_hac_workspace_bytes(n, d, linkage, opt);
   return ws + part + need > model ? ws + part + need - model : 0;
 }
@@ -782,22 +788,18 @@ static pc_status hac_impl(pc_context *ctx, const float *points, int64_t n, int32
     cache_slots = 0;
   }
   if (centroid_link(linkage) && gram_used && !direct) {
-    pc_status st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, std::max<long long>(1 << 22, 4 * n),
-                                                 kCandBytes, 1024));
+    pc_status st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, start_cands(n), kCandBytes, 1024));
     if (st != PC_OK) return st;
     if (const char *e = getenv("PC_TEST_CAND_CAP")) S.cand_cap = std::min<long long>(S.cand_cap, atoll(e));
   }
   if (!centroid_link(linkage) && !direct) {
-    pc_status st = grow_pairs(ctx, S, initial_cap(ctx, ctx->cur->pairs, std::max<long long>(1 << 20, 2 * n),
-                                                  kPairBytes, 1024));
+    pc_status st = grow_pairs(ctx, S, initial_cap(ctx, ctx->cur->pairs, start_pairs(n), kPairBytes, 1024));
     if (st != PC_OK) return st;
-    st = grow_tiles(ctx, S, initial_cap(ctx, ctx->cur->tiles, linkage == kAverage ? (1 << 22) : 1,
-                                        sizeof(double), 0));
+    st = grow_tiles(ctx, S, initial_cap(ctx, ctx->cur->tiles, linkage == kAverage ? kStartTiles : 1, sizeof(double), 0));
     if (st != PC_OK) return st;
-    st = grow_fidx(ctx, S, initial_cap(ctx, ctx->cur->fidx, linkage == kComplete ? std::max<long long>(1 << 22, 4 * n) : 1,
-                                       sizeof(int), 0));
+    st = grow_fidx(ctx, S, initial_cap(ctx, ctx->cur->fidx, linkage == kComplete ? start_cands(n) : 1, sizeof(int), 0));
     if (st != PC_OK) return st;
-    st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, std::max<long long>(1 << 22, 4 * n), kCandBytes, 1024));
+    st = grow_cand(ctx, S, initial_cap(ctx, ctx->cur->cand, start_cands(n), kCandBytes, 1024));
     if (st != PC_OK) return st;
     // test hooks: shrink the candidate record / pair list to exercise their
     // overflow paths (capacities only ever limit, never extend, the buffers)
