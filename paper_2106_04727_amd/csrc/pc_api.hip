@@ -595,6 +595,8 @@ static int scan_max(int d) {
 //   32K points d = 10, complete uniform / average blobs: 8192 15.3 / 16.8, 12288 13.7 / 14.4,
 //     16384 13.3 / 14.4 (all points, both on blobs: 23.8 / 26.1)
 //   200K points d = 5 complete: 8192 174, 16384 119, 32768 83; 250K d = 10 average: 16384 136, 24576 133, 32768 137
+//   1M points, none against the rule, s: d = 5 complete uniform 14.7 / 2.6, blobs 3.3 / 1.6, average blobs
+//     2.6 / 0.56; d = 10 complete blobs 15.9 / 3.6; 300K d = 16 complete 3.9 / 0.36
 //   24K points d = 64: 12288 19.9 / 27.8, 16384 18.2 / 22.6, all points 20.3 / 23.9
 //   50K points d = 128: 16384 72.8 / 139, 32768 63.5 / 71.1, 49152 70.9 / 73.1
 // Two matrices of 32768 clusters are 17 GB (average linkage 19, and up to 27 while
